@@ -25,8 +25,10 @@
 // FiltPart checks the outputs of a flat partition: the split point against
 // the number of trues, Bij of the indices (as above), the class order, the
 // values moved, and stability (indices strictly increasing inside each class,
-// InvFiltPart item 3), the latter with a per-class running maximum carried
-// from tile to tile by an exclusive max-scan over tiles.
+// InvFiltPart item 3).  Where class order and stability hold, nothing can
+// repeat, so the bitmap is used only after one of them fails.
+#include <type_traits>
+
 #include "device.hpp"
 #include "host.hpp"
 
@@ -52,7 +54,6 @@ struct PropsState {
     unsigned int nrep;                 // repeated values listed (may exceed the list)
     // FiltPart
     unsigned long long fp_fv;          // least index failing bits 1..4
-    unsigned long long fp_true;        // number of trues
     unsigned int fp_bits;              // OR of failing sub-check bits (2..16)
     unsigned int pad1;
 };
@@ -87,8 +88,10 @@ struct PropsArgs {
     const uint32_t *fp_dst;
     const int64_t *fp_split;
     int32_t fp_mode;
-    int64_t *fp_tmax;     // per tile, two classes: max index value seen (kNoZ if none)
-    int64_t fp_tiles;
+    int64_t *fp_last;     // [2][kFpRanges] last index value of each class in a range (kNoZ if none)
+    unsigned long long *fp_count;   // [kFpRanges] trues of a range
+    int64_t fp_range;     // elements per range
+    int64_t fp_nranges;
 };
 
 __device__ __forceinline__ int64_t load_x(const void *x, int32_t x64, int64_t i) {
@@ -131,7 +134,6 @@ __global__ void props_init_kernel(PropsState *st, uint32_t *seen, uint32_t *dup,
         st->dup_found = 0;
         st->nrep = 0;
         st->fp_fv = kNone;
-        st->fp_true = 0;
         st->fp_bits = 0;
     }
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
@@ -803,10 +805,14 @@ __global__ __launch_bounds__(kPropsBlock) void props_missing_kernel(PropsArgs a)
 }
 
 // ---------------------------------------------------------------- FiltPart --
-// One wave per tile of 64 x 64 elements, one element per lane per row.
-constexpr int kFpRows = 64;
+// The array is cut into at most kFpRanges contiguous ranges, one per workgroup
+// of fp_check, in whole steps of kFpStep elements.
+constexpr int kFpThreads = 256;
+constexpr int kFpWaves = kFpThreads / kWave;
+constexpr int kFpRows = 8;            // rows of 64 elements a wave holds at once
+constexpr int64_t kFpStep = static_cast<int64_t>(kFpThreads) * kFpRows;
+constexpr int64_t kFpRanges = 2048;   // 8 workgroups per CU
 constexpr int64_t kNoZ = INT64_MIN;   // no earlier kept element of the class
-constexpr int64_t kFpTile = kFpRows * kWave;
 
 struct FpElem {
     bool c;        // predicate
@@ -816,166 +822,316 @@ struct FpElem {
 };
 
 template <class Pred>
-__device__ __forceinline__ FpElem fp_elem(const PropsArgs &a, const Pred &pred, int64_t i) {
-    FpElem e;
+__device__ __forceinline__ bool fp_true(const PropsArgs &a, const Pred &pred, int64_t i) {
     uint32_t key = 0;
     uint8_t fl = 0;
     if constexpr (Pred::kUsesFlags) fl = pred.flags[i];
     else key = a.fp_src[i];
-    e.c = pred(key, fl);
+    return pred(key, fl);
+}
+
+template <class Pred>
+__device__ __forceinline__ FpElem fp_elem(const PropsArgs &a, const Pred &pred, int64_t i) {
+    FpElem e;
+    e.c = fp_true(a, pred, i);
     e.kept = a.fp_mode == IXP_MODE_PARTITION || e.c;
     e.cls = a.fp_mode == IXP_MODE_PARTITION ? (e.c ? 1 : 0) : 1;
     e.z = load_x(a.x, a.x64, i);
     return e;
 }
 
-// Tile maxima of the index values per class (for the carried running max;
-// kNoZ when the tile has no kept element of the class) and the number of
-// trues.
-template <class Pred>
-__global__ __launch_bounds__(kPropsBlock) void fp_tile_max_kernel(PropsArgs a, Pred pred) {
-    const int lane = threadIdx.x & 63;
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * (kPropsBlock / 64) + wave_id();
-    if (t >= a.fp_tiles) return;
-    int64_t m0 = kNoZ, m1 = kNoZ;
-    unsigned long long nt = 0;
-    for (int r = 0; r < kFpRows; ++r) {
-        const int64_t i = t * kFpTile + static_cast<int64_t>(r) * kWave + lane;
-        if (i >= a.n) break;
-        const FpElem e = fp_elem(a, pred, i);
-        nt += e.c ? 1 : 0;
-        if (!e.kept) continue;
-        if (e.cls == 0) m0 = e.z > m0 ? e.z : m0;
-        else m1 = e.z > m1 ? e.z : m1;
-    }
+// True when the element takes part in FiltPart's bijection (its index lies in
+// the range the outputs cover).
+__device__ __forceinline__ bool fp_inserts(const PropsArgs &a, const FpElem &e, int64_t split) {
+    return a.fp_mode == IXP_MODE_PARTITION ? (0 <= e.z && e.z < a.n)
+                                           : (e.c && 0 <= e.z && e.z < split && e.z < a.n);
+}
+
+__device__ __forceinline__ int64_t wave_max_i64(int64_t v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
-        const int64_t o0 = __shfl_xor(m0, off, 64), o1 = __shfl_xor(m1, off, 64);
-        m0 = o0 > m0 ? o0 : m0;
-        m1 = o1 > m1 ? o1 : m1;
+        const int64_t o = __shfl_xor(v, off, kWave);
+        v = o > v ? o : v;
     }
-    nt = wave_sum_u64(nt);
-    if (lane == 0) {
-        a.fp_tmax[2 * t] = m0;
-        a.fp_tmax[2 * t + 1] = m1;
-        if (nt) atomicAdd(&a.st->fp_true, nt);
-    }
+    return v;
 }
 
-// Exclusive running max over tiles, per class (one workgroup, chunks of 1024).
-__global__ __launch_bounds__(1024) void fp_tile_scan_kernel(PropsArgs a) {
-    __shared__ int64_t buf[2][2][1024];
-    int64_t carry0 = kNoZ, carry1 = kNoZ;
-    for (int64_t c0 = 0; c0 < a.fp_tiles; c0 += 1024) {
-        const int64_t t = c0 + threadIdx.x;
-        int64_t v0 = t < a.fp_tiles ? a.fp_tmax[2 * t] : kNoZ;
-        int64_t v1 = t < a.fp_tiles ? a.fp_tmax[2 * t + 1] : kNoZ;
-        int cur = 0;
-        buf[cur][0][threadIdx.x] = v0;
-        buf[cur][1][threadIdx.x] = v1;
-        __syncthreads();
-        for (int off = 1; off < 1024; off <<= 1) {
-            int64_t x0 = buf[cur][0][threadIdx.x], x1 = buf[cur][1][threadIdx.x];
-            if (static_cast<int>(threadIdx.x) >= off) {
-                const int64_t y0 = buf[cur][0][threadIdx.x - off], y1 = buf[cur][1][threadIdx.x - off];
-                x0 = y0 > x0 ? y0 : x0;
-                x1 = y1 > x1 ? y1 : x1;
-            }
-            buf[cur ^ 1][0][threadIdx.x] = x0;
-            buf[cur ^ 1][1][threadIdx.x] = x1;
-            cur ^= 1;
-            __syncthreads();
-        }
-        // exclusive = inclusive of the previous thread, combined with the carry
-        int64_t e0 = threadIdx.x > 0 ? buf[cur][0][threadIdx.x - 1] : kNoZ;
-        int64_t e1 = threadIdx.x > 0 ? buf[cur][1][threadIdx.x - 1] : kNoZ;
-        e0 = carry0 > e0 ? carry0 : e0;
-        e1 = carry1 > e1 ? carry1 : e1;
-        const int64_t last0 = buf[cur][0][1023], last1 = buf[cur][1][1023];
-        __syncthreads();
-        if (t < a.fp_tiles) {
-            a.fp_tmax[2 * t] = e0;
-            a.fp_tmax[2 * t + 1] = e1;
-        }
-        carry0 = last0 > carry0 ? last0 : carry0;
-        carry1 = last1 > carry1 ? last1 : carry1;
-    }
+// A value that is the same in every lane, moved to scalar registers.
+__device__ __forceinline__ int64_t uniform_i64(int64_t v) {
+    return static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(v), 0));
 }
 
-// Per element: Bij range part and bitmap insertion (bit 2), class order
-// (bit 4), stability against the running max (bit 8), values (bit 16).
+// Per range and class, the index value of the range's last kept element (kNoZ
+// if none): what the next range's first element is compared with.  Searched
+// backwards from the range's end, so it reads a few hundred keys of a range
+// unless a class is rare in it.  With `init` it also clears the state (a call
+// that checks FiltPart alone launches no props_init).
 template <class Pred>
-__global__ __launch_bounds__(kPropsBlock) void fp_check_kernel(PropsArgs a, Pred pred) {
-    const int lane = threadIdx.x & 63;
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * (kPropsBlock / 64) + wave_id();
-    if (t >= a.fp_tiles) return;
-    const int64_t split = *a.fp_split;
-    const int64_t ylen = a.fp_mode == IXP_MODE_PARTITION ? a.n : split;
-    int64_t run0 = a.fp_tmax[2 * t], run1 = a.fp_tmax[2 * t + 1];
-    unsigned long long cand = kNone;
-    uint32_t bits = 0;
-    bool dup_seen = false;
-    for (int r = 0; r < kFpRows; ++r) {
-        const int64_t i = t * kFpTile + static_cast<int64_t>(r) * kWave + lane;
-        const bool live = i < a.n;
+__global__ __launch_bounds__(kFpThreads) void fp_last_kernel(PropsArgs a, Pred pred, int init) {
+    __shared__ int64_t found[kFpWaves][2];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = wave_id();
+    const int64_t b = blockIdx.x;
+    if (init && b == 0 && tid == 0) {
+        a.st->dup_found = 0;
+        a.st->fp_fv = kNone;
+        a.st->fp_bits = 0;
+    }
+    const int64_t e0 = b * a.fp_range;
+    const int64_t e1 = e0 + a.fp_range < a.n ? e0 + a.fp_range : a.n;
+    const bool part = a.fp_mode == IXP_MODE_PARTITION;
+    int64_t last[2] = {-1, -1};   // greatest index of each class found so far (uniform)
+    int64_t hi = e1;
+    // the first step takes 256 elements, one per thread; the later ones kFpStep
+    for (int per = 1; hi > e0 && (last[1] < 0 || (part && last[0] < 0)); per = kFpRows) {
+        const int64_t lo = hi - static_cast<int64_t>(per) * kFpThreads > e0
+                               ? hi - static_cast<int64_t>(per) * kFpThreads : e0;
+        int64_t m[2] = {-1, -1};
+#pragma unroll
+        for (int r = 0; r < kFpRows; ++r) {
+            const int64_t i = lo + r * kFpThreads + tid;
+            if (r < per && i < hi) {
+                const bool c = fp_true(a, pred, i);
+                if (c) m[1] = i;
+                else if (part) m[0] = i;
+            }
+        }
+        m[0] = wave_max_i64(m[0]);
+        m[1] = wave_max_i64(m[1]);
+        if (lane == 0) {
+            found[wave][0] = m[0];
+            found[wave][1] = m[1];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            int64_t x = -1;
+            for (int w = 0; w < kFpWaves; ++w) x = found[w][k] > x ? found[w][k] : x;
+            if (last[k] < 0) last[k] = x;
+        }
+        __syncthreads();
+        hi = lo;
+    }
+    if (tid < 2) a.fp_last[tid * kFpRanges + b] = last[tid] >= 0 ? load_x(a.x, a.x64, last[tid]) : kNoZ;
+}
+
+// The general test of one wave's elements [w0, e1), at most kFpRows rows of 64,
+// a row at a time: Bij's range part (bit 2), class order (bit 4), stability
+// (bit 8) and the values moved (bit 16).  run[k] is the index value of the
+// last kept element of class k before w0 (kNoZ if none).
+//
+// Stability compares an element with its predecessor in the class.  Up to the
+// first failure the class is strictly increasing, so its running maximum is
+// the predecessor: the least failing index is that of a comparison with the
+// maximum of all earlier elements.  The predecessor inside a row comes from one
+// ballot per class and a lane permute.
+template <class Pred>
+__device__ __forceinline__ void fp_general(const PropsArgs &a, const Pred &pred, int64_t w0, int64_t e1,
+                                                     int64_t split, int64_t run0, int64_t run1,
+                                                     unsigned long long *cand, uint32_t *bits) {
+    const int lane = lane_id();
+    const bool part = a.fp_mode == IXP_MODE_PARTITION;
+    const int64_t ylen = part ? a.n : split;
+#pragma unroll 1
+    for (int r = 0; r < kFpRows && w0 + r * kWave < e1; ++r) {
+        const int64_t i = w0 + r * kWave + lane;
+        const bool live = i < e1;
         FpElem e{false, false, 0, 0};
         if (live) e = fp_elem(a, pred, i);
+        const bool kept = live && e.kept;
+        const uint64_t m1 = ballot(kept && e.cls == 1), m0 = ballot(kept && e.cls == 0);
+        const uint64_t below = (e.cls ? m1 : m0) & ((1ull << lane) - 1);
+        const int64_t pz = __shfl(e.z, below ? 63 - __builtin_clzll(below) : 0, kWave);
+        const int64_t prev = below ? pz : (e.cls ? run1 : run0);
         uint32_t bad = 0;
-        if (live) {
-            if (a.fp_mode == IXP_MODE_PARTITION) {
-                if (!(0 <= e.z && e.z < a.n)) bad |= 2;
-                else insert_value<false>(a, e.z, &dup_seen);
-                if ((e.z < split) != e.c) bad |= 4;
-            } else if (e.c) {
-                if (!(0 <= e.z && e.z < split) || e.z >= a.n) bad |= 2;
-                else insert_value<false>(a, e.z, &dup_seen);
-            } else if (0 <= e.z && e.z < split) {
-                bad |= 2;
-            }
-            if (e.kept && 0 <= e.z && e.z < ylen && e.z < a.n && a.fp_dst[e.z] != a.fp_src[i]) bad |= 16;
+        if (part) {
+            if (!(0 <= e.z && e.z < a.n)) bad |= 2;
+            if ((e.z < split) != e.c) bad |= 4;
+        } else if (e.c) {
+            if (!(0 <= e.z && e.z < split) || e.z >= a.n) bad |= 2;
+        } else if (0 <= e.z && e.z < split) {
+            bad |= 2;
         }
-        // running max of earlier kept elements of the same class: an
-        // inclusive max-scan over the lanes of this row, per class
-        const int64_t mine0 = live && e.kept && e.cls == 0 ? e.z : kNoZ;
-        const int64_t mine1 = live && e.kept && e.cls == 1 ? e.z : kNoZ;
-        int64_t s0 = mine0, s1 = mine1;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int64_t o0 = __shfl_up(s0, off, 64), o1 = __shfl_up(s1, off, 64);
-            if (lane >= off) {
-                s0 = o0 > s0 ? o0 : s0;
-                s1 = o1 > s1 ? o1 : s1;
-            }
+        if (kept && 0 <= e.z && e.z < ylen && e.z < a.n && a.fp_dst[e.z] != a.fp_src[i]) bad |= 16;
+        if (kept && prev != kNoZ && !(e.z > prev)) bad |= 8;
+        if (bad && live) {
+            *bits |= bad;
+            if (static_cast<unsigned long long>(i) < *cand) *cand = static_cast<unsigned long long>(i);
         }
-        int64_t ex0 = __shfl_up(s0, 1, 64), ex1 = __shfl_up(s1, 1, 64);
-        if (lane == 0) { ex0 = kNoZ; ex1 = kNoZ; }
-        ex0 = run0 > ex0 ? run0 : ex0;
-        ex1 = run1 > ex1 ? run1 : ex1;
-        if (live && e.kept) {
-            const int64_t before = e.cls == 0 ? ex0 : ex1;
-            if (before != kNoZ && !(e.z > before)) bad |= 8;
-        }
-        const int64_t r0 = __shfl(s0, 63, 64), r1 = __shfl(s1, 63, 64);
-        run0 = r0 > run0 ? r0 : run0;
-        run1 = r1 > run1 ? r1 : run1;
-        if (bad) {
-            bits |= bad;
-            if (static_cast<unsigned long long>(i) < cand) cand = i;
-        }
-    }
-    cand = wave_min_u64(cand);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) bits |= __shfl_xor(bits, off, 64);
-    const bool any_dup = ballot(dup_seen) != 0;
-    if (lane == 0) {
-        if (cand != kNone) atomicMin(&a.st->fp_fv, cand);
-        if (bits) atomicOr(&a.st->fp_bits, bits);
-        if (any_dup) atomicOr(&a.st->dup_found, 1u);
+        if (m1) run1 = static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(e.z), 63 - __builtin_clzll(m1)));
+        if (m0) run0 = static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(e.z), 63 - __builtin_clzll(m0)));
     }
 }
 
-// FiltPart's repeats: value inserted for element i, if any (same rule as
-// fp_check_kernel).
+// Every element once.  Workgroup b takes range b in steps of kFpStep elements,
+// a wave 512 of them; ranges, steps and waves hand on the index value of each
+// class's last element.
+//
+// In a correct partition the index values of each class simply count on, so a
+// wave first makes one comparison per element with that count (the sides of
+// the split are then a matter of where the counts start and end) and one of
+// the value moved; only a wave where that fails, or whose elements are not all
+// there, takes the general test.
+//
+// Injectivity needs no bitmap here: when the class order and stability hold,
+// the classes' index values are disjoint and strictly increasing, so nothing
+// repeats.  fp_insert looks for repeats only after a failure of one of the
+// two; this kernel clears the bitmaps it would use.
+//
+// Bound by memory: src, X and the gathered dst are read once (12 bytes per
+// element with int32 indices, the gather being two ascending streams).  2^24
+// int32 keys and indices: 45 us (4.5 TB/s); a global bitmap with an atomic per
+// element and a 64-bit max-scan per row took 995 us.
+template <bool X64, class Pred>
+__global__ __launch_bounds__(kFpThreads) void fp_check_kernel(PropsArgs a, Pred pred) {
+    using Z = typename std::conditional<X64, int64_t, int32_t>::type;
+    __shared__ int64_t sh_in[2];
+    __shared__ int64_t wlast[2][kFpWaves][2];   // by parity of the step
+    __shared__ unsigned long long wcount[kFpWaves];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = wave_id();
+    const int64_t b = blockIdx.x;
+    const int64_t e0 = b * a.fp_range;
+    const int64_t e1 = e0 + a.fp_range < a.n ? e0 + a.fp_range : a.n;
+    const bool part = a.fp_mode == IXP_MODE_PARTITION;
+    const int64_t split = *a.fp_split;
+    const Z *x = static_cast<const Z *>(a.x);
+    // last value of each class before this range, 64 ranges at a time
+    if (wave < 2) {
+        int64_t in = kNoZ;
+        for (int64_t j = b - 1; j >= 0; j -= kWave) {
+            const int64_t v = j - lane >= 0 ? a.fp_last[wave * kFpRanges + j - lane] : kNoZ;
+            const uint64_t m = ballot(v != kNoZ);
+            if (m) {
+                in = static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(v), __builtin_ctzll(m)));
+                break;
+            }
+        }
+        if (lane == 0) sh_in[wave] = in;
+    }
+    for (int64_t w = (e0 >> 5) + tid; w < ((e1 + 31) >> 5); w += kFpThreads) {
+        a.seen[w] = 0;
+        a.dup[w] = 0;
+    }
+    __syncthreads();
+    // index values that fit both the type and the array end before zmax, those
+    // of the trues before ymax1, those read from dst before ymax
+    const int64_t zmax = X64 || a.n < (int64_t{1} << 31) ? a.n : (int64_t{1} << 31);
+    const int64_t ymax1 = split < zmax ? split : zmax;
+    const int64_t ymax = part ? zmax : ymax1;
+    int64_t carry[2] = {uniform_i64(sh_in[0]), uniform_i64(sh_in[1])};
+    unsigned long long cand = kNone, trues = 0;
+    uint32_t bits = 0;
+    int par = 0;
+    for (int64_t base = e0; base < e1; base += kFpStep, par ^= 1) {
+        const int64_t w0 = base + static_cast<int64_t>(wave) * (kFpRows * kWave);
+        const bool whole = w0 + kFpRows * kWave <= e1 && ymax > 0;   // (wave-uniform)
+        uint32_t src[kFpRows], dst[kFpRows];
+        Z z[kFpRows];
+        uint64_t m1[kFpRows];   // trues of a row
+        int64_t p0 = -1, p1 = -1;   // this wave's last element of each class
+        if (whole) {
+            uint8_t fl[kFpRows];
+#pragma unroll
+            for (int r = 0; r < kFpRows; ++r) {
+                src[r] = __builtin_nontemporal_load(a.fp_src + w0 + r * kWave + lane);
+                z[r] = __builtin_nontemporal_load(x + w0 + r * kWave + lane);
+                fl[r] = 0;
+                if constexpr (Pred::kUsesFlags) fl[r] = pred.flags[w0 + r * kWave + lane];
+            }
+#pragma unroll
+            for (int r = 0; r < kFpRows; ++r) {
+                const bool in = 0 <= z[r] && z[r] < ymax;
+                dst[r] = a.fp_dst[in ? z[r] : Z{0}];
+                m1[r] = ballot(pred(src[r], fl[r]));
+                const int64_t i0 = w0 + r * kWave + 63;
+                if (m1[r]) p1 = i0 - __builtin_clzll(m1[r]);
+                if (~m1[r]) p0 = i0 - __builtin_clzll(~m1[r]);
+                trues += static_cast<uint32_t>(__builtin_popcountll(m1[r]));
+            }
+        } else {
+#pragma unroll 1
+            for (int r = 0; r < kFpRows && w0 + r * kWave < e1; ++r) {
+                const int64_t i = w0 + r * kWave + lane;
+                const bool c = i < e1 && fp_true(a, pred, i);
+                const uint64_t t = ballot(c), f = ballot(i < e1 && !c);
+                const int64_t i0 = w0 + r * kWave + 63;
+                if (t) p1 = i0 - __builtin_clzll(t);
+                if (f) p0 = i0 - __builtin_clzll(f);
+                trues += static_cast<uint32_t>(__builtin_popcountll(t));
+            }
+        }
+        if (!part) p0 = -1;
+        if (lane < 2) {
+            const int64_t p = lane ? p1 : p0;
+            wlast[par][wave][lane] = p >= 0 ? static_cast<int64_t>(x[p]) : kNoZ;
+        }
+        __syncthreads();
+        int64_t run0 = carry[0], run1 = carry[1];
+#pragma unroll
+        for (int w = 0; w < kFpWaves; ++w) {
+            const int64_t v0 = uniform_i64(wlast[par][w][0]), v1 = uniform_i64(wlast[par][w][1]);
+            if (v0 != kNoZ) {
+                carry[0] = v0;
+                if (w < wave) run0 = v0;
+            }
+            if (v1 != kNoZ) {
+                carry[1] = v1;
+                if (w < wave) run1 = v1;
+            }
+        }
+        bool good = whole;
+        if (whole) {
+            int n1 = 0;   // trues of the rows before
+            bool ok = true;
+#pragma unroll
+            for (int r = 0; r < kFpRows; ++r) {
+                const bool c = (m1[r] >> lane) & 1u;
+                const int k1 = n1 + static_cast<int>(rank_below(m1[r]));
+                const Z want = c ? static_cast<Z>(run1 + 1) + k1 : static_cast<Z>(run0 + 1) + (r * kWave + lane - k1);
+                const bool keep = part | c;
+                ok &= keep ? (z[r] == want) & (dst[r] == src[r]) : !(0 <= z[r] && z[r] < split);
+                n1 += __builtin_popcountll(m1[r]);
+            }
+            const int n0 = part ? kFpRows * kWave - n1 : 0;
+            good = ballot(ok) == ~0ull && (n1 == 0 || (run1 >= 0 && run1 + n1 < ymax1)) &&
+                   (n0 == 0 || (run0 >= 0 && run0 >= split - 1 && run0 + n0 < zmax));
+        }
+        if (!good) fp_general(a, pred, w0, e1, split, run0, run1, &cand, &bits);
+    }
+    if (lane == 0) wcount[wave] = trues;   // (uniform: counted by ballots)
+    if (ballot(bits != 0)) {
+        cand = wave_min_u64(cand);
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) bits |= __shfl_xor(bits, off, kWave);
+        if (lane == 0) {
+            atomicMin(&a.st->fp_fv, cand);
+            atomicOr(&a.st->fp_bits, bits);
+        }
+    }
+    __syncthreads();
+    // one store per range: an atomic on one total would serialise the ranges
+    if (tid == 0) {
+        unsigned long long t = 0;
+        for (int w = 0; w < kFpWaves; ++w) t += wcount[w];
+        a.fp_count[b] = t;
+    }
+}
+
+// After a failed class order or stability check, repeats are possible: the
+// bitmap insertions of the elements that take part in the bijection.
+template <class Pred>
+__global__ __launch_bounds__(kPropsBlock) void fp_insert_kernel(PropsArgs a, Pred pred) {
+    if (!(a.st->fp_bits & 12u)) return;
+    const int64_t split = *a.fp_split;
+    bool dup_seen = false;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < a.n; i += stride) {
+        const FpElem e = fp_elem(a, pred, i);
+        if (fp_inserts(a, e, split)) insert_value<false>(a, e.z, &dup_seen);
+    }
+    if (ballot(dup_seen) != 0 && (threadIdx.x & 63) == 0) atomicOr(&a.st->dup_found, 1u);
+}
+
+// FiltPart's repeats, among the values fp_insert inserted.
 template <class Pred>
 __global__ __launch_bounds__(kPropsBlock) void fp_first_kernel(PropsArgs a, Pred pred, int pass,
                                                                unsigned long long *target) {
@@ -985,9 +1141,7 @@ __global__ __launch_bounds__(kPropsBlock) void fp_first_kernel(PropsArgs a, Pred
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < a.n; i += stride) {
         const FpElem e = fp_elem(a, pred, i);
-        const bool ins = a.fp_mode == IXP_MODE_PARTITION ? (0 <= e.z && e.z < a.n)
-                                                         : (e.c && 0 <= e.z && e.z < split && e.z < a.n);
-        if (!ins || !is_dup(a, e.z)) continue;
+        if (!fp_inserts(a, e, split) || !is_dup(a, e.z)) continue;
         const uint64_t o = static_cast<uint64_t>(e.z - a.lo);
         if (pass == 0) {
             if (a.first64) atomicMin(a.first64 + o, static_cast<unsigned long long>(i));
@@ -1006,9 +1160,20 @@ __global__ __launch_bounds__(kPropsBlock) void fp_first_kernel(PropsArgs a, Pred
     }
 }
 
-// Writes the five verdicts.
+// Writes the five verdicts (one workgroup, which first adds up the ranges'
+// counts of trues for FiltPart).
 __global__ void props_finalize_kernel(PropsArgs a, ixp_verdict *out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    __shared__ unsigned long long wsum[1024 / kWave];
+    unsigned long long fp_trues = 0;
+    if (a.fp_nranges > 0) {
+        for (int64_t r = threadIdx.x; r < a.fp_nranges; r += blockDim.x) fp_trues += a.fp_count[r];
+        fp_trues = wave_sum_u64(fp_trues);
+        if ((threadIdx.x & (kWave - 1)) == 0) wsum[wave_id()] = fp_trues;
+        __syncthreads();
+        fp_trues = 0;
+        for (uint32_t w = 0; w < blockDim.x / kWave; ++w) fp_trues += wsum[w];
+    }
+    if (threadIdx.x != 0) return;
     const PropsState *st = a.st;
     for (int b = 0; b < 5; ++b) {
         out[b].holds = 1;
@@ -1034,18 +1199,19 @@ __global__ void props_finalize_kernel(PropsArgs a, ixp_verdict *out) {
     }
     if (a.mask & IXP_FILTPART) {
         uint32_t bits = st->fp_bits;
-        if (static_cast<int64_t>(st->fp_true) != *a.fp_split) bits |= 1u;
+        if (static_cast<int64_t>(fp_trues) != *a.fp_split) bits |= 1u;
         if (bits) fail(4, st->fp_fv != kNone ? static_cast<int64_t>(st->fp_fv) : a.n, bits);
     }
 }
 
 template <class Pred>
-int launch_filtpart(PropsArgs a, const Pred &pred, hipStream_t st, int grid) {
-    const uint32_t tb = static_cast<uint32_t>(ceil_div(a.fp_tiles, kPropsBlock / 64));
-    if (a.fp_tiles > 0) {
-        IXP_LAUNCH("fp_tile_max", (fp_tile_max_kernel<Pred>), dim3(tb), dim3(kPropsBlock), 0, st, a, pred);
-        IXP_LAUNCH("fp_tile_scan", fp_tile_scan_kernel, dim3(1), dim3(1024), 0, st, a);
-        IXP_LAUNCH("fp_check", (fp_check_kernel<Pred>), dim3(tb), dim3(kPropsBlock), 0, st, a, pred);
+int launch_filtpart(PropsArgs a, const Pred &pred, hipStream_t st, int grid, bool init) {
+    if (a.fp_nranges > 0) {
+        const dim3 ranges(static_cast<uint32_t>(a.fp_nranges));
+        IXP_LAUNCH("fp_last", (fp_last_kernel<Pred>), ranges, dim3(kFpThreads), 0, st, a, pred, init ? 1 : 0);
+        if (a.x64) IXP_LAUNCH("fp_check", (fp_check_kernel<true, Pred>), ranges, dim3(kFpThreads), 0, st, a, pred);
+        else IXP_LAUNCH("fp_check", (fp_check_kernel<false, Pred>), ranges, dim3(kFpThreads), 0, st, a, pred);
+        IXP_LAUNCH("fp_insert", (fp_insert_kernel<Pred>), dim3(grid), dim3(kPropsBlock), 0, st, a, pred);
         IXP_LAUNCH("fp_first", (fp_first_kernel<Pred>), dim3(grid), dim3(kPropsBlock), 0, st, a, pred, 0,
                    &a.st->fp_fv);
         IXP_LAUNCH("fp_second", (fp_first_kernel<Pred>), dim3(grid), dim3(kPropsBlock), 0, st, a, pred, 1,
@@ -1089,6 +1255,9 @@ size_t bucket_bytes(int64_t n, int nb) {
 // The repeated-value list, its hash table and each slot's least index.
 constexpr size_t kRepBytes = 2 * static_cast<size_t>(kRepCap) * 8;
 
+// FiltPart's per-range records: two last values and a count each.
+constexpr size_t kFpBytes = static_cast<size_t>(kFpRanges) * 24;
+
 int64_t rcd_width(int64_t n, uint32_t mask, const ixp_prop_args *a) {
     int64_t w = 0;
     if ((mask & (IXP_INJ | IXP_BIJ)) && a) w = a->hi - a->lo;
@@ -1104,9 +1273,8 @@ extern "C" size_t ixp_check_props_workspace(int64_t n, uint32_t mask, const ixp_
     const int64_t w = rcd_width(n, mask, a);
     const size_t words = static_cast<size_t>((w + 127) / 128 * 4);   // multiple of 4 words
     const size_t first_bytes = static_cast<size_t>(w) * (n >= (int64_t{1} << 32) ? 8 : 4);
-    const int64_t tiles = (mask & IXP_FILTPART) ? ceil_div(n, kFpTile) : 0;
     return kPropsHeader + 2 * round_up(words * 4, 256) + round_up(first_bytes, 256) +
-           round_up(static_cast<size_t>(tiles) * 16, 256) + kRepBytes +
+           ((mask & IXP_FILTPART) ? kFpBytes : 0) + kRepBytes +
            bucket_bytes(n, buckets_for(n, mask, a));
 }
 
@@ -1169,11 +1337,15 @@ extern "C" int ixp_check_props(const void *x, int32_t x_t, int64_t n, uint32_t m
     }
     a.width = w;
     const size_t first_bytes = static_cast<size_t>(w) * (n >= (int64_t{1} << 32) ? 8 : 4);
-    a.fp_tmax = reinterpret_cast<int64_t *>(fp + round_up(first_bytes, 256));
-    a.fp_tiles = (mask & IXP_FILTPART) ? ceil_div(n, kFpTile) : 0;
+    a.fp_last = reinterpret_cast<int64_t *>(fp + round_up(first_bytes, 256));
+    a.fp_count = reinterpret_cast<unsigned long long *>(a.fp_last + 2 * kFpRanges);
+    if (mask & IXP_FILTPART) {
+        a.fp_range = ceil_div(ceil_div(n, kFpRanges), kFpStep) * kFpStep;
+        a.fp_nranges = n > 0 ? ceil_div(n, a.fp_range) : 0;
+    }
     a.nbuckets = buckets_for(n, mask, pa);
     a.bucketed = a.nbuckets > 0 ? 1 : 0;
-    char *rp = reinterpret_cast<char *>(a.fp_tmax) + round_up(static_cast<size_t>(a.fp_tiles) * 16, 256);
+    char *rp = reinterpret_cast<char *>(a.fp_last) + ((mask & IXP_FILTPART) ? kFpBytes : 0);
     a.rep = reinterpret_cast<uint64_t *>(rp);
     a.rep_min = reinterpret_cast<unsigned long long *>(a.rep + kRepCap);
     if (a.bucketed) {
@@ -1190,12 +1362,15 @@ extern "C" int ixp_check_props(const void *x, int32_t x_t, int64_t n, uint32_t m
     const int grid = kPass1Grid;
     const int64_t iwords = words > 0 ? words : 1;
     const uint32_t iblocks = static_cast<uint32_t>(ceil_div(iwords / 4 + 1, 256) < 4096 ? ceil_div(iwords / 4 + 1, 256) : 4096);
+    const uint32_t main_mask = mask & (IXP_RANGE | IXP_MONO | IXP_INJ | IXP_BIJ);
+    // FiltPart alone initialises what it uses itself
+    const bool fp_only = main_mask == 0 && a.fp_nranges > 0;
     // the chunked path reads no seen bitmap: only the dup bitmap is cleared
-    IXP_LAUNCH("props_init", props_init_kernel, dim3(iblocks), dim3(256), 0, st, a.st,
+    if (!fp_only)
+        IXP_LAUNCH("props_init", props_init_kernel, dim3(iblocks), dim3(256), 0, st, a.st,
                a.bucketed ? static_cast<uint32_t *>(nullptr) : a.seen, a.dup, words, a.rep_min);
     if (launch_status() != IXP_OK) return IXP_EHIP;
 
-    const uint32_t main_mask = mask & (IXP_RANGE | IXP_MONO | IXP_INJ | IXP_BIJ);
     if (main_mask && n > 0) {
         PropsArgs b = a;
         b.mask = main_mask;
@@ -1236,19 +1411,14 @@ extern "C" int ixp_check_props(const void *x, int32_t x_t, int64_t n, uint32_t m
         PropsArgs f = a;
         f.lo = 0;
         f.hi = n;
-        if (main_mask & (IXP_INJ | IXP_BIJ)) {
-            IXP_LAUNCH("props_init_fp", props_init_kernel, dim3(iblocks), dim3(256), 0, st,
-                       static_cast<PropsState *>(nullptr), a.seen, a.dup, words,
-                       static_cast<unsigned long long *>(nullptr));
-        }
         int rc = IXP_OK;
         switch (hp.kind) {
-        case IXP_PRED_MOD_EQ: rc = launch_filtpart(f, PredModEq{hp.M, hp.d, hp.r}, st, grid); break;
-        case IXP_PRED_LT: rc = launch_filtpart(f, PredLt{hp.s}, st, grid); break;
-        default: rc = launch_filtpart(f, PredFlags{hp.flags}, st, grid); break;
+        case IXP_PRED_MOD_EQ: rc = launch_filtpart(f, PredModEq{hp.M, hp.d, hp.r}, st, grid, fp_only); break;
+        case IXP_PRED_LT: rc = launch_filtpart(f, PredLt{hp.s}, st, grid, fp_only); break;
+        default: rc = launch_filtpart(f, PredFlags{hp.flags}, st, grid, fp_only); break;
         }
         if (rc != IXP_OK) return rc;
     }
-    IXP_LAUNCH("props_finalize", props_finalize_kernel, dim3(1), dim3(64), 0, st, a, d_out);
+    IXP_LAUNCH("props_finalize", props_finalize_kernel, dim3(1), dim3(a.fp_nranges > 0 ? 1024 : kWave), 0, st, a, d_out);
     return launch_status();
 }

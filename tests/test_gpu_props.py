@@ -219,6 +219,51 @@ def test_filtpart_on_partition_outputs_and_planted_faults(mode, idx_dtype):
         _fp_both(keys, op, gp, mode, ys, z, t, idx_dtype)
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 2047, 2048, 2049, 3 * 2048 + 1, 2048 * 2048 + 2049])
+def test_filtpart_steps_and_ranges(n, mode):
+    """FiltPart works through ranges of whole 2048-element steps (up to 2048
+    ranges), waves of 512 and rows of 64, each handing on the last index value
+    of a class: faults on both sides of those edges, classes that are missing
+    from whole ranges, and repeats, which need a broken order to exist."""
+    g = np.random.default_rng(n)
+    for flags in (g.integers(0, 2, n), np.ones(n), np.zeros(n), np.arange(n) == 0, np.arange(n) == n - 1):
+        flags = flags.astype(np.uint8)
+        op, gp = O.Pred.from_flags(flags), P.Pred.from_flags(torch.from_numpy(flags).to(DEV))
+        keys = W.int_keys(n, 93)
+        ys, idx, t = O.partition2(keys, op, mode)
+        assert _fp_both(keys, op, gp, mode, ys, idx, t, np.int32) == (1, -1, 0)
+        for p in sorted({0, 63, 64, 511, 512, 2047, 2048, 2 * 2048, n // 2, n - 2, n - 1}):
+            if not 0 <= p < n:
+                continue
+            for v in (-1, n, int(idx[max(p - 1, 0)]), int(idx[n - 1 - p])):
+                z = idx.copy()
+                z[p] = v
+                _fp_both(keys, op, gp, mode, ys, z, t, np.int64)
+            if n > 1 << 20:
+                break
+        if n > 1 << 20:
+            z = idx.copy()   # every check fails somewhere, with many repeats
+            z[g.integers(0, n, 5000)] = z[g.integers(0, n, 5000)]
+            _fp_both(keys, op, gp, mode, ys, z, t, np.int32)
+
+
+def test_filtpart_beside_the_other_checks():
+    """One call for FiltPart and Inj / Bij / Mono: FiltPart reuses their bitmaps."""
+    for n in (5000, 200_001):
+        keys = W.int_keys(n, 94)
+        ys, idx, t = O.partition2(keys, O.Pred.mod_eq(2, 0), 0)
+        z = idx.copy()
+        z[n // 3] = z[n // 7]
+        for x in (idx, z):
+            xt = torch.from_numpy(x).to(DEV)
+            fp = P.FiltPartArgs(torch.from_numpy(keys).to(DEV), torch.from_numpy(ys).to(DEV), P.Pred.mod_eq(2, 0),
+                                torch.tensor([t], device=DEV))
+            v = P.verdicts(P.check_props(xt, ALL4 | P.FILTPART, 0, n, 0, n, fp=fp))
+            assert v[4] == O.check_filtpart(keys, O.Pred.mod_eq(2, 0), 0, ys, x, t)
+            assert v[:4] == P.verdicts(P.check_props(xt, ALL4, 0, n, 0, n))[:4]
+
+
 def test_filtpart_checks_gpu_partition_output():
     x = W.f32_uniform(5_000_000, 91)
     gp = P.Pred.lt(0.37)
