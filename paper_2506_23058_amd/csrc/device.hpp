@@ -84,25 +84,39 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t b, int64_t nt) {
 // ---------------------------------------------------------------- predicates --
 // Keys travel as raw 32-bit words; each predicate interprets them.
 
-// x mod d == r with the floor modulus, for int32 x and 1 <= d < 2^32.
-// |x| mod d uses the direct-remainder method of Lemire, Kaser and Kurz
-// ("Faster Remainder by Direct Computation", 2019): with M = floor((2^64-1)/d)+1,
-// a mod d = high64((M * a mod 2^64) * d), exact for all 32-bit a and d.
+// x mod d == r with the floor modulus, for int32 x and 1 <= d < 2^32, as one
+// multiplication.  With u = x + 2^31 >= 0 and r' = (r + 2^31) mod d the
+// question is whether u - r' is a multiple of d that has not wrapped below 0.
+// Let d = 2^k e, e odd, and i the inverse of e mod 2^32: a 32-bit t is a
+// multiple of d exactly when rotr(t i, k) <= (2^32 - 1) / d, and then that is
+// the quotient (the exact-division test of Granlund and Montgomery, "Division
+// by Invariant Integers using Multiplication", 1994, section 9).  A wrapped t is
+// at least 2^32 - r', so the bound (2^32 - 1 - r') / d leaves it out too.
+// (|x| mod d by two 64-bit products took about 25 instructions, 7 of them
+// quarter-rate multiplications; this takes 4, one of them a multiplication:
+// the differentiable partition of 2^22 rows 222.9 -> 219.6 us, FiltPart of 2^24
+// keys 67.1 -> 64.7 us, 10^4 segmented rows 202.2 -> 200.3 us.)
 struct PredModEq {
     static constexpr bool kUsesFlags = false;
-    uint64_t M;
-    uint32_t d;
-    int64_t r;
+    uint32_t mul, add, rot, lim;   // true when rotr((x + add) mul, rot) < lim
     // the predicate of row k (this one does not depend on the row)
     __device__ __forceinline__ PredModEq at_row(int64_t) const { return *this; }
     __device__ __forceinline__ bool operator()(uint32_t bits, uint8_t) const {
-        const int32_t x = static_cast<int32_t>(bits);
-        const uint32_t a = x < 0 ? 0u - bits : bits;   // |x|, 2^31 for INT_MIN
-        const uint32_t m = static_cast<uint32_t>(__umul64hi(M * a, d));
-        const uint32_t fm = (x < 0 && m != 0) ? d - m : m;
-        return static_cast<int64_t>(fm) == r;
+        const uint32_t q = (bits + add) * mul;
+        return __builtin_amdgcn_alignbit(q, q, rot) < lim;
     }
 };
+
+inline PredModEq mod_eq_pred(uint32_t d, int64_t r) {
+    if (r < 0 || r >= static_cast<int64_t>(d)) return PredModEq{0, 0, 0, 0};   // never
+    if (d == 1) return PredModEq{0, 0, 0, 1};                                 // always
+    const uint32_t k = static_cast<uint32_t>(__builtin_ctz(d));
+    const uint32_t e = d >> k;
+    uint32_t inv = e;   // right in the low 3 bits; each step doubles them
+    for (int i = 0; i < 4; ++i) inv *= 2u - e * inv;
+    const uint32_t rr = static_cast<uint32_t>((static_cast<uint64_t>(r) + 0x80000000ull) % d);
+    return PredModEq{inv, 0x80000000u - rr, k, (0xFFFFFFFFu - rr) / d + 1};
+}
 
 // x < s in IEEE single precision (NaN compares false).
 struct PredLt {
@@ -135,17 +149,29 @@ struct PredLtRow {
     }
 };
 
-// x mod d == k mod d, floor moduli (k >= 0, so k mod d is the remainder).
+// x mod d == k mod d, floor moduli (0 <= k < 2^31, so k mod d is the remainder).
 struct PredModRow {
     static constexpr bool kUsesFlags = false;
-    PredModEq eq;
+    PredModEq eq;        // of the row number last given to at_row
+    uint32_t d;
+    uint32_t half;       // 2^31 mod d
+    uint32_t quo, rem;   // of 2^32 - 1 by d
     __device__ __forceinline__ PredModRow at_row(int64_t k) const {
         PredModRow p = *this;
-        p.eq.r = static_cast<int64_t>(static_cast<uint64_t>(k) % eq.d);
+        if (d > 1) {
+            const uint32_t r = static_cast<uint32_t>(k) % d;
+            const uint32_t rr = r >= d - half ? r - (d - half) : r + half;   // (r + 2^31) mod d
+            p.eq.add = 0x80000000u - rr;
+            p.eq.lim = quo + (rr > rem ? 0u : 1u);   // (2^32 - 1 - rr) / d + 1
+        }
         return p;
     }
     __device__ __forceinline__ bool operator()(uint32_t bits, uint8_t f) const { return eq(bits, f); }
 };
+
+inline PredModRow mod_row_pred(uint32_t d) {
+    return PredModRow{mod_eq_pred(d, 0), d, 0x80000000u % d, 0xFFFFFFFFu / d, 0xFFFFFFFFu % d};
+}
 
 // ---------------------------------------------------------- tile descriptors --
 // One 64-bit word per tile: status in bits 63..62, value in bits 61..0.

@@ -438,7 +438,7 @@ template <int VEC>
 int dispatch_pred(const FlatArgs &a, const HostPred &hp, int mode, int idx_t, hipStream_t st) {
     switch (hp.kind) {
     case IXP_PRED_MOD_EQ: {
-        PredModEq p{hp.M, hp.d, hp.r};
+        const PredModEq p = mod_eq_pred(hp.d, hp.r);
         return launch_flat<VEC>(a, p, mode, idx_t, st);
     }
     case IXP_PRED_LT: {

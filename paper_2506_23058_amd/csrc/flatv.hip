@@ -27,17 +27,17 @@ constexpr int64_t kVCountWaves = 8192;
 constexpr size_t kVHeader = 256;
 
 // ------------------------------------------------------------------ classes --
-// floor-mod(key, v) of an int32 key (the direct-remainder method of Lemire,
-// Kaser and Kurz, as for the modulus predicate).
+// floor-mod(key, V) of an int32 key: the low bits for V = 2 and 4; for V = 3
+// u = key + 2^31 has the key's floor modulus plus 2, and u / 3 is the high
+// half of u (2^33 + 1) / 3 by 2.
+template <int V>
 struct ClassMod {
     static constexpr bool kUsesBytes = false;
-    uint64_t M;
-    uint32_t d;
     __device__ __forceinline__ uint32_t operator()(uint32_t bits, uint8_t) const {
-        const int32_t x = static_cast<int32_t>(bits);
-        const uint32_t a = x < 0 ? 0u - bits : bits;
-        const uint32_t m = static_cast<uint32_t>(__umul64hi(M * a, d));
-        return (x < 0 && m != 0) ? d - m : m;
+        if (V != 3) return bits & static_cast<uint32_t>(V - 1);
+        const uint32_t u = bits ^ 0x80000000u;
+        const uint32_t m = u - 3u * (__umulhi(u, 0xAAAAAAABu) >> 1);
+        return m == 2 ? 0u : m + 1;
     }
 };
 
@@ -458,8 +458,7 @@ template <int V>
 int dispatch_v(const VArgs &a, const ixp_classes &c, int idx_t, hipStream_t st) {
     switch (c.kind) {
     case IXP_CLASS_MOD: {
-        ClassMod cl{~0ull / static_cast<uint32_t>(V) + 1, static_cast<uint32_t>(V)};
-        return launch_v<V>(a, cl, idx_t, st);
+        return launch_v<V>(a, ClassMod<V>{}, idx_t, st);
     }
     case IXP_CLASS_THRESH: {
         ClassThresh<V> cl{c.s[0], c.s[1], c.s[2]};

@@ -26,7 +26,6 @@ inline int launch_status() {
 // Validated, device-ready form of ixp_pred.
 struct HostPred {
     int kind;
-    uint64_t M;     // MOD_EQ: ceil(2^64 / d) mod 2^64
     uint32_t d;
     int64_t r;
     float s;
@@ -43,7 +42,6 @@ inline int check_pred(const ixp_pred *p, int32_t key_t, HostPred *out, int64_t n
     out->s = p->s;
     out->r = p->r;
     out->d = 1;
-    out->M = 0;
     out->row_s = p->row_s;
     switch (p->kind) {
     case IXP_PRED_MOD_ROW:
@@ -51,7 +49,6 @@ inline int check_pred(const ixp_pred *p, int32_t key_t, HostPred *out, int64_t n
         if (key_t != IXP_I32) return key_t == IXP_I64 ? IXP_EUNSUPPORTED : IXP_EINVAL;
         if (p->d < 1 || p->d > 0xFFFFFFFFll) return IXP_EINVAL;
         out->d = static_cast<uint32_t>(p->d);
-        out->M = ~0ull / out->d + 1;
         return IXP_OK;
     case IXP_PRED_LT:
         return key_t == IXP_F32 ? IXP_OK : IXP_EINVAL;

@@ -1413,7 +1413,7 @@ extern "C" int ixp_check_props(const void *x, int32_t x_t, int64_t n, uint32_t m
         f.hi = n;
         int rc = IXP_OK;
         switch (hp.kind) {
-        case IXP_PRED_MOD_EQ: rc = launch_filtpart(f, PredModEq{hp.M, hp.d, hp.r}, st, grid, fp_only); break;
+        case IXP_PRED_MOD_EQ: rc = launch_filtpart(f, mod_eq_pred(hp.d, hp.r), st, grid, fp_only); break;
         case IXP_PRED_LT: rc = launch_filtpart(f, PredLt{hp.s}, st, grid, fp_only); break;
         default: rc = launch_filtpart(f, PredFlags{hp.flags}, st, grid, fp_only); break;
         }

@@ -1023,10 +1023,10 @@ void set_layout(int64_t n, int64_t m, const int64_t *d_shape, const SegGeom &g, 
 
 int run(const SegArgs &a, const HostPred &hp, const SegGeom &g, int mode, int idx_t, hipStream_t st) {
     switch (hp.kind) {
-    case IXP_PRED_MOD_EQ: return launch_all(a, PredModEq{hp.M, hp.d, hp.r}, g, mode, idx_t, st);
+    case IXP_PRED_MOD_EQ: return launch_all(a, mod_eq_pred(hp.d, hp.r), g, mode, idx_t, st);
     case IXP_PRED_LT: return launch_all(a, PredLt{hp.s}, g, mode, idx_t, st);
     case IXP_PRED_LT_ROW: return launch_all(a, PredLtRow{hp.row_s, 0.f}, g, mode, idx_t, st);
-    case IXP_PRED_MOD_ROW: return launch_all(a, PredModRow{PredModEq{hp.M, hp.d, 0}}, g, mode, idx_t, st);
+    case IXP_PRED_MOD_ROW: return launch_all(a, mod_row_pred(hp.d), g, mode, idx_t, st);
     default: return launch_all(a, PredFlags{hp.flags}, g, mode, idx_t, st);
     }
 }

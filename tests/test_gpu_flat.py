@@ -223,3 +223,23 @@ def test_captured_graph_replays_match_eager(mode):
         assert torch.equal(got[1], ei)
         assert torch.equal(got[0][:nout], ek[:nout])
     del g
+
+
+@pytest.mark.parametrize("d", [1, 2, 3, 6, 12, 640, 2**16, 2**31 - 1, 2**31, 2**31 + 1, 3 * 2**30, 2**32 - 2, 2**32 - 1])
+def test_modulus_predicate_over_divisors(d):
+    """The one-multiplication test of x mod d == r, for odd, even and
+    power-of-two divisors up to 2^32 - 1, remainders at both ends of [0, d)
+    and outside it (never true), and keys around multiples of d."""
+    g = np.random.default_rng(d % 1000)
+    keys = g.integers(-2**31, 2**31, 6000)
+    near = np.clip(keys[:3000] // d * d + g.integers(-2, 3, 3000), -2**31, 2**31 - 1)
+    keys = np.concatenate([keys, near, [-2**31, -2**31 + 1, -1, 0, 1, 2**31 - 2, 2**31 - 1]]).astype(np.int32)
+    for r in sorted({0, 1, d // 2, d - 1, d, -1}):
+        run_both(keys, "mod", 0, torch.int64, d=d, r=r)
+    shape = g.integers(0, 9, 3000)
+    shape[-1] += len(keys) - shape.sum() if shape.sum() < len(keys) else 0
+    shape = shape[:np.searchsorted(np.cumsum(shape), len(keys), side="right")].astype(np.int64)
+    x = keys[:shape.sum()]
+    _, oi, ss, _ = P.segmented_partition(torch.from_numpy(x).to(DEV), torch.from_numpy(shape).to(DEV), P.Pred.mod_rows(d))
+    _, idx, seg, _ = O.partition2L_rows(x, shape, O.ROW_MOD, d, np.zeros(len(shape), np.float32), 0)
+    assert np.array_equal(oi.cpu().numpy(), idx) and np.array_equal(ss.cpu().numpy(), seg)
