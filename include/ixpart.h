@@ -234,9 +234,9 @@ size_t ixp_segmented_workspace(int64_t n, int64_t m, const ixp_tuning *tune);
  * out_keys is NULL.
  * A negative size or a size sum different from n is detected on the device:
  * the call then writes no output and ixp_read_error() on the same workspace
- * reports IXP_EINVAL.  Enqueues 6 kernels (shape scan, item records, counts
- * of the multi-item rows that the main kernel does not synchronise itself,
- * item scan, item bases, main), all stream-ordered with no host
+ * reports IXP_EINVAL.  Enqueues 5 to 8 kernels (shape scan and item records,
+ * counts of the items that the main kernel does not synchronise itself, item
+ * scan, item bases, main), all stream-ordered with no host
  * synchronisation: capturable into a HIP graph.  Under IXP_ROW_SYNC_WAIT the
  * main kernel's workgroups wait on one another's published counts; the wait
  * is bounded, so no workgroup depends on another being resident.
@@ -256,7 +256,7 @@ int ixp_segmented_partition(const void *keys, int32_t key_t, int64_t n,
  *                     or IXP_I64;
  *   ixp_mk_sgm_descr: d_out[o_k] = d_xs[k] for every non-empty row k, 0 at
  *                     every other position (mkSgmDescr), int64.
- * Workspace: ixp_mk_ii_workspace(n, m) bytes, 16-byte aligned.  3 kernels. */
+ * Workspace: ixp_mk_ii_workspace(n, m) bytes, 16-byte aligned.  2 or 4 kernels. */
 size_t ixp_mk_ii_workspace(int64_t n, int64_t m);
 int ixp_mk_ii(const int64_t *d_shape, int64_t m, int64_t n, void *out,
               int32_t out_t, void *ws, size_t ws_bytes, void *stream);

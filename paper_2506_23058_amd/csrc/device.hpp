@@ -98,6 +98,7 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t b, int64_t nt) {
 // keys 67.1 -> 64.7 us, 10^4 segmented rows 202.2 -> 200.3 us.)
 struct PredModEq {
     static constexpr bool kUsesFlags = false;
+    static constexpr bool kRow = false;
     uint32_t mul, add, rot, lim;   // true when rotr((x + add) mul, rot) < lim
     // the predicate of row k (this one does not depend on the row)
     __device__ __forceinline__ PredModEq at_row(int64_t) const { return *this; }
@@ -121,6 +122,7 @@ inline PredModEq mod_eq_pred(uint32_t d, int64_t r) {
 // x < s in IEEE single precision (NaN compares false).
 struct PredLt {
     static constexpr bool kUsesFlags = false;
+    static constexpr bool kRow = false;
     float s;
     __device__ __forceinline__ PredLt at_row(int64_t) const { return *this; }
     __device__ __forceinline__ bool operator()(uint32_t bits, uint8_t) const {
@@ -128,22 +130,36 @@ struct PredLt {
     }
 };
 
+// No predicate: for loads whose elements are tested later.
+struct PredNone {
+    static constexpr bool kUsesFlags = false;
+    __device__ __forceinline__ bool operator()(uint32_t, uint8_t) const { return false; }
+};
+
 // A caller-supplied flag array (partition2L's csL): true where the byte != 0.
 struct PredFlags {
     static constexpr bool kUsesFlags = true;
+    static constexpr bool kRow = false;
     const uint8_t *flags;
     __device__ __forceinline__ PredFlags at_row(int64_t) const { return *this; }
     __device__ __forceinline__ bool operator()(uint32_t, uint8_t f) const { return f != 0; }
 };
 
 // Predicates of the row number k (segmented calls): at_row(k) fixes k and
-// returns a predicate of the key alone.
+// returns a predicate of the key alone.  Where the elements of one wave belong
+// to many rows, row_word(k) is what the predicate needs to know of row k, and
+// in_row(bits, word) the predicate of a key in that row.
 // x < row_s[k] in IEEE single precision.
 struct PredLtRow {
     static constexpr bool kUsesFlags = false;
+    static constexpr bool kRow = true;
     const float *row_s;
     float s;
     __device__ __forceinline__ PredLtRow at_row(int64_t k) const { return PredLtRow{row_s, row_s[k]}; }
+    __device__ __forceinline__ uint32_t row_word(int64_t k) const { return __float_as_uint(row_s[k]); }
+    __device__ __forceinline__ bool in_row(uint32_t bits, uint32_t word) const {
+        return __uint_as_float(bits) < __uint_as_float(word);
+    }
     __device__ __forceinline__ bool operator()(uint32_t bits, uint8_t) const {
         return __uint_as_float(bits) < s;
     }
@@ -152,20 +168,29 @@ struct PredLtRow {
 // x mod d == k mod d, floor moduli (0 <= k < 2^31, so k mod d is the remainder).
 struct PredModRow {
     static constexpr bool kUsesFlags = false;
+    static constexpr bool kRow = true;
     PredModEq eq;        // of the row number last given to at_row
     uint32_t d;
     uint32_t half;       // 2^31 mod d
     uint32_t quo, rem;   // of 2^32 - 1 by d
-    __device__ __forceinline__ PredModRow at_row(int64_t k) const {
-        PredModRow p = *this;
+    __device__ __forceinline__ uint32_t row_word(int64_t k) const {   // (k + 2^31) mod d
+        const uint32_t r = static_cast<uint32_t>(k) % d;
+        return r >= d - half ? r - (d - half) : r + half;
+    }
+    __device__ __forceinline__ PredModEq of_word(uint32_t rr) const {
+        PredModEq p = eq;
         if (d > 1) {
-            const uint32_t r = static_cast<uint32_t>(k) % d;
-            const uint32_t rr = r >= d - half ? r - (d - half) : r + half;   // (r + 2^31) mod d
-            p.eq.add = 0x80000000u - rr;
-            p.eq.lim = quo + (rr > rem ? 0u : 1u);   // (2^32 - 1 - rr) / d + 1
+            p.add = 0x80000000u - rr;
+            p.lim = quo + (rr > rem ? 0u : 1u);   // (2^32 - 1 - rr) / d + 1
         }
         return p;
     }
+    __device__ __forceinline__ PredModRow at_row(int64_t k) const {
+        PredModRow p = *this;
+        p.eq = of_word(row_word(k));
+        return p;
+    }
+    __device__ __forceinline__ bool in_row(uint32_t bits, uint32_t word) const { return of_word(word)(bits, 0); }
     __device__ __forceinline__ bool operator()(uint32_t bits, uint8_t f) const { return eq(bits, f); }
 };
 

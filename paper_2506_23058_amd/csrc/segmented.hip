@@ -16,13 +16,16 @@
 //   [A_k + j*TILE, A_k + (j+1)*TILE) ∩ [o_k, o_k + s_k),
 // A_k = o_k rounded down to 32 (a 128-byte line) when that gives the row no
 // more items than rounding down to 4, else o_k rounded down to 4.
+// Where rows are short on average, rows of at most a quarter tile are packed:
+// an item holds the whole short rows that start in one window of 3 quarter
+// tiles (up to the next longer row, and inside one block of rows).
 // Kernels (all stream-ordered, capturable in one HIP graph):
 //   seg_shape -- (up to 16384 rows) row offsets, item offsets and item
 //                descriptors in one launch: each workgroup rescans the sizes
 //                before its rows; the last one validates the shape;
-//   seg_setup, seg_items -- (more rows) the same in two launches: one
-//                workgroup scans the shape, then the descriptors are written
-//                in parallel over items;
+//   seg_sizes, seg_rows, seg_records -- (more rows) the same in three launches
+//                over chunks of rows, each workgroup adding up the chunk
+//                totals before its own;
 //   seg_count -- one wave per 1024-element chunk counts the trues of the items
 //                whose row spans several items and is not synchronised in
 //                seg_main (partition), or of every item (filter), into a
@@ -67,9 +70,12 @@ struct alignas(16) SegItem {
     int32_t row;         // row k
     int32_t kind;        // bit 0: row fits one item; bit 1: first item of its row;
                          // bit 2: row synchronised in seg_main, with its item
-                         // count in bits 8..23 (tbase then holds o_k)
-    int64_t first;       // first item of the row (bit 2), else 0
+                         // count in bits 8..23 (tbase then holds o_k);
+                         // bit 3: packed item, the whole short rows [row, first)
+    int64_t first;       // first item of the row (bit 2), end row (bit 3), else 0
 };
+constexpr int32_t kOwnRows = 1 | 8;        // the item holds whole rows
+constexpr int32_t kPacked = 8;
 
 struct SegArgs {
     const uint32_t *keys;
@@ -96,10 +102,50 @@ struct SegArgs {
     int32_t mode;
     int32_t need_keys;
     int32_t row_sync;     // IXP_ROW_SYNC_COUNT, _WAIT or _NOWAIT
+    int64_t short_max;    // rows of at most this many elements are packed (0: none)
+    int64_t chunk_rows;   // rows per workgroup of seg_sizes / seg_rows / seg_records
+    int64_t nchunks;
+    int64_t *csum, *citems, *ccounted, *cbad;   // [kShapeChunks] of a chunk: elements, items, counted
+                                                // items, whether a size is negative
 };
 
-int64_t seg_max_items(int64_t n, int64_t m, int64_t tile) {
-    return ceil_div(n + 3 * m, tile) + m + 1;
+constexpr int64_t kShapeFusedRows = 16384;   // up to here the shape takes one launch (seg_shape)
+constexpr int kFusedPackShift = 8, kChunkPackShift = 12;
+constexpr int64_t kShapeChunks = 1024;
+
+// Packed rows have at most tile / 4 elements and start in one window of
+// 3 tile / 4, so an item of them spans less than a tile whatever their sizes.
+int64_t seg_max_items(int64_t n, int64_t m, int64_t tile, bool pack) {
+    const int64_t plain = ceil_div(n + 3 * m, tile) + m + 1;
+    if (!pack) return plain;
+    // long rows; windows, each cut once more by every long row and block edge
+    const int64_t longs = n / (tile / 4 + 1) < m ? n / (tile / 4 + 1) : m;
+    const int64_t edges = (m >> (m <= kShapeFusedRows ? kFusedPackShift : kChunkPackShift)) + 1;
+    const int64_t packed = n / (tile / 4 * 3) + 1 + longs + edges;
+    const int64_t bound = packed + (n + 3 * longs) / tile + longs + 2;
+    return bound < plain ? bound : plain;
+}
+
+// The items a row begins: 0 for an empty row and for a short row that joins
+// the item of the row before it (`prev` elements, 0 if the block of rows
+// holds no non-empty row before this one).
+__device__ __forceinline__ int64_t row_items(const SegArgs &a, int64_t o, int64_t sk, int64_t prev) {
+    if (sk <= 0) return 0;
+    if (sk <= a.short_max) {
+        // windows of 3 quarter tiles, counted in 32 bits (2^42 elements)
+        const int32_t q = a.tile_shift - 2;
+        return prev == 0 || prev > a.short_max ||
+               static_cast<uint32_t>((o - prev) >> q) / 3 != static_cast<uint32_t>(o >> q) / 3;
+    }
+    return (o + sk - (o & ~int64_t{3}) + a.tile - 1) >> a.tile_shift;
+}
+
+// True when a row of nit items has its items counted by the counting pass.
+__device__ __forceinline__ bool row_synced(const SegArgs &a, int64_t nit) {
+    return a.mode == IXP_MODE_PARTITION && a.row_sync != IXP_ROW_SYNC_COUNT && nit > 1 && nit <= kSibMax;
+}
+__device__ __forceinline__ bool row_counted(const SegArgs &a, int64_t nit) {
+    return a.mode != IXP_MODE_PARTITION || (nit > 1 && !row_synced(a, nit));
 }
 
 // Rows are cut into items of `tile` elements from the 16-byte group holding
@@ -114,10 +160,7 @@ __device__ __forceinline__ int64_t row_first_base(int64_t o, int64_t sk, int64_t
     return ((o + sk - line + tile - 1) >> shift) == nit ? line : (o & ~int64_t{3});
 }
 
-// ------------------------------------------------------------------ setup --
-// One workgroup of 1024 threads.  Shapes are processed in chunks of 4096 rows
-// (4 consecutive rows per thread); the per-thread sums of row sizes and item
-// counts are scanned with wave shuffles and LDS, carried across chunks.
+// ------------------------------------------------------------------ shape --
 constexpr int kSetupThreads = 1024;
 constexpr int kSetupPer = 4;
 
@@ -145,124 +188,212 @@ __device__ __forceinline__ int64_t block_exclusive_scan_1024(int64_t v, int64_t 
     return before + inc - v;
 }
 
-__global__ __launch_bounds__(kSetupThreads) void seg_setup_kernel(SegArgs a) {
-    __shared__ int64_t lds_a[16], lds_b[16];
-    __shared__ int bad;
-    const int tid = threadIdx.x;
-    if (tid == 0) {
-        bad = 0;
-        *a.num_counted = 0;
-    }
+// Sum over the workgroup of one value per thread, in every thread.
+__device__ __forceinline__ int64_t block_sum_of(int64_t v, int64_t *lds16) {
+    v = wave_sum_i64(v);
+    if ((threadIdx.x & 63) == 0) lds16[wave_id()] = v;
     __syncthreads();
-    int64_t carry_off = 0, carry_items = 0;
-    for (int64_t c0 = 0; c0 < a.m; c0 += static_cast<int64_t>(kSetupThreads) * kSetupPer) {
-        const int64_t r0 = c0 + static_cast<int64_t>(tid) * kSetupPer;
-        int64_t s[kSetupPer];
-        int64_t sum_s = 0;
+    int64_t tot = 0;
+    for (uint32_t w = 0; w < blockDim.x / kWave; ++w) tot += lds16[w];
+    __syncthreads();
+    return tot;
+}
+
+// Record `idx` of the items begun by rows [r0, r0 + nr), whose offsets and
+// first items stand in s_off[0..nr], s_it[0..nr].
+__device__ __forceinline__ void write_item(const SegArgs &a, int64_t idx, const int64_t *s_off,
+                                           const int64_t *s_it, int64_t r0, int nr) {
+    auto row_of = [&](int64_t it) {   // last row j with s_it[j] <= it
+        int lo = 0, hi = nr - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (s_it[mid] <= it) lo = mid;
+            else hi = mid - 1;
+        }
+        return lo;
+    };
+    const int j = row_of(idx);
+    const int64_t o = s_off[j], e = s_off[j + 1];
+    SegItem d;
+    d.fbase = 0;
+    d.row = static_cast<int32_t>(r0 + j);
+    if (e - o <= a.short_max) {
+        // up to the row that begins the next item, or the end of the block
+        const int j1 = idx + 1 < s_it[nr] ? row_of(idx + 1) : nr;
+        d.lo = o;
+        d.hi = s_off[j1];
+        d.base = o & ~int64_t{31};
+        d.tbase = 0;
+        d.kind = kPacked | 2;
+        d.first = r0 + j1;
+    } else {
+        const int64_t i0 = s_it[j], nit = s_it[j + 1] - i0, q = idx - i0;
+        const bool sib = row_synced(a, nit);
+        d.base = row_first_base(o, e - o, nit, a.tile, a.tile_shift) + q * a.tile;
+        d.lo = d.base > o ? d.base : o;
+        d.hi = d.base + a.tile < e ? d.base + a.tile : e;
+        d.tbase = sib ? o : 0;
+        d.kind = (nit == 1 ? 1 : 0) | (q == 0 ? 2 : 0) | (sib ? 4 | static_cast<int32_t>(nit << 8) : 0);
+        d.first = sib ? i0 : 0;
+    }
+    a.items[idx] = d;
+    a.counts[idx] = 0;
+}
+
+// More than kShapeFusedRows rows: three launches over at most kShapeChunks
+// chunks of whole 4096-row blocks.  Every workgroup adds up the chunk totals
+// before its own, so none waits for another and nothing carries over between
+// calls.  (One workgroup scanning the whole shape and one launch for the
+// records took 340 us for 250,000 rows; the three launches take 25 us.)
+//   seg_sizes   -- elements per chunk;
+//   seg_rows    -- row offsets, and the items of a chunk;
+//   seg_records -- the item records; the last chunk validates the shape.
+__global__ __launch_bounds__(kSetupThreads) void seg_sizes_kernel(SegArgs a) {
+    __shared__ int64_t lds[16];
+    __shared__ int bad;
+    const int64_t c = blockIdx.x, r0 = c * a.chunk_rows;
+    const int64_t r1 = r0 + a.chunk_rows < a.m ? r0 + a.chunk_rows : a.m;
+    if (threadIdx.x == 0) bad = 0;
+    __syncthreads();
+    int64_t sum = 0;
+    bool neg = false;
+    for (int64_t b = r0; b < r1; b += kSetupThreads * kSetupPer) {
 #pragma unroll
         for (int j = 0; j < kSetupPer; ++j) {
-            const int64_t k = r0 + j;
-            s[j] = k < a.m ? a.shape[k] : 0;
-            if (s[j] < 0) atomicOr(&bad, 1);
-            s[j] = s[j] < 0 ? 0 : s[j];
+            const int64_t k = b + j * kSetupThreads + threadIdx.x;
+            const int64_t v = k < r1 ? a.shape[k] : 0;
+            neg |= v < 0;
+            sum += v < 0 ? 0 : v;
+        }
+    }
+    if (ballot(neg) != 0 && (threadIdx.x & 63) == 0) atomicOr(&bad, 1);
+    sum = block_sum_of(sum, lds);
+    if (threadIdx.x == 0) {
+        a.csum[c] = sum;
+        a.cbad[c] = bad;
+    }
+    // clear the item scan's ticket and look-back descriptors
+    const int64_t g = c * kSetupThreads + threadIdx.x;
+    const int64_t nd = (a.max_items + kScanChunk - 1) / kScanChunk;
+    for (int64_t j = g; j < nd; j += static_cast<int64_t>(gridDim.x) * kSetupThreads) a.scan_desc[j] = 0;
+    if (g == 0) *a.scan_ticket = 0;
+}
+
+__global__ __launch_bounds__(kSetupThreads) void seg_rows_kernel(SegArgs a) {
+    constexpr int kBlockRows = kSetupThreads * kSetupPer;
+    static_assert(kBlockRows == 1 << kChunkPackShift, "packing block");
+    __shared__ int64_t lds[16];
+    __shared__ int64_t sz[kBlockRows];
+    __shared__ int wlast[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
+    const int64_t c = blockIdx.x, c0 = c * a.chunk_rows;
+    const int64_t c1 = c0 + a.chunk_rows < a.m ? c0 + a.chunk_rows : a.m;
+    int64_t off = block_sum_of(tid < c ? a.csum[tid] : 0, lds);
+    int64_t items = 0, counted = 0;
+    for (int64_t b = c0; b < c1; b += kBlockRows) {
+        __syncthreads();   // sz is reused
+#pragma unroll
+        for (int j = 0; j < kSetupPer; ++j) {
+            const int64_t k = b + j * kSetupThreads + tid;
+            const int64_t v = k < c1 ? a.shape[k] : 0;
+            sz[j * kSetupThreads + tid] = v < 0 ? 0 : v;
+        }
+        __syncthreads();
+        int64_t s[kSetupPer], sum_s = 0;
+        int last = 0;   // 1 + this thread's last non-empty row in the block
+#pragma unroll
+        for (int j = 0; j < kSetupPer; ++j) {
+            s[j] = sz[tid * kSetupPer + j];
             sum_s += s[j];
+            if (s[j] > 0) last = tid * kSetupPer + j + 1;
         }
         int64_t tot_s;
-        const int64_t off0 = carry_off + block_exclusive_scan_1024(sum_s, lds_a, &tot_s);
-        // items per row depend on the row offset (4-alignment of its start)
-        int64_t nitems[kSetupPer];
-        int64_t sum_it = 0;
-        {
-            int64_t o = off0;
+        const int64_t off0 = off + block_exclusive_scan_1024(sum_s, lds, &tot_s);
+        int64_t prev = 0;
+        if (a.short_max) {
+            int inc = last;   // running maximum over the lanes, then the waves
 #pragma unroll
-            for (int j = 0; j < kSetupPer; ++j) {
-                const int64_t ak = o & ~int64_t{3};
-                nitems[j] = s[j] > 0 ? ((o + s[j] - ak + a.tile - 1) >> a.tile_shift) : 0;
-                sum_it += nitems[j];
-                o += s[j];
+            for (int o = 1; o < kWave; o <<= 1) {
+                const int x = __shfl_up(inc, o, kWave);
+                if (lane >= o && x > inc) inc = x;
             }
+            if (lane == kWave - 1) wlast[wave] = inc;
+            __syncthreads();
+            int before = __shfl_up(inc, 1, kWave);
+            if (lane == 0) before = 0;
+            for (int w = 0; w < wave; ++w) before = wlast[w] > before ? wlast[w] : before;
+            prev = before ? sz[before - 1] : 0;
+            __syncthreads();   // wlast is reused
         }
-        int64_t tot_it;
-        const int64_t it0 = carry_items + block_exclusive_scan_1024(sum_it, lds_b, &tot_it);
-        int64_t o = off0, it = it0;
+        int64_t nit[kSetupPer], sum_it = 0, o = off0;
 #pragma unroll
         for (int j = 0; j < kSetupPer; ++j) {
-            const int64_t k = r0 + j;
-            if (k < a.m) {
+            nit[j] = row_items(a, o, s[j], prev);
+            sum_it += nit[j];
+            if (row_counted(a, nit[j])) counted += nit[j];
+            if (s[j] > 0) prev = s[j];
+            o += s[j];
+        }
+        int64_t tot_it;
+        int64_t it = items + block_exclusive_scan_1024(sum_it, lds, &tot_it);
+        o = off0;
+#pragma unroll
+        for (int j = 0; j < kSetupPer; ++j) {
+            const int64_t k = b + tid * kSetupPer + j;
+            if (k < c1) {
                 a.offsets[k] = o;
-                a.item_off[k] = it;
+                a.item_off[k] = it;   // inside the chunk, until seg_records adds the chunk's start
             }
             o += s[j];
-            it += nitems[j];
+            it += nit[j];
         }
-        carry_off += tot_s;
-        carry_items += tot_it;
+        off += tot_s;
+        items += tot_it;
     }
-    __syncthreads();
+    counted = block_sum_of(counted, lds);
     if (tid == 0) {
-        const bool ok = !bad && carry_off == a.n && carry_items <= a.max_items;
-        a.offsets[a.m] = carry_off;
-        a.item_off[a.m] = carry_items;
-        *a.num_items = ok ? carry_items : 0;
+        a.citems[c] = items;
+        a.ccounted[c] = counted;
+        if (c1 == a.m) a.offsets[a.m] = off;
+    }
+}
+
+__global__ __launch_bounds__(kSetupThreads) void seg_records_kernel(SegArgs a) {
+    constexpr int kBlockRows = kSetupThreads * kSetupPer;
+    __shared__ int64_t lds[16];
+    __shared__ int64_t s_off[kBlockRows + 1], s_it[kBlockRows + 1];
+    const int tid = threadIdx.x;
+    const int64_t c = blockIdx.x, c0 = c * a.chunk_rows;
+    const int64_t c1 = c0 + a.chunk_rows < a.m ? c0 + a.chunk_rows : a.m;
+    const int64_t ibase = block_sum_of(tid < c ? a.citems[tid] : 0, lds);
+    const int64_t iend = ibase + a.citems[c];
+    for (int64_t b = c0; b < c1; b += kBlockRows) {
+        const int nr = static_cast<int>(c1 - b < kBlockRows ? c1 - b : kBlockRows);
+        for (int j = tid; j <= nr; j += kSetupThreads) {
+            s_off[j] = a.offsets[b + j];
+            s_it[j] = b + j < c1 ? ibase + a.item_off[b + j] : iend;
+        }
+        __syncthreads();
+        for (int j = tid; j < nr; j += kSetupThreads) a.item_off[b + j] = s_it[j];
+        // (a bad shape may ask for more records than fit: the rest is left out)
+        for (int64_t idx = s_it[0] + tid; idx < s_it[nr] && idx < a.max_items; idx += kSetupThreads)
+            write_item(a, idx, s_off, s_it, b, nr);
+        __syncthreads();
+    }
+    if (c1 < a.m) return;
+    const int64_t bad = block_sum_of(tid < a.nchunks ? a.cbad[tid] : 0, lds);
+    const int64_t counted = block_sum_of(tid < a.nchunks ? a.ccounted[tid] : 0, lds);
+    if (tid == 0) {
+        const bool ok = !bad && a.offsets[a.m] == a.n && iend <= a.max_items;
+        a.item_off[a.m] = iend;
+        *a.num_items = ok ? iend : 0;
+        *a.num_counted = ok ? static_cast<unsigned long long>(counted) : 0ull;
         *a.err = ok ? 0 : kErrShape;
     }
 }
 
-// One workgroup per 256 rows: the rows' offsets go to LDS, then the
-// workgroup's threads write the rows' item descriptors in parallel (an item
-// finds its row by binary search in LDS), so a row of many items costs no
-// more than many rows of one item.  (T_k of empty rows is written by seg_count.)
-__global__ __launch_bounds__(256) void seg_items_kernel(SegArgs a) {
-    __shared__ int64_t s_off[257], s_it[257];
-    __shared__ unsigned long long s_counted;
-    if (*a.err != 0) return;
-    if (threadIdx.x == 0) s_counted = 0;
-    {   // clear the item scan's ticket and look-back descriptors
-        const int64_t g = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-        const int64_t nd = (a.max_items + kScanChunk - 1) / kScanChunk;
-        for (int64_t j = g; j < nd; j += static_cast<int64_t>(gridDim.x) * 256) a.scan_desc[j] = 0;
-        if (g == 0) *a.scan_ticket = 0;
-    }
-    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * 256;
-    const int nr = static_cast<int>(a.m - r0 < 256 ? a.m - r0 : 256);
-    for (int j = threadIdx.x; j <= nr; j += blockDim.x) {
-        s_off[j] = a.offsets[r0 + j];
-        s_it[j] = a.item_off[r0 + j];
-    }
-    __syncthreads();
-    for (int64_t idx = s_it[0] + threadIdx.x; idx < s_it[nr]; idx += blockDim.x) {
-        int lo = 0, hi = nr - 1;   // last row j with s_it[j] <= idx
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_it[mid] <= idx) lo = mid;
-            else hi = mid - 1;
-        }
-        const int64_t o = s_off[lo], e = s_off[lo + 1];
-        const int64_t i0 = s_it[lo], i1 = s_it[lo + 1];
-        const int64_t q = idx - i0;
-        const int64_t nit = i1 - i0;
-        const int64_t ak = row_first_base(o, e - o, nit, a.tile, a.tile_shift);
-        const bool sib = a.mode == IXP_MODE_PARTITION && a.row_sync != IXP_ROW_SYNC_COUNT && nit > 1 &&
-                         nit <= kSibMax;
-        SegItem d;
-        d.base = ak + q * a.tile;
-        d.lo = d.base > o ? d.base : o;
-        d.hi = d.base + a.tile < e ? d.base + a.tile : e;
-        d.tbase = sib ? o : 0;
-        d.fbase = 0;
-        d.row = static_cast<int32_t>(r0 + lo);
-        d.kind = (nit == 1 ? 1 : 0) | (q == 0 ? 2 : 0) | (sib ? 4 | static_cast<int32_t>(nit << 8) : 0);
-        d.first = sib ? i0 : 0;
-        a.items[idx] = d;
-        a.counts[idx] = 0;
-        if (a.mode != IXP_MODE_PARTITION || (nit > 1 && !sib)) atomicAdd(&s_counted, 1ull);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0 && s_counted) atomicAdd(a.num_counted, s_counted);
-}
-
-// Fused shape scan and item records, for up to kShapeFusedRows rows (one
-// launch instead of seg_setup + seg_items).  Workgroup j owns rows
+// Shape scan and item records in one launch, for up to kShapeFusedRows rows.
+// Workgroup j owns rows
 // [256 j, 256 j + 256) and recomputes the scan of every row before and
 // including its own (at most kShapeFusedRows sizes, read from L2), so no
 // workgroup waits for another and no state carries over between calls.  The
@@ -271,7 +402,6 @@ __global__ __launch_bounds__(256) void seg_items_kernel(SegArgs a) {
 // writes no output: T_k of empty rows is written by the counting kernel, once
 // the shape is known good.
 constexpr int kShapeThreads = 1024;
-constexpr int64_t kShapeFusedRows = 16384;          // sizes staged in 128 KiB of LDS
 
 __global__ __launch_bounds__(kShapeThreads) void seg_shape_kernel(SegArgs a) {
     __shared__ int64_t lds_a[16], lds_b[16];
@@ -317,34 +447,39 @@ __global__ __launch_bounds__(kShapeThreads) void seg_shape_kernel(SegArgs a) {
     for (int64_t k = k0; k < k1; ++k) sum_s += sz[k];
     int64_t tot_s;
     const int64_t off0 = block_exclusive_scan_1024(sum_s, lds_a, &tot_s);
-    // items per row depend on the row offset (4-alignment of its start)
-    auto items_of = [&](int64_t o, int64_t sk) {
-        return sk > 0 ? ((o + sk - (o & ~int64_t{3}) + a.tile - 1) >> a.tile_shift) : int64_t{0};
-    };
+    // the last non-empty size before this thread's rows in their block of rows
+    int64_t prev0 = 0;
+    if (a.short_max) {
+        const int64_t block0 = k0 & ~((int64_t{1} << kFusedPackShift) - 1);
+        for (int64_t k = k0 - 1; k >= block0 && k < rend && prev0 == 0; --k) prev0 = sz[k];
+    }
+    auto at_block = [](int64_t k) { return (k & ((int64_t{1} << kFusedPackShift) - 1)) == 0; };
     int64_t sum_it = 0, counted = 0;
     {
-        int64_t o = off0;
+        int64_t o = off0, prev = prev0;
         for (int64_t k = k0; k < k1; ++k) {
-            const int64_t nit = items_of(o, sz[k]);
+            if (at_block(k)) prev = 0;
+            const int64_t nit = row_items(a, o, sz[k], prev);
             sum_it += nit;
-            const bool sib = a.mode == IXP_MODE_PARTITION && a.row_sync != IXP_ROW_SYNC_COUNT && nit > 1 &&
-                             nit <= kSibMax;
-            if (a.mode != IXP_MODE_PARTITION || (nit > 1 && !sib)) counted += nit;
+            if (row_counted(a, nit)) counted += nit;
+            if (sz[k] > 0) prev = sz[k];
             o += sz[k];
         }
     }
     int64_t tot_it;
     const int64_t it0 = block_exclusive_scan_1024(sum_it, lds_b, &tot_it);
     {
-        int64_t o = off0, it = it0;
+        int64_t o = off0, it = it0, prev = prev0;
         for (int64_t k = k0; k < k1; ++k) {
+            if (at_block(k)) prev = 0;
             if (k >= r0) {
                 s_off[k - r0] = o;
                 s_it[k - r0] = it;
                 a.offsets[k] = o;
                 a.item_off[k] = it;
             }
-            it += items_of(o, sz[k]);
+            it += row_items(a, o, sz[k], prev);
+            if (sz[k] > 0) prev = sz[k];
             o += sz[k];
         }
     }
@@ -367,32 +502,8 @@ __global__ __launch_bounds__(kShapeThreads) void seg_shape_kernel(SegArgs a) {
     __syncthreads();
     // this workgroup's item records (a bad shape may ask for more than fit:
     // those are not written, and the last workgroup reports the error)
-    for (int64_t idx = s_it[0] + tid; idx < s_it[nr] && idx < a.max_items; idx += kShapeThreads) {
-        int lo = 0, hi = nr - 1;   // last row j with s_it[j] <= idx
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_it[mid] <= idx) lo = mid;
-            else hi = mid - 1;
-        }
-        const int64_t o = s_off[lo], e = s_off[lo + 1];
-        const int64_t i0 = s_it[lo], i1 = s_it[lo + 1];
-        const int64_t q = idx - i0;
-        const int64_t nit = i1 - i0;
-        const int64_t ak = row_first_base(o, e - o, nit, a.tile, a.tile_shift);
-        const bool sib = a.mode == IXP_MODE_PARTITION && a.row_sync != IXP_ROW_SYNC_COUNT && nit > 1 &&
-                         nit <= kSibMax;
-        SegItem d;
-        d.base = ak + q * a.tile;
-        d.lo = d.base > o ? d.base : o;
-        d.hi = d.base + a.tile < e ? d.base + a.tile : e;
-        d.tbase = sib ? o : 0;
-        d.fbase = 0;
-        d.row = static_cast<int32_t>(r0 + lo);
-        d.kind = (nit == 1 ? 1 : 0) | (q == 0 ? 2 : 0) | (sib ? 4 | static_cast<int32_t>(nit << 8) : 0);
-        d.first = sib ? i0 : 0;
-        a.items[idx] = d;
-        a.counts[idx] = 0;
-    }
+    for (int64_t idx = s_it[0] + tid; idx < s_it[nr] && idx < a.max_items; idx += kShapeThreads)
+        write_item(a, idx, s_off, s_it, r0, nr);
 }
 
 // ------------------------------------------------------------------ count --
@@ -407,10 +518,10 @@ __global__ __launch_bounds__(256) void seg_count_kernel(SegArgs a, Pred pred) {
     const int lane = threadIdx.x & (kWave - 1);
     if (*a.err != 0) return;   // a bad shape: no output is written
     if (a.seg_split) {
-        // T_k = 0 for empty rows (rows without items), once the shape is known good
+        // T_k = 0 for empty rows, once the shape is known good
         for (int64_t k = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; k < a.m;
              k += static_cast<int64_t>(gridDim.x) * blockDim.x)
-            if (a.item_off[k] == a.item_off[k + 1]) a.seg_split[k] = 0;
+            if (a.offsets[k] == a.offsets[k + 1]) a.seg_split[k] = 0;
     }
     if (*a.num_counted == 0) return;   // every item is counted in seg_main
     const int64_t nitems = *a.num_items;
@@ -421,7 +532,8 @@ __global__ __launch_bounds__(256) void seg_count_kernel(SegArgs a, Pred pred) {
         const int64_t it = w >> cshift;
         const int64_t c = w & ((int64_t{1} << cshift) - 1);
         const SegItem &d = a.items[it];
-        if (a.mode == IXP_MODE_PARTITION && (d.kind & 5)) continue;   // counted in seg_main
+        if (a.mode == IXP_MODE_PARTITION && (d.kind & (kOwnRows | 4))) continue;   // counted in seg_main
+        if (Pred::kRow && (d.kind & kPacked)) continue;   // (seg_count_packed)
         const int64_t b = d.base + (c << kCLog);
         if (b >= d.hi) continue;
         WT chunk;
@@ -497,7 +609,7 @@ __global__ __launch_bounds__(256) void seg_item_bases_kernel(SegArgs a) {
     const int64_t k = d.row;
     const int64_t i0 = a.item_off[k], i1 = a.item_off[k + 1];
     if (a.mode == IXP_MODE_PARTITION) {
-        if (d.kind & 5) return;   // finished by the main kernel
+        if (d.kind & (kOwnRows | 4)) return;   // finished by the main kernel
         const int64_t ok = a.offsets[k];
         const int64_t p0 = a.prefix[i0];
         const int64_t before = a.prefix[i] - p0;
@@ -508,7 +620,7 @@ __global__ __launch_bounds__(256) void seg_item_bases_kernel(SegArgs a) {
     } else {
         a.items[i].tbase = a.prefix[i];
         a.items[i].fbase = 0;
-        if (i == i0 && a.seg_split) a.seg_split[k] = a.prefix[i1] - a.prefix[i0];
+        if (i == i0 && a.seg_split && !(d.kind & kPacked)) a.seg_split[k] = a.prefix[i1] - a.prefix[i0];
     }
 }
 
@@ -577,6 +689,306 @@ __device__ __forceinline__ void row_counts(const SegArgs &a, const Pred &pred, i
     }
 }
 
+// ----------------------------------------------------------- packed items --
+// A packed item holds the whole short rows [row, first): every row's elements
+// and T_k are inside it, so it waits for no other item.  Where the rows start
+// is kept as one bit per position of the tile (`head`); an element finds its
+// row's start and the next row's start in its own 32-bit word or in a table of
+// the nearest start before / after each word, so no per-element search is
+// needed and rows may be of any size.  Window and limit (3/4 and 1/4 of the
+// tile) let every such item fit its tile while filling three quarters of it.
+// About 60 vector instructions an element and the chain of barriers bound it,
+// not memory: 2^25 int32 keys in rows of 128 on average take 110 us in
+// seg_main (3.7 TB/s), where a workgroup per row took 700 us.  Keeping keys and
+// counts in one LDS array and 5 waves per SIMD (58 -> 35 us for 8 million keys in
+// 250,000 rows) is what helped; 6 or 7 waves, or as many workgroups as fit that
+// take many items each, changed nothing or were slower.
+constexpr int kPackThreads = 256, kPackRows = 4;
+constexpr int kPackTile = kPackThreads * kPackRows * 4;
+constexpr int kPackWords = kPackTile / 32;
+static_assert(kPackWords == 2 * kWave, "one wave scans the words");
+
+struct PackLds {
+    uint32_t head[kPackWords];
+    int16_t before[kPackWords];   // last start before the word (or the item's first)
+    int16_t after[kPackWords];    // first start after the word, or the item's end
+};
+// At a start: the trues of the tile before the row, and before the next row;
+// at the item's end: all its trues.  One word per position: the same LDS
+// holds each row's word before, and the keys in output order after.
+struct PackRow {
+    uint16_t trues, next;
+};
+
+// Start bits, and with `words` each row's word at its start; then (tables) the
+// nearest starts of every word.  All threads of the workgroup; ends with a
+// barrier.  `ok`, `oe` are the offsets of row d.row + tid and the one after it
+// (equal past the last row), loaded by the caller beside the keys.
+template <class WordOf>
+__device__ __forceinline__ void pack_starts(const SegArgs &a, const SegItem &d, PackLds &p, uint32_t *words,
+                                            const WordOf &word_of, bool tables, int64_t ok, int64_t oe) {
+    const int tid = threadIdx.x;
+    for (int64_t k = d.row + tid;;) {
+        if (oe > ok) {
+            const uint32_t l = static_cast<uint32_t>(ok - d.base);
+            atomicOr(p.head + (l >> 5), 1u << (l & 31));
+            if (words) words[l] = word_of(k);
+        }
+        k += kPackThreads;
+        if (k >= d.first) break;
+        ok = a.offsets[k];
+        oe = a.offsets[k + 1];
+    }
+    __syncthreads();
+    if (!tables) return;
+    if (wave_id() == 0) {
+        const int lane = tid & (kWave - 1);
+        const uint32_t w0 = p.head[2 * lane], w1 = p.head[2 * lane + 1];
+        const int f0 = w0 ? 64 * lane + __builtin_ctz(w0) : kPackTile;
+        const int f1 = w1 ? 64 * lane + 32 + __builtin_ctz(w1) : kPackTile;
+        const int l0 = w0 ? 64 * lane + 31 - __builtin_clz(w0) : -1;
+        const int l1 = w1 ? 64 * lane + 63 - __builtin_clz(w1) : -1;
+        int last = l1 > l0 ? l1 : l0, next = f0 < f1 ? f0 : f1;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const int x = __shfl_up(last, o, kWave), y = __shfl_down(next, o, kWave);
+            if (lane >= o && x > last) last = x;
+            if (lane + o < kWave && y < next) next = y;
+        }
+        int before = __shfl_up(last, 1, kWave), after = __shfl_down(next, 1, kWave);
+        const int lo = static_cast<int>(d.lo - d.base), end = static_cast<int>(d.hi - d.base);
+        if (lane == 0 || before < lo) before = lo;
+        if (lane == kWave - 1 || after > end) after = end;
+        p.before[2 * lane] = static_cast<int16_t>(before);
+        p.before[2 * lane + 1] = static_cast<int16_t>(l0 >= 0 ? l0 : before);
+        p.after[2 * lane + 1] = static_cast<int16_t>(after);
+        p.after[2 * lane] = static_cast<int16_t>(f1 < kPackTile ? f1 : after);
+    }
+    __syncthreads();
+}
+
+// The starts around the element at position l of the tile, from its word.
+__device__ __forceinline__ int row_start(uint32_t w, int l, int before) {
+    const uint32_t m = w & ((2u << (l & 31)) - 1u);
+    return m ? (l | 31) - __builtin_clz(m) : before;
+}
+__device__ __forceinline__ int row_end(uint32_t w, int l, int after) {
+    const uint32_t m = w & ~((2u << (l & 31)) - 1u);
+    return m ? (l & ~31) + __builtin_ctz(m) : after;
+}
+
+// Loads a packed item's keys and evaluates the predicate of each element's row.
+// A wave past the item's end (`live` false) loads nothing.  Leaves the offsets
+// of row d.row + tid and the one after it in ok, oe (equal past the last row).
+template <class T, class Pred>
+__device__ __forceinline__ void pack_load(const SegArgs &a, const Pred &pred, const SegItem &d, PackLds &p,
+                                          uint32_t *words, bool tables, bool need_keys, bool live, T &tile, int wave,
+                                          int lane, int64_t &ok, int64_t &oe) {
+    const int tid = threadIdx.x;
+    if (tid < kPackWords) p.head[tid] = 0;
+    const int64_t k = d.row + tid;
+    ok = k < d.first ? a.offsets[k] : 0;
+    oe = k < d.first ? a.offsets[k + 1] : 0;
+    if (!live) {
+#pragma unroll
+        for (int r = 0; r < kPackRows; ++r)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) tile.key[r][q] = 0;
+    } else if constexpr (Pred::kRow) {
+        tile.load(a.keys, a.n, d.base, d.lo, d.hi, PredNone{}, true, wave, lane);
+    } else {
+        tile.load(a.keys, a.n, d.base, d.lo, d.hi, pred, need_keys, wave, lane);
+    }
+    __syncthreads();   // head is clear
+    if constexpr (Pred::kRow) {
+        pack_starts(a, d, p, words, [&](int64_t r) { return pred.row_word(r); }, true, ok, oe);
+        if (!live) return;
+        int l0 = wave * T::kPerWave + lane * 4;
+        asm volatile("" : "+v"(l0));   // (see packed_item)
+#pragma unroll
+        for (int r = 0; r < kPackRows; ++r) {
+            const int lr = l0 + r * (kWave * 4);
+            const uint32_t w = p.head[lr >> 5];
+            int s = row_start(w, lr, p.before[lr >> 5]);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (q > 0) s = (w >> ((lr & 31) + q)) & 1u ? lr + q : s;
+                const bool f = tile.valid(r, q) && pred.in_row(tile.key[r][q], words[s]);
+                tile.fbits |= static_cast<uint32_t>(f) << (r * 4 + q);
+            }
+            __builtin_amdgcn_sched_barrier(0);   // a row's LDS words at a time, to hold few registers
+        }
+    } else {
+        pack_starts(a, d, p, nullptr, [](int64_t) { return 0u; }, tables, ok, oe);
+    }
+}
+
+// One packed item (see seg_main).  Its keys are staged in output order and
+// leave as one run.  `stage` (kPackTile + 1 words) holds in turn the rows'
+// words, the rows' counts and the keys.  Every barrier is reached by the whole
+// workgroup.
+template <class Pred, int MODE, class Idx>
+__device__ __forceinline__ void packed_item(const SegArgs &a, const Pred &pred, const SegItem &d, PackLds &p,
+                                            uint32_t *stage, uint32_t *wtot, int wave, int lane) {
+    using T = Tile<kPackThreads, kPackRows, 4, uint32_t>;
+    const int tid = threadIdx.x;
+    Idx *out_idx = static_cast<Idx *>(a.out_idx);
+    const bool part = MODE == IXP_MODE_PARTITION;
+    const bool live = T::wave_live(d.base, d.lo, d.hi, wave);
+    T tile;
+    int64_t ok, oe;
+    pack_load(a, pred, d, p, stage, part, a.need_keys != 0, live, tile, wave, lane, ok, oe);
+    uint32_t pre[kPackRows];   // trues of the tile before this lane's group of a row
+    uint32_t wt = 0;
+#pragma unroll
+    for (int r = 0; r < kPackRows; ++r) {
+        uint32_t below = 0, row_total = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint64_t m = ballot(tile.flag(r, q));
+            below += rank_below(m);
+            row_total += static_cast<uint32_t>(__builtin_popcountll(m));
+        }
+        pre[r] = wt + below;
+        wt += row_total;
+    }
+    if (lane == 0) wtot[wave] = wt;
+    __syncthreads();
+    uint32_t tbefore = 0, tcount = 0;
+#pragma unroll
+    for (int w = 0; w < T::kWaves; ++w) {
+        const uint32_t v = wtot[w];
+        tbefore += w < wave ? v : 0u;
+        tcount += v;
+    }
+    PackRow *at = reinterpret_cast<PackRow *>(stage);
+    // opaque: the positions, words and masks derived from it would otherwise be
+    // kept in registers across the whole item loop
+    int l0 = wave * T::kPerWave + lane * 4;
+    uint32_t fb = tile.fbits;
+    asm volatile("" : "+v"(l0), "+v"(fb));
+    const int end = static_cast<int>(d.hi - d.base);
+    auto rank = [&](int r, int q) {   // trues of the tile before element (r, q)
+        return pre[r] + static_cast<uint32_t>(__builtin_popcount((fb >> (4 * r)) & ((1u << q) - 1u)));
+    };
+#pragma unroll
+    for (int r = 0; r < kPackRows; ++r) {
+        pre[r] += tbefore;
+        const int lr = l0 + r * (kWave * 4);
+        const uint32_t h = live ? (p.head[lr >> 5] >> (lr & 31)) & 0xFu : 0u;
+        if (h) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if ((h >> q) & 1u) at[lr + q].trues = static_cast<uint16_t>(rank(r, q));
+        }
+    }
+    if (tid == 0) at[end].trues = static_cast<uint16_t>(tcount);
+    __syncthreads();
+    if (a.seg_split) {
+        for (int64_t k = d.row + tid; k < d.first; k += kPackThreads) {
+            if (oe > ok) a.seg_split[k] = at[oe - d.base].trues - at[ok - d.base].trues;   // (empty: seg_count)
+            if (k + kPackThreads < d.first) {
+                ok = a.offsets[k + kPackThreads];
+                oe = a.offsets[k + kPackThreads + 1];
+            }
+        }
+    }
+    if (part) {
+#pragma unroll
+        for (int r = 0; r < kPackRows; ++r) {
+            const int lr = l0 + r * (kWave * 4);
+            const uint32_t w = p.head[lr >> 5];
+            const uint32_t h = live ? (w >> (lr & 31)) & 0xFu : 0u;
+            if (h) {
+                const int after = p.after[lr >> 5];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if ((h >> q) & 1u) at[lr + q].next = at[row_end(w, lr + q, after)].trues;
+            }
+        }
+        __syncthreads();
+    }
+    asm volatile("" : "+v"(l0), "+v"(fb));
+    uint32_t to[kPackRows][4];   // place of the key in the stage
+#pragma unroll
+    for (int r = 0; r < kPackRows; ++r) {
+        const int lr = l0 + r * (kWave * 4);
+        const int64_t p0 = d.base + lr;
+        const uint32_t w = p.head[lr >> 5];
+        int s = part ? row_start(w, lr, p.before[lr >> 5]) : 0;
+        const uint32_t h = (w >> (lr & 31)) & 0xFu;
+        const uint32_t vm = (tile.vbits >> (4 * r)) & 0xFu;
+        Idx v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t e = rank(r, q);
+            const bool f = (fb >> (4 * r + q)) & 1u;
+            if (MODE == IXP_MODE_PARTITION) {
+                if (q > 0) s = (h >> q) & 1u ? lr + q : s;
+                const uint32_t row = stage[s];   // (its two counts by one load)
+                // a true: the row's start + its trues before; a false: after all of them
+                const uint32_t t = s + e - (row & 0xFFFFu), u = static_cast<uint32_t>(lr + q) - e + (row >> 16);
+                to[r][q] = f ? t : u;
+                v[q] = static_cast<Idx>(d.base + to[r][q]);
+            } else {
+                to[r][q] = e;
+                v[q] = static_cast<Idx>(f ? d.tbase + e : -1);
+            }
+        }
+        if (vm) {
+            if (out_idx) store_idx_group<4, Idx>(out_idx, p0, v, vm);
+            if (a.flags_out) {
+                const uint32_t fl = (h & 1u) | (h & 2u) << 7 | (h & 4u) << 14 | (h & 8u) << 21;
+                if (vm == 0xFu) {
+                    stream_store(reinterpret_cast<uint32_t *>(a.flags_out + p0), fl);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if ((vm >> q) & 1u) a.flags_out[p0 + q] = static_cast<uint8_t>(fl >> (8 * q));
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (a.out_keys) {
+        __syncthreads();   // the rows' counts are read
+#pragma unroll
+        for (int r = 0; r < kPackRows; ++r)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (((MODE == IXP_MODE_PARTITION ? tile.vbits : fb) >> (4 * r + q)) & 1u)
+                    stage[to[r][q]] = tile.key[r][q];
+        __syncthreads();
+        if (part)
+            write_run<kPackThreads>(stage, static_cast<uint32_t>(d.lo - d.base), static_cast<uint32_t>(d.hi - d.lo),
+                                    d.lo, a.out_keys, a.n, tid);
+        else
+            write_run<kPackThreads>(stage, 0, tcount, d.tbase, a.out_keys, a.n, tid);
+    }
+}
+
+// Filter with a predicate of the row number: the trues of the packed items,
+// one workgroup per item (seg_count's waves do not know their rows).
+template <class Pred>
+__global__ __launch_bounds__(kPackThreads) void seg_count_packed_kernel(SegArgs a, Pred pred) {
+    using T = Tile<kPackThreads, kPackRows, 4, uint32_t>;
+    __shared__ PackLds p;
+    __shared__ uint32_t words[kPackTile];
+    const int wave = wave_id(), lane = threadIdx.x & (kWave - 1);
+    const int64_t nitems = *a.num_items;
+    for (int64_t it = blockIdx.x; it < nitems; it += gridDim.x) {
+        const SegItem d = a.items[it];
+        if (!(d.kind & kPacked)) continue;
+        T tile;
+        int64_t ok, oe;
+        const bool live = T::wave_live(d.base, d.lo, d.hi, wave);
+        pack_load(a, pred, d, p, words, true, true, live, tile, wave, lane, ok, oe);
+        const uint32_t cnt = tile.wave_count();
+        if (lane == 0 && cnt) atomicAdd(a.counts + it, static_cast<unsigned long long>(cnt));
+        __syncthreads();   // LDS is reused by the next item
+    }
+}
+
 // Workgroups take items round-robin (item = blockIdx.x + k * gridDim.x: no
 // shared queue counter, whose serialised atomics would cost ~10 ns per
 // item); a grid smaller than the item count makes them persistent.  Wave 0
@@ -590,14 +1002,16 @@ __device__ __forceinline__ void row_counts(const SegArgs &a, const Pred &pred, i
 // output (its trues follow the trues of the waves before it, its falses the
 // falses before it).  No other wave reads that LDS run, so it needs no
 // barrier of its own; the one at the top of the loop separates items.
-template <int BLOCK, int ROWS, class Pred, int MODE, class Idx>
-__global__ __launch_bounds__(BLOCK) void seg_main_kernel(SegArgs a, Pred pred) {
+// With PACK some items are packed ones (256 x 4 tiles only).
+template <int BLOCK, int ROWS, class Pred, int MODE, class Idx, bool PACK = false>
+__global__ __launch_bounds__(BLOCK, PACK ? 5 : 1) void seg_main_kernel(SegArgs a, Pred pred) {
+    static_assert(!PACK || (BLOCK == kPackThreads && ROWS == kPackRows), "packed tiles");
     using T = Tile<BLOCK, ROWS, 4, uint32_t>;
     constexpr int kTile = T::kSize;
     constexpr int kPerWave = T::kPerWave;
     constexpr int kWords = sizeof(SegItem) / 8;
     static_assert(sizeof(SegItem) % 8 == 0 && kWords <= kWave, "descriptor words");
-    __shared__ uint32_t stage[kTile];
+    __shared__ uint32_t stage[kTile + (PACK ? 1 : 0)];
     __shared__ uint32_t wtot[T::kWaves];
     __shared__ int64_t sh_desc[kWords];
     __shared__ int64_t sh_item;
@@ -641,6 +1055,13 @@ __global__ __launch_bounds__(BLOCK) void seg_main_kernel(SegArgs a, Pred pred) {
         if (wave == 0) {   // overlaps with this item
             next = it + gridDim.x;
             prefetch();
+        }
+        if constexpr (PACK) {
+            if (d.kind & kPacked) {
+                __shared__ PackLds pk;
+                packed_item<Pred, MODE, Idx>(a, pred, d, pk, stage, wtot, wave, lane);
+                continue;
+            }
         }
         const int64_t lo = d.lo, hi = d.hi, base = d.base;
         const int32_t span = static_cast<int32_t>(hi - lo);
@@ -793,15 +1214,56 @@ __global__ __launch_bounds__(BLOCK) void seg_main_kernel(SegArgs a, Pred pred) {
 // Workgroup w takes items w, w + grid, ...; consecutive threads write
 // consecutive 16-byte groups of the item's aligned middle (when `out` is
 // 16-byte aligned), and single elements at its ends.
+// A packed item's rows start where its start bits say; each start also holds
+// its row's number (from the item's first row), from which mkII fills and
+// mkSgmDescr looks xs up.
+template <int TOOL, class Out>
+__device__ __forceinline__ void fill_packed(const SegArgs &a, const SegItem &d, Out *out, const int64_t *xs,
+                                            bool vec_ok, PackLds &p, uint32_t *val) {
+    constexpr int kV = 16 / sizeof(Out);   // elements per 16-byte group
+    typedef Out vec_t __attribute__((ext_vector_type(kV)));
+    const int tid = threadIdx.x;
+    if (tid < kPackWords) p.head[tid] = 0;
+    const int64_t k = d.row + tid;
+    const int64_t ok = k < d.first ? a.offsets[k] : 0, oe = k < d.first ? a.offsets[k + 1] : 0;
+    __syncthreads();
+    pack_starts(a, d, p, val, [&](int64_t r) { return static_cast<uint32_t>(r - d.row); }, TOOL == 0, ok, oe);
+    const int end = static_cast<int>(d.hi - d.base), lo = static_cast<int>(d.lo - d.base);
+    for (int l = tid * kV; l < end; l += kPackThreads * kV) {   // (base is a multiple of 32)
+        const uint32_t w = p.head[l >> 5];
+        const int before = TOOL == 0 ? p.before[l >> 5] : 0;
+        vec_t v;
+#pragma unroll
+        for (int q = 0; q < kV; ++q) {
+            if (TOOL == 0) v[q] = static_cast<Out>(d.row + val[row_start(w, l + q, before)]);
+            else v[q] = (w >> ((l + q) & 31)) & 1u ? static_cast<Out>(xs[d.row + val[l + q]]) : Out{0};
+        }
+        if (vec_ok && l >= lo && l + kV <= end) {
+            stream_store(reinterpret_cast<vec_t *>(out + d.base + l), v);
+        } else {
+#pragma unroll
+            for (int q = 0; q < kV; ++q)
+                if (l + q >= lo && l + q < end) stream_store(out + d.base + l + q, v[q]);
+        }
+    }
+    __syncthreads();   // the LDS is the next item's
+}
+
 template <int TOOL, class Out>
 __global__ __launch_bounds__(256) void seg_fill_kernel(SegArgs a, Out *out, const int64_t *xs) {
     constexpr int kV = 16 / sizeof(Out);   // elements per 16-byte group
     typedef Out vec_t __attribute__((ext_vector_type(kV)));
+    __shared__ PackLds pk;
+    __shared__ uint32_t val[kPackTile];
     if (*a.err != 0) return;
     const int64_t nitems = *a.num_items;
     const bool vec_ok = (reinterpret_cast<uintptr_t>(out) & 15) == 0;
     for (int64_t it = blockIdx.x; it < nitems; it += gridDim.x) {
         const SegItem d = a.items[it];
+        if (d.kind & kPacked) {
+            fill_packed<TOOL, Out>(a, d, out, xs, vec_ok, pk, val);
+            continue;
+        }
         const bool first = (d.kind & 2) != 0;
         const Out fill = TOOL == 0 ? static_cast<Out>(d.row) : static_cast<Out>(0);
         const Out head = TOOL == 0 ? fill : static_cast<Out>(first ? xs[d.row] : 0);
@@ -821,17 +1283,18 @@ __global__ __launch_bounds__(256) void seg_fill_kernel(SegArgs a, Out *out, cons
     }
 }
 
-// Row offsets, item offsets and item records: one fused launch for up to
-// kShapeFusedRows rows, else the one-workgroup scan and the item writer.
+// Row offsets, item offsets and item records: one launch for up to
+// kShapeFusedRows rows, else three.
 int launch_shape(const SegArgs &a, hipStream_t st) {
-    const uint32_t rblocks = static_cast<uint32_t>(ceil_div(a.m > 0 ? a.m : 1, 256));
     if (a.m <= kShapeFusedRows) {
+        const uint32_t rblocks = static_cast<uint32_t>(ceil_div(a.m > 0 ? a.m : 1, 256));
         IXP_LAUNCH("seg_shape", seg_shape_kernel, dim3(rblocks), dim3(kShapeThreads), 0, st, a);
         return launch_status();
     }
-    IXP_LAUNCH("seg_setup", seg_setup_kernel, dim3(1), dim3(kSetupThreads), 0, st, a);
-    if (launch_status() != IXP_OK) return IXP_EHIP;
-    IXP_LAUNCH("seg_items", seg_items_kernel, dim3(rblocks), dim3(256), 0, st, a);
+    const dim3 chunks(static_cast<uint32_t>(a.nchunks));
+    IXP_LAUNCH("seg_sizes", seg_sizes_kernel, chunks, dim3(kSetupThreads), 0, st, a);
+    IXP_LAUNCH("seg_rows", seg_rows_kernel, chunks, dim3(kSetupThreads), 0, st, a);
+    IXP_LAUNCH("seg_records", seg_records_kernel, chunks, dim3(kSetupThreads), 0, st, a);
     return launch_status();
 }
 
@@ -883,21 +1346,21 @@ SegGeom geom_from(const ixp_tuning *t) {
     return g;
 }
 
-template <int BLOCK, int ROWS, class Pred>
+template <int BLOCK, int ROWS, class Pred, bool PACK = false>
 int launch_main_geom(const SegArgs &a, const Pred &p, int mode, int idx_t, int grid, hipStream_t st) {
     if (mode == IXP_MODE_PARTITION) {
         if (idx_t == IXP_I32)
-            IXP_LAUNCH("seg_main_partition", (seg_main_kernel<BLOCK, ROWS, Pred, IXP_MODE_PARTITION, int32_t>),
+            IXP_LAUNCH("seg_main_partition", (seg_main_kernel<BLOCK, ROWS, Pred, IXP_MODE_PARTITION, int32_t, PACK>),
                        dim3(grid), dim3(BLOCK), 0, st, a, p);
         else
-            IXP_LAUNCH("seg_main_partition", (seg_main_kernel<BLOCK, ROWS, Pred, IXP_MODE_PARTITION, int64_t>),
+            IXP_LAUNCH("seg_main_partition", (seg_main_kernel<BLOCK, ROWS, Pred, IXP_MODE_PARTITION, int64_t, PACK>),
                        dim3(grid), dim3(BLOCK), 0, st, a, p);
     } else {
         if (idx_t == IXP_I32)
-            IXP_LAUNCH("seg_main_filter", (seg_main_kernel<BLOCK, ROWS, Pred, IXP_MODE_FILTER, int32_t>),
+            IXP_LAUNCH("seg_main_filter", (seg_main_kernel<BLOCK, ROWS, Pred, IXP_MODE_FILTER, int32_t, PACK>),
                        dim3(grid), dim3(BLOCK), 0, st, a, p);
         else
-            IXP_LAUNCH("seg_main_filter", (seg_main_kernel<BLOCK, ROWS, Pred, IXP_MODE_FILTER, int64_t>),
+            IXP_LAUNCH("seg_main_filter", (seg_main_kernel<BLOCK, ROWS, Pred, IXP_MODE_FILTER, int64_t, PACK>),
                        dim3(grid), dim3(BLOCK), 0, st, a, p);
     }
     return launch_status();
@@ -905,7 +1368,14 @@ int launch_main_geom(const SegArgs &a, const Pred &p, int mode, int idx_t, int g
 
 template <class Pred>
 int launch_main(const SegArgs &a, const Pred &p, const SegGeom &g, int mode, int idx_t, hipStream_t st) {
-    const int grid = device_cus() * g.wgs_per_cu;
+    const int64_t cap = static_cast<int64_t>(device_cus()) * g.wgs_per_cu;
+    const int grid = static_cast<int>(a.max_items < cap ? a.max_items : cap);
+    if (a.short_max > 0) {
+        // about the number of items; a workgroup without one still costs its dispatch
+        const int64_t want = a.n / (kPackTile / 2) + device_cus() * 4;
+        return launch_main_geom<kPackThreads, kPackRows, Pred, true>(a, p, mode, idx_t,
+                                                                     static_cast<int>(want < grid ? want : grid), st);
+    }
 #define IXP_SEG_GEOM(B, R) \
     if (g.block == B && g.rows == R) return launch_main_geom<B, R, Pred>(a, p, mode, idx_t, grid, st);
     IXP_SEG_GEOM(256, 2)
@@ -930,6 +1400,14 @@ int launch_all(const SegArgs &a, const Pred &p, const SegGeom &g, int mode, int 
                                 ? ceil_div(chunk_waves, 4) : static_cast<int64_t>(cus) * 16;
     IXP_LAUNCH("seg_count", (seg_count_kernel<Pred>), dim3(static_cast<uint32_t>(cblocks)), dim3(256), 0,
                st, a, p);
+    if constexpr (Pred::kRow) {
+        if (a.short_max > 0 && mode == IXP_MODE_FILTER) {
+            const int64_t cap = static_cast<int64_t>(cus) * 16;
+            IXP_LAUNCH("seg_count_packed", (seg_count_packed_kernel<Pred>),
+                       dim3(static_cast<uint32_t>(a.max_items < cap ? a.max_items : cap)), dim3(kPackThreads), 0, st,
+                       a, p);
+        }
+    }
     IXP_LAUNCH("seg_scan_items", seg_scan_items_kernel,
                dim3(static_cast<uint32_t>(ceil_div(a.max_items > 0 ? a.max_items : 1, kScanChunk))), dim3(1024), 0,
                st, a);
@@ -939,12 +1417,24 @@ int launch_all(const SegArgs &a, const Pred &p, const SegGeom &g, int mode, int 
     return launch_main(a, p, g, mode, idx_t, st);
 }
 
+// Short rows are packed when rows have at most kPackMean elements on average
+// (the sizes themselves are known on the device only) and the tile is the
+// default one.  2^25 int32 keys in log-normal rows, a partition with an item per
+// row / with packed items, by the rows' mean size: 16: 5165 / 172 us, 128: 750 /
+// 145, 512: 251 / 173, 1024: 171 / 170, 2048: 121 / 144 (a packed item costs
+// more per element, and rows above 1024 elements cut the packed ones short).
+constexpr int64_t kPackMean = 768;
+bool packs(int64_t n, int64_t m, const SegGeom &g) {
+    return g.block == kPackThreads && g.rows == kPackRows && m > 0 && n / m <= kPackMean && n < (int64_t{1} << 42);
+}
+
 size_t seg_workspace(int64_t n, int64_t m, const SegGeom &g) {
-    const int64_t mi = seg_max_items(n, m, g.tile());
+    const int64_t mi = seg_max_items(n, m, g.tile(), packs(n, m, g));
     return kSegHeader + round_up(static_cast<size_t>(m + 1) * 8, 256) * 2 +
            round_up(static_cast<size_t>(mi) * sizeof(SegItem), 256) +
            round_up(static_cast<size_t>(mi + 1) * 8, 256) + round_up(static_cast<size_t>(mi) * 8, 256) +
-           static_cast<size_t>(ceil_div(mi > 0 ? mi : 1, kScanChunk)) * 8;
+           round_up(static_cast<size_t>(ceil_div(mi > 0 ? mi : 1, kScanChunk)) * 8, 256) +
+           (m > kShapeFusedRows ? 4 * kShapeChunks * sizeof(int64_t) : 0);
 }
 
 void set_layout(int64_t n, int64_t m, const int64_t *d_shape, const SegGeom &g, void *ws, SegArgs *a);
@@ -1005,13 +1495,23 @@ void set_layout(int64_t n, int64_t m, const int64_t *d_shape, const SegGeom &g, 
     a->offsets = reinterpret_cast<int64_t *>(w + kSegHeader);
     a->item_off = reinterpret_cast<int64_t *>(w + kSegHeader + rows_bytes);
     a->items = reinterpret_cast<SegItem *>(w + kSegHeader + 2 * rows_bytes);
-    a->max_items = seg_max_items(n, m, g.tile());
+    const bool pack = packs(n, m, g);
+    a->max_items = seg_max_items(n, m, g.tile(), pack);
     a->prefix = reinterpret_cast<int64_t *>(
         w + kSegHeader + 2 * rows_bytes + round_up(static_cast<size_t>(a->max_items) * sizeof(SegItem), 256));
     a->counts = reinterpret_cast<unsigned long long *>(
         reinterpret_cast<char *>(a->prefix) + round_up(static_cast<size_t>(a->max_items + 1) * 8, 256));
     a->scan_desc = reinterpret_cast<uint64_t *>(reinterpret_cast<char *>(a->counts) +
                                                 round_up(static_cast<size_t>(a->max_items) * 8, 256));
+    const int64_t nd = ceil_div(a->max_items > 0 ? a->max_items : 1, kScanChunk);
+    a->csum = reinterpret_cast<int64_t *>(reinterpret_cast<char *>(a->scan_desc) +
+                                          round_up(static_cast<size_t>(nd) * 8, 256));
+    a->citems = a->csum + kShapeChunks;
+    a->ccounted = a->citems + kShapeChunks;
+    a->cbad = a->ccounted + kShapeChunks;
+    a->chunk_rows = ceil_div(ceil_div(m, int64_t{1} << kChunkPackShift), kShapeChunks) << kChunkPackShift;
+    a->nchunks = m > 0 ? ceil_div(m, a->chunk_rows) : 0;
+    a->short_max = pack ? g.tile() / 4 : 0;
     a->scan_ticket = reinterpret_cast<uint32_t *>(w + 16);
     a->tile = g.tile();
     a->tile_shift = 0;

@@ -356,3 +356,88 @@ def test_item_starts_on_and_off_the_cache_line(tune):
     keys = W.int_keys(int(shape.sum()), 23)
     for mode in (0, 1):
         run_both(keys, shape, mode=mode, tune=tune)
+
+
+def _short_shapes():
+    g = np.random.default_rng(7)
+    two = lambda a, b, m: np.where(g.random(m) < 0.5, a, b)   # noqa: E731
+    return {
+        "ones": np.ones(9000, np.int64),
+        "ones and empties": two(0, 1, 40_000),
+        "mostly empty": (g.random(70_000) < 0.01) * g.integers(1, 5000, 70_000),
+        "short limit": two(1024, 1025, 60),
+        "around the limit": g.integers(1000, 1060, 50),
+        "windows": two(3072, 1024, 40),
+        "window ends": np.concatenate([[3071, 1, 1, 3072, 1024, 2048, 1], np.full(30, 512)]),
+        "one past every window": np.concatenate([[1023], np.full(40, 1024)]),
+        "short rows among long ones": np.where(g.random(3000) < 0.02, g.integers(5000, 60_000, 3000),
+                                               g.integers(0, 20, 3000)),
+        "blocks of 256": np.full(1030, 3),
+        "blocks of 4096": g.integers(0, 4, 3 * 4096 + 16384 + 5),
+        "up to one launch": g.integers(0, 9, 16384),
+        "three launches": g.integers(0, 9, 16385),
+        "single": np.array([5]),
+        "one row at the end": np.concatenate([np.zeros(20_000, np.int64), [700]]),
+        "mean at the rule": np.full(33, 2048),
+        "mean past the rule": np.full(33, 2049),
+    }
+
+
+@pytest.mark.parametrize("name", list(_short_shapes()))
+def test_short_rows_share_items(name):
+    """Rows of at most 1024 elements share a work item when they start in the
+    same window of 3072 and the same block of rows: partition and filter by
+    every kind of predicate, and the shape tools, on rows of every such edge."""
+    shape = _short_shapes()[name].astype(np.int64)
+    n, m = int(shape.sum()), len(shape)
+    g = np.random.default_rng(n)
+    xi = W.int_keys(n, 130) - (1 << 30)
+    xf = W.f32_uniform(n, 131)
+    fl = (g.random(n) < 0.4).astype(np.uint8)
+    for mode in (0, 1):
+        run_both(xi, shape, "mod", mode, d=3, r=1)
+        run_both(xf, shape, "lt", mode, torch.int64, s=0.3)
+        run_both(xf, shape, "flags", mode, flags=fl)
+    st = torch.from_numpy(shape).to(DEV)
+    s_rows = g.random(m).astype(np.float32)
+    for pred, x, kind in ((P.Pred.lt_rows(torch.from_numpy(s_rows).to(DEV)), xf, O.ROW_LT),
+                          (P.Pred.mod_rows(5), xi, O.ROW_MOD)):
+        for mode in (0, 1):
+            ok, oi, ss, dl = P.segmented_partition(torch.from_numpy(x).to(DEV), st, pred, mode=mode)
+            ys, idx, seg, flags = O.partition2L_rows(x, shape, kind, 5, s_rows, mode)
+            assert P.segmented_error() == 0
+            assert np.array_equal(oi.cpu().numpy(), idx) and np.array_equal(ss.cpu().numpy(), seg)
+            assert np.array_equal(dl.cpu().numpy(), flags)
+            nout = n if mode == 0 else int(seg.sum())
+            assert np.array_equal(ok.cpu().numpy()[:nout].view(np.uint32), ys[:nout].view(np.uint32))
+    rows = np.repeat(np.arange(m), shape)
+    off = np.cumsum(shape) - shape
+    xs = g.integers(-1 << 40, 1 << 40, m)
+    descr = np.zeros(n, np.int64)
+    descr[off[shape > 0]] = xs[shape > 0]
+    for dt in (torch.int32, torch.int64):
+        out = torch.empty(n + 8, dtype=dt, device=DEV)
+        for lead in (0, 1):   # the second start is off the 16-byte boundary
+            got = P.mk_ii(st, n, dt, out=out[lead:lead + n])
+            assert np.array_equal(got.cpu().numpy(), rows)
+    assert np.array_equal(P.mk_sgm_descr(st, torch.from_numpy(xs).to(DEV), n).cpu().numpy(), descr)
+
+
+def test_more_rows_than_one_block_per_chunk():
+    """Above 2^22 rows a workgroup of the shape scan takes several blocks of 4096 rows."""
+    g = np.random.default_rng(9)
+    shape = (g.random((1 << 22) + 9000) < 0.3) * g.integers(1, 4, (1 << 22) + 9000)
+    run_both(W.int_keys(int(shape.sum()), 132), shape.astype(np.int64), "mod", 0, d=2, r=0)
+
+
+@pytest.mark.parametrize("m", [300, 20_000])
+def test_invalid_shape_of_short_rows_writes_nothing(m):
+    shape = np.full(m, 7, np.int64)
+    keys = torch.from_numpy(W.int_keys(7 * m, 133)).to(DEV)
+    for bad in (shape + (np.arange(m) == m // 2), np.where(np.arange(m) == 3, -7, shape)):
+        out = torch.full((7 * m,), -5, dtype=torch.int32, device=DEV)
+        idx, seg = out.clone(), torch.full((m,), -5, dtype=torch.int64, device=DEV)
+        P.segmented_partition(keys, torch.from_numpy(bad).to(DEV), P.Pred.mod_eq(2, 0), out_keys=out, out_idx=idx,
+                              seg_split=seg)
+        assert P.segmented_error() == -1
+        assert all(bool((t == -5).all()) for t in (out, idx, seg))
