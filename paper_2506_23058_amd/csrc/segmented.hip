@@ -66,13 +66,14 @@ struct alignas(16) SegItem {
     int64_t lo, hi;      // valid positions [lo, hi)
     int64_t base;        // first position of the item's tile (4-aligned; see row_first_base)
     int64_t tbase;       // output position of the item's first true
-    int64_t fbase;       // output position of the item's first false
+    int64_t fbase;       // output position of the item's first false (until seg_item_bases
+                         // sets it, the number of items of the row)
     int32_t row;         // row k
     int32_t kind;        // bit 0: row fits one item; bit 1: first item of its row;
                          // bit 2: row synchronised in seg_main, with its item
                          // count in bits 8..23 (tbase then holds o_k);
                          // bit 3: packed item, the whole short rows [row, first)
-    int64_t first;       // first item of the row (bit 2), end row (bit 3), else 0
+    int64_t first;       // first item of the row, or end row (bit 3)
 };
 constexpr int32_t kOwnRows = 1 | 8;        // the item holds whole rows
 constexpr int32_t kPacked = 8;
@@ -87,7 +88,7 @@ struct SegArgs {
     int64_t *seg_split;
     uint8_t *flags_out;
     int64_t *offsets;     // [m + 1] row offsets
-    int64_t *item_off;    // [m + 1] first item of each row
+    int64_t *item_off;    // [m + 1] first item of each row inside its chunk (three-launch shape scan)
     SegItem *items;       // [max_items]
     int64_t *prefix;      // [max_items + 1] exclusive scan of item counts
     unsigned long long *counts;   // [max_items] trues per counted item
@@ -110,7 +111,7 @@ struct SegArgs {
 };
 
 constexpr int64_t kShapeFusedRows = 16384;   // up to here the shape takes one launch (seg_shape)
-constexpr int kFusedPackShift = 8, kChunkPackShift = 12;
+constexpr int kFusedPackShift = 8, kChunkPackShift = 10;
 constexpr int64_t kShapeChunks = 1024;
 
 // Packed rows have at most tile / 4 elements and start in one window of
@@ -130,14 +131,13 @@ int64_t seg_max_items(int64_t n, int64_t m, int64_t tile, bool pack) {
 // the item of the row before it (`prev` elements, 0 if the block of rows
 // holds no non-empty row before this one).
 __device__ __forceinline__ int64_t row_items(const SegArgs &a, int64_t o, int64_t sk, int64_t prev) {
-    if (sk <= 0) return 0;
-    if (sk <= a.short_max) {
+    if (sk <= a.short_max) {   // (never a non-empty row when nothing is packed)
         // windows of 3 quarter tiles, counted in 32 bits (2^42 elements)
         const int32_t q = a.tile_shift - 2;
-        return prev == 0 || prev > a.short_max ||
-               static_cast<uint32_t>((o - prev) >> q) / 3 != static_cast<uint32_t>(o >> q) / 3;
+        const uint32_t w0 = static_cast<uint32_t>((o - prev) >> q) / 3, w1 = static_cast<uint32_t>(o >> q) / 3;
+        return (sk > 0) & ((prev == 0) | (prev > a.short_max) | (w0 != w1));
     }
-    return (o + sk - (o & ~int64_t{3}) + a.tile - 1) >> a.tile_shift;
+    return ((o & 3) + sk + a.tile - 1) >> a.tile_shift;
 }
 
 // True when a row of nit items has its items counted by the counting pass.
@@ -161,11 +161,12 @@ __device__ __forceinline__ int64_t row_first_base(int64_t o, int64_t sk, int64_t
 }
 
 // ------------------------------------------------------------------ shape --
-constexpr int kSetupThreads = 1024;
+constexpr int kSetupThreads = 256;   // of the three-launch shape scan
 constexpr int kSetupPer = 4;
 
-__device__ __forceinline__ int64_t block_exclusive_scan_1024(int64_t v, int64_t *lds16,
-                                                             int64_t *total) {
+// Exclusive scan over a workgroup of WAVES waves; `lds` holds WAVES words.
+template <int WAVES>
+__device__ __forceinline__ int64_t block_exclusive_scan(int64_t v, int64_t *lds, int64_t *total) {
     const int lane = threadIdx.x & 63;
     const int wave = wave_id();
     int64_t inc = v;
@@ -174,12 +175,12 @@ __device__ __forceinline__ int64_t block_exclusive_scan_1024(int64_t v, int64_t 
         const int64_t o = __shfl_up(inc, off, 64);
         if (lane >= off) inc += o;
     }
-    if (lane == 63) lds16[wave] = inc;
+    if (lane == 63) lds[wave] = inc;
     __syncthreads();
     int64_t before = 0, tot = 0;
 #pragma unroll
-    for (int w = 0; w < 16; ++w) {
-        const int64_t x = lds16[w];
+    for (int w = 0; w < WAVES; ++w) {
+        const int64_t x = lds[w];
         before += w < wave ? x : 0;
         tot += x;
     }
@@ -199,27 +200,39 @@ __device__ __forceinline__ int64_t block_sum_of(int64_t v, int64_t *lds16) {
     return tot;
 }
 
-// Record `idx` of the items begun by rows [r0, r0 + nr), whose offsets and
-// first items stand in s_off[0..nr], s_it[0..nr].
+// This thread's share of the sum of x[0..c), c <= kShapeChunks.
+__device__ __forceinline__ int64_t chunks_before(const int64_t *x, int64_t c) {
+    int64_t v = 0;
+#pragma unroll
+    for (int j = 0; j < kShapeChunks / kSetupThreads; ++j) {
+        const int64_t i = j * kSetupThreads + static_cast<int64_t>(threadIdx.x);
+        v += i < c ? x[i] : 0;
+    }
+    return v;
+}
+
+// Record `idx` of the items begun by rows [r0, r0 + own), whose offsets and
+// first items, and those of the rows up to r0 + nr >= r0 + own, stand in
+// s_off[0..nr], s_it[0..nr]; a packed item ends before r0 + nr.
 __device__ __forceinline__ void write_item(const SegArgs &a, int64_t idx, const int64_t *s_off,
-                                           const int64_t *s_it, int64_t r0, int nr) {
-    auto row_of = [&](int64_t it) {   // last row j with s_it[j] <= it
-        int lo = 0, hi = nr - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_it[mid] <= it) lo = mid;
-            else hi = mid - 1;
-        }
-        return lo;
-    };
-    const int j = row_of(idx);
+                                           const int64_t *s_it, int64_t r0, int own, int nr) {
+    // the last rows with s_it <= idx and s_it <= idx + 1: both searches at once
+    int j = 0, hi = own - 1, j1 = 0, hi1 = nr - 1;
+    while (j < hi || j1 < hi1) {
+        const int m0 = (j + hi + 1) >> 1, m1 = (j1 + hi1 + 1) >> 1;
+        const int64_t x0 = s_it[m0], x1 = s_it[m1];
+        if (x0 <= idx) j = m0;
+        else hi = m0 - 1;
+        if (x1 <= idx + 1) j1 = m1;
+        else hi1 = m1 - 1;
+    }
     const int64_t o = s_off[j], e = s_off[j + 1];
     SegItem d;
     d.fbase = 0;
     d.row = static_cast<int32_t>(r0 + j);
     if (e - o <= a.short_max) {
         // up to the row that begins the next item, or the end of the block
-        const int j1 = idx + 1 < s_it[nr] ? row_of(idx + 1) : nr;
+        if (idx + 1 >= s_it[nr]) j1 = nr;
         d.lo = o;
         d.hi = s_off[j1];
         d.base = o & ~int64_t{31};
@@ -233,15 +246,16 @@ __device__ __forceinline__ void write_item(const SegArgs &a, int64_t idx, const 
         d.lo = d.base > o ? d.base : o;
         d.hi = d.base + a.tile < e ? d.base + a.tile : e;
         d.tbase = sib ? o : 0;
+        d.fbase = nit;   // for seg_item_bases
         d.kind = (nit == 1 ? 1 : 0) | (q == 0 ? 2 : 0) | (sib ? 4 | static_cast<int32_t>(nit << 8) : 0);
-        d.first = sib ? i0 : 0;
+        d.first = i0;
     }
     a.items[idx] = d;
     a.counts[idx] = 0;
 }
 
 // More than kShapeFusedRows rows: three launches over at most kShapeChunks
-// chunks of whole 4096-row blocks.  Every workgroup adds up the chunk totals
+// chunks of whole 1024-row blocks.  Every workgroup adds up the chunk totals
 // before its own, so none waits for another and nothing carries over between
 // calls.  (One workgroup scanning the whole shape and one launch for the
 // records took 340 us for 250,000 rows; the three launches take 25 us.)
@@ -284,11 +298,11 @@ __global__ __launch_bounds__(kSetupThreads) void seg_rows_kernel(SegArgs a) {
     static_assert(kBlockRows == 1 << kChunkPackShift, "packing block");
     __shared__ int64_t lds[16];
     __shared__ int64_t sz[kBlockRows];
-    __shared__ int wlast[16];
+    __shared__ int wlast[kSetupThreads / kWave];
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
     const int64_t c = blockIdx.x, c0 = c * a.chunk_rows;
     const int64_t c1 = c0 + a.chunk_rows < a.m ? c0 + a.chunk_rows : a.m;
-    int64_t off = block_sum_of(tid < c ? a.csum[tid] : 0, lds);
+    int64_t off = block_sum_of(chunks_before(a.csum, c), lds);
     int64_t items = 0, counted = 0;
     for (int64_t b = c0; b < c1; b += kBlockRows) {
         __syncthreads();   // sz is reused
@@ -308,7 +322,7 @@ __global__ __launch_bounds__(kSetupThreads) void seg_rows_kernel(SegArgs a) {
             if (s[j] > 0) last = tid * kSetupPer + j + 1;
         }
         int64_t tot_s;
-        const int64_t off0 = off + block_exclusive_scan_1024(sum_s, lds, &tot_s);
+        const int64_t off0 = off + block_exclusive_scan<kSetupThreads / kWave>(sum_s, lds, &tot_s);
         int64_t prev = 0;
         if (a.short_max) {
             int inc = last;   // running maximum over the lanes, then the waves
@@ -335,14 +349,14 @@ __global__ __launch_bounds__(kSetupThreads) void seg_rows_kernel(SegArgs a) {
             o += s[j];
         }
         int64_t tot_it;
-        int64_t it = items + block_exclusive_scan_1024(sum_it, lds, &tot_it);
+        int64_t it = items + block_exclusive_scan<kSetupThreads / kWave>(sum_it, lds, &tot_it);
         o = off0;
 #pragma unroll
         for (int j = 0; j < kSetupPer; ++j) {
             const int64_t k = b + tid * kSetupPer + j;
             if (k < c1) {
                 a.offsets[k] = o;
-                a.item_off[k] = it;   // inside the chunk, until seg_records adds the chunk's start
+                a.item_off[k] = it;   // inside the chunk
             }
             o += s[j];
             it += nit[j];
@@ -358,34 +372,33 @@ __global__ __launch_bounds__(kSetupThreads) void seg_rows_kernel(SegArgs a) {
     }
 }
 
+// Workgroup w takes rows [256 w, 256 w + 256); the other rows of their block
+// tell where a packed item that reaches past them ends.
 __global__ __launch_bounds__(kSetupThreads) void seg_records_kernel(SegArgs a) {
     constexpr int kBlockRows = kSetupThreads * kSetupPer;
-    __shared__ int64_t lds[16];
+    __shared__ int64_t lds[kSetupThreads / kWave];
     __shared__ int64_t s_off[kBlockRows + 1], s_it[kBlockRows + 1];
     const int tid = threadIdx.x;
-    const int64_t c = blockIdx.x, c0 = c * a.chunk_rows;
-    const int64_t c1 = c0 + a.chunk_rows < a.m ? c0 + a.chunk_rows : a.m;
-    const int64_t ibase = block_sum_of(tid < c ? a.citems[tid] : 0, lds);
+    const int64_t r0 = static_cast<int64_t>(blockIdx.x) * kSetupThreads;
+    const int own = static_cast<int>(a.m - r0 < kSetupThreads ? a.m - r0 : kSetupThreads);
+    const int64_t bend = (r0 | (kBlockRows - 1)) + 1;   // end of the block of rows
+    const int nr = static_cast<int>((a.m < bend ? a.m : bend) - r0);
+    const int64_t c = r0 / a.chunk_rows, c1 = (c + 1) * a.chunk_rows < a.m ? (c + 1) * a.chunk_rows : a.m;
+    const int64_t ibase = block_sum_of(chunks_before(a.citems, c), lds);
     const int64_t iend = ibase + a.citems[c];
-    for (int64_t b = c0; b < c1; b += kBlockRows) {
-        const int nr = static_cast<int>(c1 - b < kBlockRows ? c1 - b : kBlockRows);
-        for (int j = tid; j <= nr; j += kSetupThreads) {
-            s_off[j] = a.offsets[b + j];
-            s_it[j] = b + j < c1 ? ibase + a.item_off[b + j] : iend;
-        }
-        __syncthreads();
-        for (int j = tid; j < nr; j += kSetupThreads) a.item_off[b + j] = s_it[j];
-        // (a bad shape may ask for more records than fit: the rest is left out)
-        for (int64_t idx = s_it[0] + tid; idx < s_it[nr] && idx < a.max_items; idx += kSetupThreads)
-            write_item(a, idx, s_off, s_it, b, nr);
-        __syncthreads();
+    for (int j = tid; j <= nr; j += kSetupThreads) {
+        s_off[j] = a.offsets[r0 + j];
+        s_it[j] = r0 + j < c1 ? ibase + a.item_off[r0 + j] : iend;
     }
-    if (c1 < a.m) return;
-    const int64_t bad = block_sum_of(tid < a.nchunks ? a.cbad[tid] : 0, lds);
-    const int64_t counted = block_sum_of(tid < a.nchunks ? a.ccounted[tid] : 0, lds);
+    __syncthreads();
+    // (a bad shape may ask for more records than fit: the rest is left out)
+    for (int64_t idx = s_it[0] + tid; idx < s_it[own] && idx < a.max_items; idx += kSetupThreads)
+        write_item(a, idx, s_off, s_it, r0, own, nr);
+    if (r0 + own < a.m) return;
+    const int64_t bad = block_sum_of(chunks_before(a.cbad, a.nchunks), lds);
+    const int64_t counted = block_sum_of(chunks_before(a.ccounted, a.nchunks), lds);
     if (tid == 0) {
         const bool ok = !bad && a.offsets[a.m] == a.n && iend <= a.max_items;
-        a.item_off[a.m] = iend;
         *a.num_items = ok ? iend : 0;
         *a.num_counted = ok ? static_cast<unsigned long long>(counted) : 0ull;
         *a.err = ok ? 0 : kErrShape;
@@ -446,7 +459,7 @@ __global__ __launch_bounds__(kShapeThreads) void seg_shape_kernel(SegArgs a) {
     int64_t sum_s = 0;
     for (int64_t k = k0; k < k1; ++k) sum_s += sz[k];
     int64_t tot_s;
-    const int64_t off0 = block_exclusive_scan_1024(sum_s, lds_a, &tot_s);
+    const int64_t off0 = block_exclusive_scan<16>(sum_s, lds_a, &tot_s);
     // the last non-empty size before this thread's rows in their block of rows
     int64_t prev0 = 0;
     if (a.short_max) {
@@ -459,16 +472,17 @@ __global__ __launch_bounds__(kShapeThreads) void seg_shape_kernel(SegArgs a) {
         int64_t o = off0, prev = prev0;
         for (int64_t k = k0; k < k1; ++k) {
             if (at_block(k)) prev = 0;
-            const int64_t nit = row_items(a, o, sz[k], prev);
+            const int64_t sk = sz[k];
+            const int64_t nit = row_items(a, o, sk, prev);
             sum_it += nit;
             if (row_counted(a, nit)) counted += nit;
-            if (sz[k] > 0) prev = sz[k];
-            o += sz[k];
+            if (sk > 0) prev = sk;
+            o += sk;
         }
     }
     int64_t tot_it;
-    const int64_t it0 = block_exclusive_scan_1024(sum_it, lds_b, &tot_it);
-    {
+    const int64_t it0 = block_exclusive_scan<16>(sum_it, lds_b, &tot_it);
+    if (k1 > r0) {   // (the other threads' rows are other workgroups')
         int64_t o = off0, it = it0, prev = prev0;
         for (int64_t k = k0; k < k1; ++k) {
             if (at_block(k)) prev = 0;
@@ -476,11 +490,11 @@ __global__ __launch_bounds__(kShapeThreads) void seg_shape_kernel(SegArgs a) {
                 s_off[k - r0] = o;
                 s_it[k - r0] = it;
                 a.offsets[k] = o;
-                a.item_off[k] = it;
             }
-            it += row_items(a, o, sz[k], prev);
-            if (sz[k] > 0) prev = sz[k];
-            o += sz[k];
+            const int64_t sk = sz[k];
+            it += row_items(a, o, sk, prev);
+            if (sk > 0) prev = sk;
+            o += sk;
         }
     }
     if (tid == 0) {
@@ -489,11 +503,10 @@ __global__ __launch_bounds__(kShapeThreads) void seg_shape_kernel(SegArgs a) {
     }
     if (last) {
         int64_t tot_counted;
-        (void)block_exclusive_scan_1024(counted, lds_a, &tot_counted);
+        (void)block_exclusive_scan<16>(counted, lds_a, &tot_counted);
         if (tid == 0) {
             const bool ok = !bad && tot_s == a.n && tot_it <= a.max_items;
             a.offsets[a.m] = tot_s;
-            a.item_off[a.m] = tot_it;
             *a.num_items = ok ? tot_it : 0;
             *a.num_counted = ok ? static_cast<unsigned long long>(tot_counted) : 0ull;
             *a.err = ok ? 0 : kErrShape;
@@ -503,7 +516,7 @@ __global__ __launch_bounds__(kShapeThreads) void seg_shape_kernel(SegArgs a) {
     // this workgroup's item records (a bad shape may ask for more than fit:
     // those are not written, and the last workgroup reports the error)
     for (int64_t idx = s_it[0] + tid; idx < s_it[nr] && idx < a.max_items; idx += kShapeThreads)
-        write_item(a, idx, s_off, s_it, r0, nr);
+        write_item(a, idx, s_off, s_it, r0, nr, nr);
 }
 
 // ------------------------------------------------------------------ count --
@@ -573,7 +586,7 @@ __global__ __launch_bounds__(1024) void seg_scan_items_kernel(SegArgs a) {
         sum += v[j];
     }
     int64_t tot;
-    const int64_t in_chunk = block_exclusive_scan_1024(sum, lds, &tot);
+    const int64_t in_chunk = block_exclusive_scan<16>(sum, lds, &tot);
     if (wave == 0) {
         // a chunk holds at most 8192 * 16384 = 2^27 trues: below 2^32, as the
         // look-back's aggregates must be; 64 of them may pass 2^32, so the
@@ -607,7 +620,7 @@ __global__ __launch_bounds__(256) void seg_item_bases_kernel(SegArgs a) {
     if (i >= nitems) return;
     const SegItem d = a.items[i];
     const int64_t k = d.row;
-    const int64_t i0 = a.item_off[k], i1 = a.item_off[k + 1];
+    const int64_t i0 = d.first, i1 = i0 + d.fbase;   // the row's items (not of a packed item)
     if (a.mode == IXP_MODE_PARTITION) {
         if (d.kind & (kOwnRows | 4)) return;   // finished by the main kernel
         const int64_t ok = a.offsets[k];
@@ -1294,7 +1307,8 @@ int launch_shape(const SegArgs &a, hipStream_t st) {
     const dim3 chunks(static_cast<uint32_t>(a.nchunks));
     IXP_LAUNCH("seg_sizes", seg_sizes_kernel, chunks, dim3(kSetupThreads), 0, st, a);
     IXP_LAUNCH("seg_rows", seg_rows_kernel, chunks, dim3(kSetupThreads), 0, st, a);
-    IXP_LAUNCH("seg_records", seg_records_kernel, chunks, dim3(kSetupThreads), 0, st, a);
+    IXP_LAUNCH("seg_records", seg_records_kernel, dim3(static_cast<uint32_t>(ceil_div(a.m, kSetupThreads))),
+               dim3(kSetupThreads), 0, st, a);
     return launch_status();
 }
 
