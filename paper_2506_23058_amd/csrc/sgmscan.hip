@@ -10,9 +10,9 @@
 //             the values from there;
 //   scan   -- one workgroup: exclusive scan of the C aggregates under the
 //             lifted operator (8 per thread, wave shuffles, LDS);
-//   rescan -- one workgroup per chunk: its tiles in order, each loaded through
-//             LDS (coalesced), 8 consecutive elements per thread, waves
-//             combined with shuffles and LDS, starting from the chunk's prefix.
+//   rescan -- one workgroup per chunk: a wave holds rows of 128 consecutive
+//             elements, two per lane, and hands its last running sum to the
+//             waves after it.
 // No inter-workgroup waiting; the values from each chunk's last flag on are
 // read twice, everything else once.
 #include "device.hpp"
@@ -21,9 +21,7 @@
 namespace ixp {
 namespace {
 
-constexpr int kSgThreads = 1024;
-constexpr int kSgPer = 8;
-constexpr int64_t kSgTile = kSgThreads * kSgPer;
+constexpr int64_t kSgTile = 8192;      // chunks are multiples of this
 constexpr int64_t kSgMaxChunks = 8192;
 
 struct Pair {
@@ -44,33 +42,28 @@ struct SgArgs {
     int32_t *agg_f;     // [chunks] aggregate flag
 };
 
-// Block-wide reductions of 1024 threads through LDS.
-__device__ __forceinline__ int64_t block_max_1024(int64_t x, int64_t *lds16) {
+// Reduce.  256 threads a chunk, so that eight chunks share a CU: with 1024 the
+// chain flags, maximum, values, sum ran two chunks at a time (2^25 elements, a
+// flag every 335: 39 us; now 14).
+constexpr int kRedThreads = 256;
+
+__device__ __forceinline__ int64_t block_max(int64_t x, int64_t *lds) {
     for (int off = 32; off > 0; off >>= 1) {
         const int64_t o = __shfl_xor(x, off, kWave);
         x = o > x ? o : x;
     }
-    if ((threadIdx.x & 63) == 0) lds16[threadIdx.x >> 6] = x;
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = x;
     __syncthreads();
-    int64_t r = lds16[0];
-    for (int w = 1; w < 16; ++w) r = lds16[w] > r ? lds16[w] : r;
-    __syncthreads();
-    return r;
-}
-__device__ __forceinline__ int64_t block_sum_1024(int64_t x, int64_t *lds16) {
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, kWave);
-    if ((threadIdx.x & 63) == 0) lds16[threadIdx.x >> 6] = x;
-    __syncthreads();
-    int64_t r = 0;
-    for (int w = 0; w < 16; ++w) r += lds16[w];
+    int64_t r = lds[0];
+    for (int w = 1; w < kRedThreads / kWave; ++w) r = lds[w] > r ? lds[w] : r;
     __syncthreads();
     return r;
 }
 
-// The 8 flags of a thread's 8 consecutive elements, as one 8-byte load when
+// The 8 flags of 8 consecutive elements, as one 8-byte load when
 // the flag array is 8-byte aligned and the group lies inside [0, len).
 __device__ __forceinline__ uint64_t flag_group(const uint8_t *f, int64_t p, int64_t len, bool vec) {
-    if (vec && p + 8 <= len) return *reinterpret_cast<const uint64_t *>(f + p);
+    if (vec && p + 8 <= len) return __builtin_nontemporal_load(reinterpret_cast<const uint64_t *>(f + p));
     uint64_t x = 0;
 #pragma unroll
     for (int k = 0; k < 8; ++k)
@@ -78,25 +71,47 @@ __device__ __forceinline__ uint64_t flag_group(const uint8_t *f, int64_t p, int6
     return x;
 }
 
-__global__ __launch_bounds__(kSgThreads) void sg_reduce_kernel(SgArgs a) {
-    __shared__ int64_t lds[16];
+__global__ __launch_bounds__(kRedThreads) void sg_reduce_kernel(SgArgs a) {
+    constexpr int kLoads = kSgTile / (8 * kRedThreads);   // flag groups of a tile per thread
+    constexpr int kVals = 8;                              // values in flight per thread
+    __shared__ int64_t lds[kRedThreads / kWave];
+    const int tid = threadIdx.x;
     const int64_t c = blockIdx.x;
     const int64_t lo = c * a.chunk;
     const int64_t hi = lo + a.chunk < a.n ? lo + a.chunk : a.n;
-    // last flagged position of the chunk (lo - 1 if none), from 8 flag bytes per thread and step
+    // last flagged position of the chunk (lo - 1 if none)
     int64_t last = lo - 1;
     const bool fvec = (reinterpret_cast<uintptr_t>(a.flags) & 7) == 0;
-    for (int64_t p = static_cast<int64_t>(threadIdx.x) * 8; lo + p < hi; p += kSgThreads * 8) {
-        const uint64_t fg = flag_group(a.flags + lo, p, hi - lo, fvec);
-        if (fg) last = lo + p + (63 - __builtin_clzll(fg)) / 8;
+    for (int64_t t = lo; t < hi; t += kSgTile) {
+        uint64_t fg[kLoads];
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) {
+            const int64_t p = t - lo + (static_cast<int64_t>(j) * kRedThreads + tid) * 8;
+            fg[j] = lo + p < hi ? flag_group(a.flags + lo, p, hi - lo, fvec) : 0;
+        }
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) {
+            const int64_t p = t + (static_cast<int64_t>(j) * kRedThreads + tid) * 8;
+            if (fg[j]) last = p + (63 - __builtin_clzll(fg[j])) / 8;
+        }
     }
-    last = block_max_1024(last, lds);
+    last = block_max(last, lds);
     // a flagged element restarts the sum with its own value
     const int64_t start = last >= lo ? last : lo;
     int64_t s = 0;
-    for (int64_t p = start + threadIdx.x; p < hi; p += kSgThreads) s += a.xs[p];
-    s = block_sum_1024(s, lds);
-    if (threadIdx.x == 0) {
+    for (int64_t p = start + tid; p < hi; p += kVals * kRedThreads) {
+        int64_t v[kVals];
+#pragma unroll
+        for (int j = 0; j < kVals; ++j) v[j] = p + j * kRedThreads < hi ? a.xs[p + j * kRedThreads] : 0;
+#pragma unroll
+        for (int j = 0; j < kVals; ++j) s += v[j];
+    }
+    s = wave_sum_i64(s);
+    if ((tid & 63) == 0) lds[tid >> 6] = s;
+    __syncthreads();
+    if (tid == 0) {
+        s = 0;
+        for (int w = 0; w < kRedThreads / kWave; ++w) s += lds[w];
         a.agg_v[c] = s;
         a.agg_f[c] = last >= lo ? 1 : 0;
     }
@@ -143,67 +158,130 @@ __global__ __launch_bounds__(1024) void sg_chunk_scan_kernel(SgArgs a) {
     }
 }
 
-__global__ __launch_bounds__(kSgThreads) void sg_rescan_kernel(SgArgs a) {
-    static_assert(kSgPer == 8, "one 8-byte flag group per thread");
-    __shared__ int64_t sv[kSgTile];
-    __shared__ int64_t wv[kSgThreads / kWave];
-    __shared__ int32_t wf[kSgThreads / kWave];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = wave_id();
+// Inclusive scan (+) over the lanes of a wave by DPP: four shifts inside the
+// rows of 16 lanes, then lane 15 of a row to the next row and lane 31 to the
+// upper half.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int64_t dpp_i64(int64_t v) {
+    const uint64_t u = static_cast<uint64_t>(v);
+    const uint32_t lo = static_cast<uint32_t>(
+        __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(u)), CTRL, ROWS, 0xF, false));
+    const uint32_t hi = static_cast<uint32_t>(
+        __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(u >> 32)), CTRL, ROWS, 0xF, false));
+    return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+}
+__device__ __forceinline__ int64_t wave_scan_i64(int64_t v) {
+    v += dpp_i64<0x111, 0xF>(v);
+    v += dpp_i64<0x112, 0xF>(v);
+    v += dpp_i64<0x114, 0xF>(v);
+    v += dpp_i64<0x118, 0xF>(v);
+    v += dpp_i64<0x142, 0xA>(v);
+    v += dpp_i64<0x143, 0xC>(v);
+    return v;
+}
+
+// Rescan.  The sums wrap, so a running sum since the last flag is a difference
+// of plain prefix sums: a row of 128 elements takes one plain scan of the
+// lanes' pairs, and an unflagged element looks up the prefix at the nearest
+// flagged lane below it (from the ballot of the flags).  Loads and stores are
+// 16 bytes a lane and consecutive, nothing is transposed, and the only barrier
+// of a step publishes the waves' last running sums.
+// 2^25 int64 values, a flag every 335: 101 us (17 bytes an element, 5.6 TB/s);
+// 8 consecutive elements per thread, transposed through 64 KiB of LDS with four
+// barriers a tile, took 165 us.
+constexpr int kScThreads = 512;
+constexpr int kScRows = 4;
+constexpr int kScWave = kScRows * 2 * kWave;              // elements of a wave
+constexpr int kScStep = kScThreads / kWave * kScWave;     // elements of a step
+static_assert(kSgTile % kScStep == 0, "whole steps");
+
+__global__ __launch_bounds__(kScThreads) void sg_rescan_kernel(SgArgs a) {
+    constexpr int kWaves = kScThreads / kWave;
+    typedef int64_t i64x2 __attribute__((ext_vector_type(2)));
+    __shared__ int64_t wv[2][kWaves];   // by parity of the step
+    __shared__ int32_t wf[2][kWaves];
+    const int lane = threadIdx.x & (kWave - 1), wave = wave_id();
     const int64_t c = blockIdx.x;
     const int64_t lo_c = c * a.chunk;
     const int64_t hi_c = lo_c + a.chunk < a.n ? lo_c + a.chunk : a.n;
-    int64_t carry = a.agg_v[c];   // value before the chunk (a flag inside the chunk resets it)
-    const bool fvec = (reinterpret_cast<uintptr_t>(a.flags) & 7) == 0;
-    for (int64_t lo = lo_c; lo < hi_c; lo += kSgTile) {
-        const int64_t len = hi_c - lo < kSgTile ? hi_c - lo : kSgTile;
-        const uint64_t fg = flag_group(a.flags + lo, static_cast<int64_t>(tid) * kSgPer, len, fvec);
+    int64_t carry = a.agg_v[c];   // running sum before the chunk (a flag inside the chunk resets it)
+    const bool fvec = (reinterpret_cast<uintptr_t>(a.flags) & 1) == 0;
+    const bool xvec = (reinterpret_cast<uintptr_t>(a.xs) & 15) == 0;
+    const bool ovec = (reinterpret_cast<uintptr_t>(a.out) & 15) == 0;
+    int par = 0;
+    for (int64_t lo = lo_c; lo < hi_c; lo += kScStep, par ^= 1) {
+        const int64_t e0 = lo + wave * kScWave + 2 * lane;
+        const bool whole = lo + (wave + 1) * kScWave <= hi_c;   // (wave-uniform)
+        int64_t v[kScRows][2];
+        uint32_t fl[kScRows];   // the pair's flags: nonzero low byte, nonzero second byte
+        if (whole && xvec && fvec) {
 #pragma unroll
-        for (int k = 0; k < kSgPer; ++k) {
-            const int l = k * kSgThreads + tid;
-            sv[l] = l < len ? __builtin_nontemporal_load(a.xs + lo + l) : 0;
+            for (int r = 0; r < kScRows; ++r) {
+                const i64x2 x = __builtin_nontemporal_load(reinterpret_cast<const i64x2 *>(a.xs + e0 + r * 2 * kWave));
+                fl[r] = __builtin_nontemporal_load(reinterpret_cast<const uint16_t *>(a.flags + e0 + r * 2 * kWave));
+                v[r][0] = x.x;
+                v[r][1] = x.y;
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < kScRows; ++r) {
+                const int64_t e = e0 + r * 2 * kWave;
+                v[r][0] = e < hi_c ? a.xs[e] : 0;
+                v[r][1] = e + 1 < hi_c ? a.xs[e + 1] : 0;
+                fl[r] = (e < hi_c ? a.flags[e] : 0u) | (e + 1 < hi_c ? static_cast<uint32_t>(a.flags[e + 1]) << 8 : 0u);
+            }
+        }
+        // run: running sum before the row, from the wave's start; seen: some
+        // flag before the row; open: bit r*2+q, the element adds what comes
+        // before the wave
+        int64_t run = 0;
+        bool seen = false;
+        uint32_t open = 0;
+#pragma unroll
+        for (int r = 0; r < kScRows; ++r) {
+            const bool f0 = (fl[r] & 0xFFu) != 0, f1 = (fl[r] >> 8) != 0;
+            const int64_t inc = wave_scan_i64(v[r][0] + v[r][1]);
+            const int64_t excl = inc - v[r][0] - v[r][1];
+            const int64_t total = static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(inc), kWave - 1));
+            const uint64_t m = ballot(f0 | f1);
+            const int64_t at = f1 ? excl + v[r][0] : excl;   // prefix before this lane's last flag
+            const uint64_t below = m & ((1ull << lane) - 1);
+            const int64_t from = __shfl(at, below ? 63 - __builtin_clzll(below) : 0, kWave);
+            const int64_t x0 = f0 ? v[r][0] : v[r][0] + excl + (below ? -from : run);
+            const bool o0 = !(f0 | seen | (below != 0));
+            open |= (static_cast<uint32_t>(o0) | static_cast<uint32_t>(o0 & !f1) << 1) << (2 * r);
+            v[r][1] += f1 ? 0 : x0;
+            v[r][0] = x0;
+            run = m ? total - static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(at), 63 - __builtin_clzll(m)))
+                    : run + total;
+            seen |= m != 0;
+        }
+        if (lane == 0) {
+            wv[par][wave] = run;
+            wf[par][wave] = seen ? 1 : 0;
         }
         __syncthreads();
-        Pair run{false, 0};
-        Pair el[kSgPer];
+        int64_t before = carry;   // running sum before this wave
 #pragma unroll
-        for (int k = 0; k < kSgPer; ++k) {
-            const int l = tid * kSgPer + k;
-            run = combine(run, Pair{((fg >> (8 * k)) & 0xFFu) != 0, sv[l]});
-            el[k] = run;
+        for (int w = 0; w < kWaves; ++w) {
+            const int64_t x = wv[par][w];
+            const bool f = wf[par][w] != 0;
+            carry = f ? x : carry + x;
+            if (w < wave) before = carry;
         }
-        Pair inc = run;
 #pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            Pair o;
-            o.f = __shfl_up(static_cast<int>(inc.f), off, kWave) != 0;
-            o.v = __shfl_up(inc.v, off, kWave);
-            if (lane >= off) inc = combine(o, inc);
+        for (int r = 0; r < kScRows; ++r) {
+            const int64_t e = e0 + r * 2 * kWave;
+            i64x2 y;
+            y.x = v[r][0] + ((open >> (2 * r)) & 1u ? before : 0);
+            y.y = v[r][1] + ((open >> (2 * r + 1)) & 1u ? before : 0);
+            if (whole && ovec) {
+                stream_store(reinterpret_cast<i64x2 *>(a.out + e), y);
+            } else {
+                if (e < hi_c) stream_store(a.out + e, static_cast<int64_t>(y.x));
+                if (e + 1 < hi_c) stream_store(a.out + e + 1, static_cast<int64_t>(y.y));
+            }
         }
-        Pair before_lane{__shfl_up(static_cast<int>(inc.f), 1, kWave) != 0, __shfl_up(inc.v, 1, kWave)};
-        if (lane == 0) before_lane = Pair{false, 0};
-        if (lane == kWave - 1) {
-            wv[wave] = inc.v;
-            wf[wave] = inc.f ? 1 : 0;
-        }
-        __syncthreads();
-        Pair before_wave{false, 0}, tile{false, 0};
-#pragma unroll
-        for (int w = 0; w < kSgThreads / kWave; ++w) {
-            const Pair x{wf[w] != 0, wv[w]};
-            if (w < wave) before_wave = combine(before_wave, x);
-            tile = combine(tile, x);
-        }
-        const Pair prefix = combine(Pair{false, carry}, combine(before_wave, before_lane));
-#pragma unroll
-        for (int k = 0; k < kSgPer; ++k) sv[tid * kSgPer + k] = combine(prefix, el[k]).v;
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kSgPer; ++k) {
-            const int l = k * kSgThreads + tid;
-            if (l < len) stream_store(a.out + lo + l, sv[l]);
-        }
-        carry = combine(Pair{false, carry}, tile).v;
-        __syncthreads();   // LDS reused by the next tile
     }
 }
 
@@ -243,8 +321,8 @@ extern "C" int ixp_sgm_sum(const uint8_t *d_flags, const int64_t *d_xs, int64_t 
     a.agg_f = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + round_up(static_cast<size_t>(a.chunks) * 8, 256));
     hipStream_t st = as_stream(stream);
     const dim3 grid(static_cast<uint32_t>(a.chunks));
-    IXP_LAUNCH("sgm_reduce", sg_reduce_kernel, grid, dim3(kSgThreads), 0, st, a);
+    IXP_LAUNCH("sgm_reduce", sg_reduce_kernel, grid, dim3(kRedThreads), 0, st, a);
     IXP_LAUNCH("sgm_chunk_scan", sg_chunk_scan_kernel, dim3(1), dim3(1024), 0, st, a);
-    IXP_LAUNCH("sgm_rescan", sg_rescan_kernel, grid, dim3(kSgThreads), 0, st, a);
+    IXP_LAUNCH("sgm_rescan", sg_rescan_kernel, grid, dim3(kScThreads), 0, st, a);
     return launch_status();
 }

@@ -119,3 +119,27 @@ def test_sgm_sum_chunks_of_several_tiles():
     print(f"[sgm_sum] n={n} multi-tile chunks", flush=True)
     got = P.sgm_sum(torch.from_numpy(flags).to(DEV), torch.from_numpy(xs).to(DEV))
     assert np.array_equal(got.cpu().numpy(), O.sgm_sum(flags, xs))
+
+
+@pytest.mark.parametrize("n", [1, 127, 128, 129, 511, 513, 4095, 4096, 4097, 8191, 8193, 3 * 8192 + 130])
+def test_sgm_sum_rows_waves_and_steps(n):
+    """The rescan works in rows of 128 (a pair per lane), waves of 512 and steps
+    of 4096 elements: flags on both sides of those edges, none, all, and sums
+    that wrap, with values and output on and off the 16-byte boundary."""
+    g = np.random.default_rng(n)
+    xs = g.integers(-1 << 63, (1 << 63) - 1, n, dtype=np.int64)
+    edges = np.zeros(n, np.uint8)
+    for e in (0, 1, 127, 128, 511, 512, 4095, 4096, 8191, 8192, n - 1):
+        edges[e:e + 1] = 200
+    for flags in (edges, np.zeros(n, np.uint8), np.ones(n, np.uint8), (g.random(n) < 0.01).astype(np.uint8),
+                  (g.random(n) < 0.6).astype(np.uint8)):
+        want = O.sgm_sum(flags, xs)
+        for off in (0, 1):
+            xt = torch.from_numpy(np.concatenate([np.zeros(off, np.int64), xs])).to(DEV)[off:]
+            ft = torch.from_numpy(np.concatenate([np.zeros(off, np.uint8), flags])).to(DEV)[off:]
+            buf = torch.full((n + 4,), -7, dtype=torch.int64, device=DEV)
+            got = P.sgm_sum(ft, xt, out=buf[off:off + n])
+            assert np.array_equal(got.cpu().numpy(), want)
+            assert (buf[:off] == -7).all() and (buf[off + n:] == -7).all()
+            P.sgm_sum(ft, xt, out=xt)   # in place
+            assert np.array_equal(xt.cpu().numpy(), want)
