@@ -412,6 +412,23 @@ int ixp_match_min(uint8_t *d_flags, const int64_t *d_hist, int64_t n_hist,
                   const void *idx, int32_t idx_t, const int64_t *vals,
                   int64_t m, void *stream);
 
+/* get_smallest_pairs (Sections 5.4 and 6, maximal matching) in one call:
+ *   d_hist[v] = min(neutral, the least is[k] with es[k] = v), v in [0, n_verts);
+ *   entry k is kept iff 0 <= es[k] < n_verts and d_hist[es[k]] = is[k];
+ *   es_out / is_out = the kept entries' es and is, in input order; *d_split =
+ *   how many (positions past it are not written).
+ * The same as ixp_hist_min, ixp_match_min, ixp_partition (FILTER) and two
+ * ixp_scatter_inj calls, without random accesses to d_hist.  es_out and is_out
+ * have room for m entries and overlap nothing else.  Workspace:
+ * ixp_smallest_pairs_workspace(m, n_verts) bytes (about 13 per entry), 256-byte
+ * aligned.  m > 0 and 0 < n_verts <= 2^25; otherwise the workspace size is 0
+ * and the call IXP_EUNSUPPORTED.  5 kernels. */
+size_t ixp_smallest_pairs_workspace(int64_t m, int64_t n_verts);
+int ixp_smallest_pairs(const int64_t *es, const int64_t *is, int64_t m,
+                       int64_t n_verts, int64_t neutral, int64_t *d_hist,
+                       int64_t *es_out, int64_t *is_out, int64_t *d_split,
+                       void *ws, size_t ws_bytes, void *stream);
+
 size_t ixp_scatter_checked_workspace(int64_t n_dst);
 
 /* The dynamically verified scatter of the evaluation's Base variant

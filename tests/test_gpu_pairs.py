@@ -41,3 +41,44 @@ def test_pairs_edge_cases():
     g = np.random.default_rng(5)
     es = np.where(g.random(10_001) < 0.1, -3, g.integers(0, 100, 10_001))   # out-of-range endpoints
     _run(100, 20_002, es, g.permutation(20_002)[:10_001])
+
+
+def _fused(n_verts, n_es, es, is_):
+    sp = P.SmallestPairs(n_verts, n_es, torch.from_numpy(es).to(DEV), torch.from_numpy(is_).to(DEV))
+    assert sp.fused
+    for _ in range(2):   # the second call finds the buffers of the first
+        eo, io = sp()
+        re, ri = O.get_smallest_pairs(n_verts, n_es, es, is_)
+        assert np.array_equal(eo.cpu().numpy(), re) and np.array_equal(io.cpu().numpy(), ri)
+    assert np.array_equal(sp.hist.cpu().numpy(), O.hist_min(n_verts, n_es, es, is_))
+
+
+@pytest.mark.parametrize("n_verts", [1, 2047, 2049, 5000, 1 << 20, (1 << 24) - 1, (1 << 24) + 1, 1 << 25])
+@pytest.mark.parametrize("m", [1, 5, 16383, 16384, 16385, 70_000])
+def test_fused_pairs_match_oracle(n_verts, m, monkeypatch):
+    """The fused call at the edges of its chunks (16384 entries) and bucket
+    widths (1 to 2^14 vertices): uniform endpoints, runs of one bucket longer than 16
+    and than 256 entries, endpoints out of range, equal ids, ids beyond the
+    neutral element and negative ones."""
+    monkeypatch.setattr(P.SmallestPairs, "FUSED_MIN", 0)
+    g = np.random.default_rng(n_verts + m)
+    es = g.integers(0, n_verts, m)
+    _fused(n_verts, m, es, g.permutation(m))
+    _fused(n_verts, m, np.where(g.random(m) < 0.5, n_verts - 1, es), g.integers(-9, m + 9, m))
+    _fused(n_verts, m // 2, np.where(g.random(m) < 0.2, g.integers(-3, 2 * n_verts + 3, m), es),
+           g.integers(0, m // 4 + 1, m))
+
+
+def test_fused_pairs_large():
+    g = np.random.default_rng(3)
+    m = (1 << 21) + 12_345
+    es = np.where(g.random(m) < 0.3, g.integers(0, 9, m), g.integers(0, 300_000, m))
+    _fused(300_000, m, es, g.permutation(m))
+
+
+def test_pairs_beyond_the_fused_range(monkeypatch):
+    monkeypatch.setattr(P.SmallestPairs, "FUSED_MIN", 0)
+    g = np.random.default_rng(4)
+    es, is_ = g.integers(0, (1 << 25) + 1, 5000), g.permutation(5000)
+    assert not P.SmallestPairs((1 << 25) + 1, 5000, torch.from_numpy(es).to(DEV), torch.from_numpy(is_).to(DEV)).fused
+    _run((1 << 25) + 1, 5000, es, is_)
