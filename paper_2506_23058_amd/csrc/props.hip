@@ -6,12 +6,12 @@
 // wave minimum and an atomicMin, so verdicts do not depend on scheduling.
 //
 // Inj and Bij need to know which in-Rcd values occur more than once.  For
-// large arrays whose Rcd spans at most 4096 buckets of 2^20 values, the pass
+// large arrays whose Rcd spans at most 4096 buckets of up to 2^20 values, the pass
 // over X also groups each workgroup's chunk of in-Rcd values by bucket in LDS
 // and writes the chunk's values bucket by bucket into its own region, with a
 // per-chunk table of where each bucket starts (no global histogram is
 // needed); then one workgroup per bucket reads that bucket's runs from every
-// chunk into a 128 KiB LDS bitmap.  Smaller arrays insert into a bitmap over
+// chunk into an LDS bitmap.  Smaller arrays insert into a bitmap over
 // Rcd in global memory directly.  A bit found already set says that its value
 // repeats, not which occurrence is the first, so each repeated value is
 // listed once (a second bitmap marks it).  One more streaming pass then looks
@@ -37,7 +37,7 @@ namespace {
 
 constexpr uint64_t kNone = 0x7FFFFFFFFFFFFFFFull;
 constexpr int kPropsBlock = 256;
-constexpr int kBucketShift = 20;              // 2^20 values: a 128 KiB LDS bitmap
+constexpr int kBucketShift = 20;              // at most 2^20 values a bucket: a 128 KiB LDS bitmap
 constexpr int kMaxBuckets = 4096;
 constexpr int kChunk = 16384;                 // elements per props_scan workgroup
 constexpr int kScanThreads = 512;             // two workgroups per CU (64 KiB of LDS each)
@@ -74,9 +74,10 @@ struct PropsArgs {
     unsigned long long *first64;   // ... 64-bit when n >= 2^32
     int64_t width;        // hi - lo when a bitmap is in use
     // Chunked Inj/Bij (props_scan / props_check): values of Rcd grouped in
-    // buckets of 2^kBucketShift consecutive values.
+    // buckets of 2^bshift consecutive values.
     int32_t bucketed;
     int32_t nbuckets;
+    int32_t bshift;
     int64_t nchunks;
     uint16_t *ctab;       // [(nbuckets + 1) * nchunks]: bucket starts per chunk; last row: chunk totals
     uint32_t *records;    // [nchunks * kChunk]: value - lo - bucket base (20 bits)
@@ -296,7 +297,7 @@ __global__ __launch_bounds__(kPropsBlock) void props_pass1_kernel(PropsArgs a) {
 
 // Chunked Inj/Bij.  Random device-scope atomics on a bitmap in HBM run far
 // below the memory bandwidth, so the in-Rcd values are routed to one
-// workgroup per bucket of 2^20 values, whose bitmap sits in LDS.
+// workgroup per bucket of up to 2^20 values, whose bitmap sits in LDS.
 //
 // props_scan: workgroup c owns elements [c kChunk, (c+1) kChunk) (chunks in
 // an XCD-aware order).  Besides Range / Monotonic / Img it ranks every in-Rcd
@@ -393,8 +394,8 @@ void props_scan_kernel(PropsArgs a) {
                 if (want_img && !(a.ilo <= v && v < a.ihi) && static_cast<unsigned long long>(i) < c_img)
                     c_img = i;
                 const uint64_t o = static_cast<uint64_t>(v - a.lo);
-                const uint32_t bk = static_cast<uint32_t>(o >> kBucketShift);
-                off[k] = static_cast<uint32_t>(o & ((1u << kBucketShift) - 1));
+                const uint32_t bk = static_cast<uint32_t>(o >> a.bshift);
+                off[k] = static_cast<uint32_t>(o) & ((1u << a.bshift) - 1);
                 meta[k] = (bk << 16) | atomicAdd(bstart + bk, 1u);
             }
         }
@@ -415,8 +416,8 @@ void props_scan_kernel(PropsArgs a) {
                 if (want_img && !(a.ilo <= v && v < a.ihi) && static_cast<unsigned long long>(i) < c_img)
                     c_img = i;
                 const uint64_t o = static_cast<uint64_t>(v - a.lo);
-                const uint32_t bk = static_cast<uint32_t>(o >> kBucketShift);
-                toff[j] = static_cast<uint32_t>(o & ((1u << kBucketShift) - 1));
+                const uint32_t bk = static_cast<uint32_t>(o >> a.bshift);
+                toff[j] = static_cast<uint32_t>(o) & ((1u << a.bshift) - 1);
                 tmeta[j] = (bk << 16) | atomicAdd(bstart + bk, 1u);
             }
         }
@@ -486,8 +487,8 @@ void props_scan_kernel(PropsArgs a) {
     }
 }
 
-// props_check: workgroup b sets the bits of bucket b's values in a 128 KiB
-// LDS bitmap.  The bucket's records are one run per chunk; a wave takes 16
+// props_check: workgroup b sets the bits of bucket b's values in an LDS
+// bitmap of up to 128 KiB.  The bucket's records are one run per chunk; a wave takes 16
 // chunks at a time, 4 lanes per chunk, and reads each run as the aligned
 // 16-byte quads that cover it (records of neighbouring buckets in the edge
 // quads are skipped), each lane up to kCheckDepth quads per pass, all loads
@@ -497,17 +498,19 @@ void props_scan_kernel(PropsArgs a) {
 // once.  A bit found set lists its value as repeated.  For Bij it also finds
 // the least value of Img inside the bucket whose bit is clear; the
 // workgroup of the last bucket adds up the chunks' in-Rcd totals.
+// Neighbouring buckets meet in the cache lines at the ends of their runs, so the
+// buckets of one XCD are consecutive (2^28 entries: 268 -> 228 us).
 constexpr int kCheckThreads = 1024;
-constexpr int kBucketWords = (1 << kBucketShift) / 32;
 constexpr int kCheckLanes = 4;
 constexpr int kCheckDepth = 8;
 
+template <int SHIFT>   // at least a.bshift
 __global__ __launch_bounds__(kCheckThreads) void props_check_kernel(PropsArgs a) {
-    __shared__ uint32_t bits[kBucketWords];
+    __shared__ uint32_t bits[(1 << SHIFT) / 32];
     __shared__ unsigned long long wsum[kCheckThreads / kWave];
-    const int b = blockIdx.x;
+    const int b = static_cast<int>(xcd_tile(blockIdx.x, a.nbuckets));
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
-    for (int w = tid; w < kBucketWords; w += kCheckThreads) bits[w] = 0;
+    for (int w = tid; w < (1 << a.bshift) / 32; w += kCheckThreads) bits[w] = 0;
     __syncthreads();
     const int64_t nc = a.nchunks;
     const uint16_t *rs = a.ctab + static_cast<int64_t>(b) * nc;
@@ -532,7 +535,7 @@ __global__ __launch_bounds__(kCheckThreads) void props_check_kernel(PropsArgs a)
                 const uint32_t bit = 1u << (off & 31);
                 const uint32_t old = atomicOr(bits + (off >> 5), bit);
                 if (old & bit) {
-                    note_repeat(a, (static_cast<uint64_t>(b) << kBucketShift) + off, true);
+                    note_repeat(a, (static_cast<uint64_t>(b) << a.bshift) + off, true);
                     dup_seen = true;
                 }
             }
@@ -593,9 +596,9 @@ __global__ __launch_bounds__(kCheckThreads) void props_check_kernel(PropsArgs a)
     if (!(a.mask & IXP_BIJ)) return;
     __syncthreads();
     // least value of Img inside this bucket whose bit is clear
-    const int64_t v0 = a.lo + (static_cast<int64_t>(b) << kBucketShift);
+    const int64_t v0 = a.lo + (static_cast<int64_t>(b) << a.bshift);
     const int64_t lo_b = a.ilo > v0 ? a.ilo - v0 : 0;
-    const int64_t hi_b = a.ihi - v0 < (int64_t{1} << kBucketShift) ? a.ihi - v0 : (int64_t{1} << kBucketShift);
+    const int64_t hi_b = a.ihi - v0 < (int64_t{1} << a.bshift) ? a.ihi - v0 : (int64_t{1} << a.bshift);
     unsigned long long cm = kNone;
     if (lo_b < hi_b) {
         for (int64_t w = (lo_b >> 5) + tid; w <= ((hi_b - 1) >> 5); w += kCheckThreads) {
@@ -1229,13 +1232,25 @@ namespace {
 constexpr int kPass1Grid = 2048;   // fixed, so the workspace size does not depend on the device
 constexpr int kRescanGrid = 512;
 
+// Values per bucket: the narrowest power of two that leaves at most 256 buckets
+// (one workgroup reads a bucket), so that props_check fills the chip whatever the
+// width.  Range + Inj + Bij of a permutation, with buckets of 2^20 values / this
+// rule: 2^17 entries 659 / 39 us, 2^20 762 / 42, 2^24 312 / 83, 2^27 538 / 431.  Up
+// to 512 buckets: 2^27 490, 1024: 617 (the runs get shorter than two lines).
+constexpr int64_t kBuckets = 256;
+int bucket_shift(int64_t w) {
+    int s = 5;   // whole bitmap words
+    while (s < kBucketShift && ceil_div(w, int64_t{1} << s) > kBuckets) ++s;
+    return s;
+}
+
 // Inj/Bij take the chunked path when Rcd spans at most kMaxBuckets buckets
 // and the array is large enough for the extra pass to pay.
 int buckets_for(int64_t n, uint32_t mask, const ixp_prop_args *a) {
     if (!(mask & (IXP_INJ | IXP_BIJ)) || !a) return 0;
     const int64_t w = a->hi - a->lo;
     if (w <= 0 || n < (int64_t{1} << 16) || n >= (int64_t{1} << 43)) return 0;
-    const int64_t b = (w + (int64_t{1} << kBucketShift) - 1) >> kBucketShift;
+    const int64_t b = ceil_div(w, int64_t{1} << bucket_shift(w));
     // one workgroup reads each bucket: with more than 2^22 values per bucket
     // on average the global bitmap is faster
     if (n > (b << 22)) return 0;
@@ -1345,6 +1360,7 @@ extern "C" int ixp_check_props(const void *x, int32_t x_t, int64_t n, uint32_t m
     }
     a.nbuckets = buckets_for(n, mask, pa);
     a.bucketed = a.nbuckets > 0 ? 1 : 0;
+    if (a.bucketed) a.bshift = bucket_shift(pa->hi - pa->lo);
     char *rp = reinterpret_cast<char *>(a.fp_last) + ((mask & IXP_FILTPART) ? kFpBytes : 0);
     a.rep = reinterpret_cast<uint64_t *>(rp);
     a.rep_min = reinterpret_cast<unsigned long long *>(a.rep + kRepCap);
@@ -1382,7 +1398,12 @@ extern "C" int ixp_check_props(const void *x, int32_t x_t, int64_t n, uint32_t m
             else
                 IXP_LAUNCH("props_scan", props_scan_kernel<false>, dim3(static_cast<uint32_t>(b.nchunks)),
                            dim3(kScanThreads), scan_lds, st, b);
-            IXP_LAUNCH("props_check", props_check_kernel, dim3(b.nbuckets), dim3(kCheckThreads), 0, st, b);
+            if (b.bshift < kBucketShift)
+                IXP_LAUNCH("props_check", props_check_kernel<kBucketShift - 1>, dim3(b.nbuckets), dim3(kCheckThreads),
+                           0, st, b);
+            else
+                IXP_LAUNCH("props_check", props_check_kernel<kBucketShift>, dim3(b.nbuckets), dim3(kCheckThreads), 0,
+                           st, b);
         } else if (b.x64) {
             IXP_LAUNCH("props_pass1", (props_pass1_kernel<true, 4>), dim3(grid), dim3(kPropsBlock), 0, st, b);
         } else {

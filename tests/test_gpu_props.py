@@ -301,3 +301,21 @@ def test_bucketed_and_fallback_paths():
     # a bucket boundary: values just around multiples of 2^20
     z = (np.arange(n) // 7) * (1 << 20) + (np.arange(n) % 7) - 3
     both(z, P.INJ | P.RANGE, -3, int(z.max()) + 1)
+
+
+@pytest.mark.parametrize("w", [66_000, 256 << 9, (256 << 9) + 1, (1 << 20) - 1, (1 << 27) + 1, 1 << 28, (1 << 28) + 1])
+def test_bucket_widths(w):
+    """Buckets hold 2^s values, s the least that leaves 256 of them (up to s = 20):
+    both sides of such widths, with repeats, a missing value and entries outside Rcd."""
+    g = np.random.default_rng(w)
+    n = 70_001
+    x = g.integers(0, w, n)
+    both(x, ALL4, 0, w, 0, w)
+    y = np.unique(x)
+    y = np.concatenate([y, np.setdiff1d(g.integers(0, w, 4 * n), y)])[:66_000] if w > n else g.permutation(w)
+    g.shuffle(y)
+    both(y, ALL4, 0, w, 0, w)                 # injective
+    y[7], y[len(y) - 5] = -1, w               # outside Rcd
+    both(y - 3, ALL4, -3, w - 3, -3, w - 3)
+    y[11] = y[60_000]
+    both(y, ALL4, 0, w, 0, w)
