@@ -114,7 +114,7 @@ size_t ixp_partition_workspace(int64_t n);
  * key_t: IXP_I32 or IXP_F32 (see ixp_pred); idx_t: IXP_I32 (needs n < 2^31)
  * or IXP_I64.  out_keys and out_idx may each be NULL (not produced); d_split
  * is required.  n == 0 is valid and writes T = 0.
- * Enqueues 2-3 kernels on `stream`; capturable into a HIP graph. */
+ * Enqueues 1 to 3 kernels on `stream`; capturable into a HIP graph. */
 int ixp_partition(const void *keys, int32_t key_t, int64_t n,
                   const ixp_pred *pred, int32_t mode, void *out_keys,
                   void *out_idx, int32_t idx_t, int64_t *d_split, void *ws,

@@ -23,7 +23,8 @@
 //                and written as the tile's two contiguous runs.
 // Up to 1024 tiles (n <= 2^22) skip the tile scan: one workgroup counts each
 // tile (a wave per 1024 elements), and each scatter workgroup adds up the tile
-// counts before its tile and in total itself.
+// counts before its tile and in total itself.  Up to 32768 elements a partition
+// or filter is one launch, each workgroup counting the whole array (flat_one).
 // Filter (single pass, two kernels):
 //   init      -- clears the tile descriptors, ticket and error word;
 //   scan      -- tiles taken in ticket order; each publishes its count, finds
@@ -371,9 +372,120 @@ __global__ __launch_bounds__((FlatCfg<MODE, VEC>::kBlock)) void flat_scan_kernel
     }
 }
 
+// The smallest calls, in one launch: a workgroup of 1024 threads per 4096
+// elements, which beside ranking its own tile counts the whole array (16 elements
+// per thread and step, from the L2 once another workgroup has read them), so that
+// it needs nothing from a launch before it, no look-back and no cleared workspace.
+// A step of 16384 elements costs 2.2 us, a second launch about the same and some
+// host time.  Back to back, two launches / one: partition of 100 int32 keys 6.4 /
+// 3.3 us, 4099: 7.3 / 4.9, 16384: 7.3 / 5.2, 30000: 7.5 / 6.6, 65536: 7.5 / 8.8; filter
+// 8.1 / 3.2, 8.3 / 4.6, 8.0 / 5.0, 8.7 / 6.3, 8.5 / 8.6.  Hence two steps at most.
+constexpr int kOneThreads = 1024;
+constexpr int kOneTile = kOneThreads * 4;
+constexpr int64_t kOneMax = 32768;
+
+template <int VEC, class Pred, int MODE, class Idx>
+__global__ __launch_bounds__(kOneThreads) void flat_one_kernel(FlatArgs a, Pred pred) {
+    constexpr int kRows = 4 / VEC;
+    using T = Tile<kOneThreads, kRows, VEC>;
+    using All = Tile<kOneThreads, 16 / VEC, VEC>;
+    static_assert(T::kSize == kOneTile && kOneTile % All::kPerWave == 0, "a wave counts on one side of a tile");
+    __shared__ uint32_t stage[kOneTile];
+    __shared__ uint32_t wtot[T::kWaves];
+    __shared__ uint32_t wbefore[T::kWaves], wall[T::kWaves];
+    const int tid = threadIdx.x;
+    const int wave = wave_id();
+    const int lane = tid & (kWave - 1);
+    const int64_t lo = static_cast<int64_t>(blockIdx.x) * kOneTile;
+    const int64_t hi = lo + kOneTile < a.n ? lo + kOneTile : a.n;
+    T tile;
+    if (T::wave_live(lo, lo, hi, wave)) {
+        tile.load(a.keys, a.n, lo, lo, hi, pred, a.need_keys != 0, wave, lane);
+    } else {
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+#pragma unroll
+            for (int q = 0; q < VEC; ++q) tile.key[r][q] = 0;
+    }
+    tile.wave_ranks();
+    if (a.n > kOneTile) {
+        uint32_t before = 0, all = 0;   // trues this wave counts before the tile, in the whole array
+        for (int64_t jlo = 0; jlo < a.n; jlo += All::kSize) {
+            const int64_t jhi = jlo + All::kSize < a.n ? jlo + All::kSize : a.n;
+            if (!All::wave_live(jlo, jlo, jhi, wave)) continue;
+            All part;
+            part.load(a.keys, a.n, jlo, jlo, jhi, pred, !Pred::kUsesFlags, wave, lane);
+            const uint32_t c = part.wave_count();
+            all += c;
+            before += jlo + wave * All::kPerWave < lo ? c : 0u;
+        }
+        if (lane == 0) {
+            wbefore[wave] = before;
+            wall[wave] = all;
+        }
+    }
+    // (its barrier also publishes the counts)
+    const uint32_t tcount = tile.block_ranks(wtot, wave, lane);
+    uint32_t excl = 0, total = tcount;
+    if (a.n > kOneTile) {
+        total = 0;
+#pragma unroll
+        for (int w = 0; w < T::kWaves; ++w) {
+            excl += wbefore[w];
+            total += wall[w];
+        }
+    }
+    if (lo == 0 && tid == 0) {
+        *a.split = total;
+        *a.err = 0;
+    }
+    const uint32_t false_base = total + (static_cast<uint32_t>(lo) - excl);
+    Idx *out_idx = static_cast<Idx *>(a.out_idx);
+    const int32_t l0 = wave * T::kPerWave + lane * VEC;
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        const int64_t p0 = T::pos(lo, wave, r, lane, 0);
+        Idx v[VEC];
+        uint32_t vm = 0;
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) {
+            const uint32_t rt = tile.rank[r][q];
+            const uint32_t rf = static_cast<uint32_t>(l0 + r * (kWave * VEC) + q) - rt;
+            const bool f = tile.flag(r, q);
+            const bool ok = tile.valid(r, q);
+            vm |= static_cast<uint32_t>(ok) << q;
+            if (MODE == IXP_MODE_PARTITION) v[q] = static_cast<Idx>(f ? excl + rt : false_base + rf);
+            else v[q] = f ? static_cast<Idx>(excl + rt) : static_cast<Idx>(-1);
+            if (a.out_keys && ok && (MODE == IXP_MODE_PARTITION || f)) stage[f ? rt : tcount + rf] = tile.key[r][q];
+        }
+        if (out_idx && vm) store_idx_group<VEC, Idx>(out_idx, p0, v, vm);
+    }
+    if (a.out_keys) {
+        __syncthreads();
+        write_run<kOneThreads>(stage, 0, tcount, excl, a.out_keys, a.n, tid);
+        if (MODE == IXP_MODE_PARTITION)
+            write_run<kOneThreads>(stage, tcount, static_cast<uint32_t>(hi - lo) - tcount, false_base, a.out_keys, a.n,
+                                   tid);
+    }
+}
+
+template <int VEC, class Pred, int MODE>
+int launch_one(const FlatArgs &a, const Pred &pred, int idx_t, hipStream_t st) {
+    const dim3 grid(static_cast<uint32_t>(ceil_div(a.n, kOneTile)));
+    const char *name = MODE == IXP_MODE_PARTITION ? "flat_one_partition" : "flat_one_filter";
+    if (idx_t == IXP_I32)
+        IXP_LAUNCH(name, (flat_one_kernel<VEC, Pred, MODE, int32_t>), grid, dim3(kOneThreads), 0, st, a, pred);
+    else
+        IXP_LAUNCH(name, (flat_one_kernel<VEC, Pred, MODE, int64_t>), grid, dim3(kOneThreads), 0, st, a, pred);
+    return launch_status();
+}
+
 template <int VEC, class Pred>
 int launch_flat(FlatArgs a, const Pred &pred, int mode, int idx_t, hipStream_t st) {
     const int64_t n = a.n;
+    if (n > 0 && n <= kOneMax)
+        return mode == IXP_MODE_PARTITION ? launch_one<VEC, Pred, IXP_MODE_PARTITION>(a, pred, idx_t, st)
+                                          : launch_one<VEC, Pred, IXP_MODE_FILTER>(a, pred, idx_t, st);
     if (mode == IXP_MODE_PARTITION) {
         using Cfg = FlatCfg<IXP_MODE_PARTITION, VEC>;
         a.num_tiles = ceil_div(n, Cfg::kTile);

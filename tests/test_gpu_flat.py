@@ -243,3 +243,35 @@ def test_modulus_predicate_over_divisors(d):
     _, oi, ss, _ = P.segmented_partition(torch.from_numpy(x).to(DEV), torch.from_numpy(shape).to(DEV), P.Pred.mod_rows(d))
     _, idx, seg, _ = O.partition2L_rows(x, shape, O.ROW_MOD, d, np.zeros(len(shape), np.float32), 0)
     assert np.array_equal(oi.cpu().numpy(), idx) and np.array_equal(ss.cpu().numpy(), seg)
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 1023, 1025, 4095, 4096, 4097, 16383, 16384, 16385, 20_481, 32_767, 32_768, 32_769])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_one_launch_sizes(n, mode):
+    """Up to 32768 elements one launch does it all: workgroups of 4096 elements
+    that count the array in steps of 16384; aligned arrays, views one element
+    off, flags and every subset of the outputs."""
+    g = np.random.default_rng(n)
+    keys = W.int_keys(n, 95) - (1 << 30)
+    f32 = W.f32_uniform(n, 96)
+    run_both(keys, "mod", mode, d=3, r=2)
+    run_both(f32, "lt", mode, torch.int32, s=0.3)
+    for s in (0.0, 2.0):   # no trues, all trues
+        run_both(f32, "lt", mode, s=s)
+    fl = (g.random(n) < 0.5).astype(np.uint8) * 7
+    run_both(f32, "flags", mode, flags=fl)
+    run_both(keys, "mod", mode, keys_t=torch.from_numpy(np.concatenate([[0], keys]).astype(np.int32)).to(DEV)[1:], d=2, r=0)
+    ft = torch.from_numpy(np.concatenate([[0], fl]).astype(np.uint8)).to(DEV)[1:]
+    kt = torch.from_numpy(keys).to(DEV)
+    ys, idx, t = O.partition2(keys, O.Pred.from_flags(fl), mode)
+    nout = n if mode == 0 else t
+    for want_keys, want_idx in ((True, True), (True, False), (False, True), (False, False)):
+        ok, oi, sp = P.partition(kt, P.Pred.from_flags(ft), mode=mode, want_keys=want_keys, want_idx=want_idx)
+        assert int(sp.item()) == t
+        assert not want_idx or np.array_equal(oi.cpu().numpy(), idx)
+        assert not want_keys or np.array_equal(ok.cpu().numpy()[:nout], ys[:nout])
+    # nothing past the kept part of a filter's output is written
+    out = torch.full((n,), -77, dtype=torch.int32, device=DEV)
+    P.partition(kt, P.Pred.mod_eq(2, 0), mode=mode, out_keys=out)
+    if mode == 1:
+        assert bool((out[int((keys % 2 == 0).sum()):] == -77).all())
