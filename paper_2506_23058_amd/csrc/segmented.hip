@@ -41,6 +41,8 @@
 //                item is read once: its T_k comes from the item itself.  A
 //                row of 2..kSibMax items is read once too (partition, row
 //                sync WAIT): its items publish their counts to one another.
+#include <type_traits>
+
 #include "device.hpp"
 #include "host.hpp"
 
@@ -145,7 +147,7 @@ __device__ __forceinline__ bool row_synced(const SegArgs &a, int64_t nit) {
     return a.mode == IXP_MODE_PARTITION && a.row_sync != IXP_ROW_SYNC_COUNT && nit > 1 && nit <= kSibMax;
 }
 __device__ __forceinline__ bool row_counted(const SegArgs &a, int64_t nit) {
-    return a.mode != IXP_MODE_PARTITION || (nit > 1 && !row_synced(a, nit));
+    return a.mode != IXP_MODE_PARTITION || nit > (a.row_sync == IXP_ROW_SYNC_COUNT ? 1 : kSibMax);
 }
 
 // Rows are cut into items of `tile` elements from the 16-byte group holding
@@ -425,9 +427,10 @@ __global__ __launch_bounds__(kShapeThreads) void seg_shape_kernel(SegArgs a) {
     const int64_t r0 = static_cast<int64_t>(blockIdx.x) * 256;
     const int64_t rend = a.m - r0 < 256 ? a.m : r0 + 256;   // rows [0, rend) are scanned
     const int nr = static_cast<int>(rend - r0);
-    const bool last = rend == a.m;
+    const int part = blockIdx.y;   // of the workgroups that share these rows' records
+    const bool last = rend == a.m && part == 0;
     if (tid == 0) bad = 0;
-    {   // clear the item scan's ticket and look-back descriptors
+    if (part == 0) {   // clear the item scan's ticket and look-back descriptors
         const int64_t g = static_cast<int64_t>(blockIdx.x) * kShapeThreads + tid;
         const int64_t nd = (a.max_items + kScanChunk - 1) / kScanChunk;
         for (int64_t j = g; j < nd; j += static_cast<int64_t>(gridDim.x) * kShapeThreads) a.scan_desc[j] = 0;
@@ -460,42 +463,48 @@ __global__ __launch_bounds__(kShapeThreads) void seg_shape_kernel(SegArgs a) {
     for (int64_t k = k0; k < k1; ++k) sum_s += sz[k];
     int64_t tot_s;
     const int64_t off0 = block_exclusive_scan<16>(sum_s, lds_a, &tot_s);
-    // the last non-empty size before this thread's rows in their block of rows
-    int64_t prev0 = 0;
-    if (a.short_max) {
-        const int64_t block0 = k0 & ~((int64_t{1} << kFusedPackShift) - 1);
-        for (int64_t k = k0 - 1; k >= block0 && k < rend && prev0 == 0; --k) prev0 = sz[k];
-    }
-    auto at_block = [](int64_t k) { return (k & ((int64_t{1} << kFusedPackShift) - 1)) == 0; };
-    int64_t sum_it = 0, counted = 0;
-    {
-        int64_t o = off0, prev = prev0;
+    // calls row(k, o, items) for this thread's rows; the packed form keeps the
+    // last non-empty size before a row in its block of rows
+    const bool pack = a.short_max > 0;
+    auto rows = [&](auto packed, auto &&row) {
+        constexpr bool kPack = decltype(packed)::value;
+        constexpr int64_t kBlock = int64_t{1} << kFusedPackShift;
+        int64_t o = off0, prev = 0;
+        if (kPack)
+            for (int64_t k = k0 - 1; k >= (k0 & ~(kBlock - 1)) && k < rend && prev == 0; --k) prev = sz[k];
         for (int64_t k = k0; k < k1; ++k) {
-            if (at_block(k)) prev = 0;
             const int64_t sk = sz[k];
-            const int64_t nit = row_items(a, o, sk, prev);
-            sum_it += nit;
-            if (row_counted(a, nit)) counted += nit;
-            if (sk > 0) prev = sk;
+            if (kPack) {
+                if ((k & (kBlock - 1)) == 0) prev = 0;
+                row(k, o, row_items(a, o, sk, prev));
+                if (sk > 0) prev = sk;
+            } else {
+                row(k, o, sk > 0 ? ((o & 3) + sk + a.tile - 1) >> a.tile_shift : int64_t{0});
+            }
             o += sk;
         }
-    }
+    };
+    int64_t sum_it = 0, counted = 0;
+    auto add = [&](int64_t, int64_t, int64_t nit) {
+        sum_it += nit;
+        counted += row_counted(a, nit) ? nit : 0;
+    };
+    if (pack) rows(std::true_type{}, add);
+    else rows(std::false_type{}, add);
     int64_t tot_it;
     const int64_t it0 = block_exclusive_scan<16>(sum_it, lds_b, &tot_it);
     if (k1 > r0) {   // (the other threads' rows are other workgroups')
-        int64_t o = off0, it = it0, prev = prev0;
-        for (int64_t k = k0; k < k1; ++k) {
-            if (at_block(k)) prev = 0;
+        int64_t it = it0;
+        auto put = [&](int64_t k, int64_t o, int64_t nit) {
             if (k >= r0) {
                 s_off[k - r0] = o;
                 s_it[k - r0] = it;
-                a.offsets[k] = o;
+                if (part == 0) a.offsets[k] = o;
             }
-            const int64_t sk = sz[k];
-            it += row_items(a, o, sk, prev);
-            if (sk > 0) prev = sk;
-            o += sk;
-        }
+            it += nit;
+        };
+        if (pack) rows(std::true_type{}, put);
+        else rows(std::false_type{}, put);
     }
     if (tid == 0) {
         s_off[nr] = tot_s;
@@ -515,7 +524,8 @@ __global__ __launch_bounds__(kShapeThreads) void seg_shape_kernel(SegArgs a) {
     __syncthreads();
     // this workgroup's item records (a bad shape may ask for more than fit:
     // those are not written, and the last workgroup reports the error)
-    for (int64_t idx = s_it[0] + tid; idx < s_it[nr] && idx < a.max_items; idx += kShapeThreads)
+    for (int64_t idx = s_it[0] + part * kShapeThreads + tid; idx < s_it[nr] && idx < a.max_items;
+         idx += gridDim.y * kShapeThreads)
         write_item(a, idx, s_off, s_it, r0, nr, nr);
 }
 
@@ -1300,8 +1310,13 @@ __global__ __launch_bounds__(256) void seg_fill_kernel(SegArgs a, Out *out, cons
 // kShapeFusedRows rows, else three.
 int launch_shape(const SegArgs &a, hipStream_t st) {
     if (a.m <= kShapeFusedRows) {
-        const uint32_t rblocks = static_cast<uint32_t>(ceil_div(a.m > 0 ? a.m : 1, 256));
-        IXP_LAUNCH("seg_shape", seg_shape_kernel, dim3(rblocks), dim3(kShapeThreads), 0, st, a);
+        // few rows of many items: several workgroups share a group of 256 rows
+        // (each rescans the shape), as far as they fit the chip at once
+        const int64_t groups = ceil_div(a.m > 0 ? a.m : 1, 256);
+        const int64_t want = a.n / (a.tile * groups * kShapeThreads) + 1, fit = device_cus() / groups;
+        const int64_t parts = want < fit ? want : (fit > 0 ? fit : 1);
+        IXP_LAUNCH("seg_shape", seg_shape_kernel, dim3(static_cast<uint32_t>(groups), static_cast<uint32_t>(parts)),
+                   dim3(kShapeThreads), 0, st, a);
         return launch_status();
     }
     const dim3 chunks(static_cast<uint32_t>(a.nchunks));
