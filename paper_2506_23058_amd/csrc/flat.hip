@@ -68,11 +68,11 @@ constexpr size_t kWsHeader = 256;   // ticket (u32), error word (i32), padding
 #define IXP_COUNT_ROWS 16
 #endif
 
-template <int MODE, int VEC>
+template <int MODE, int VEC, int PATH = 0>
 struct FlatCfg {
     static constexpr int kBlock = MODE == IXP_MODE_PARTITION ? IXP_FLAT_PART_BLOCK : IXP_FLAT_FILT_BLOCK;
-    static constexpr int kRows = VEC == 4 ? (MODE == IXP_MODE_PARTITION ? IXP_FLAT_PART_ROWS : 4)
-                                          : 16 * (MODE == IXP_MODE_PARTITION ? IXP_FLAT_PART_ROWS : 4) / 4;
+    static constexpr int kRows4 = MODE == IXP_MODE_PARTITION ? IXP_FLAT_PART_ROWS : PATH == 2 ? 8 : 4;
+    static constexpr int kRows = VEC == 4 ? kRows4 : 4 * kRows4;
     using T = Tile<kBlock, kRows, VEC>;
     static constexpr int kTile = T::kSize;
 };
@@ -98,6 +98,14 @@ struct FlatArgs {
 // tile 0 writes T.
 constexpr int64_t kSmallTiles = 1024;
 constexpr int64_t kSmallChunk = 1024;
+
+// A filter with 32-bit indices takes tiles of 32768 elements from this many
+// elements on: half the tickets and look-backs, which cost 6 ns a tile, for one
+// workgroup per CU instead of two.  16384- / 32768-element tiles, f32 keys, s = 0.5:
+// 2 10^7 51.0 / 51.8 us, 3.3 10^7 80.2 / 74.3, 10^8 229 / 217, 2^28 599 / 545 (s = 0.01
+// 529 / 480, s = 0.99 668 / 637).  With 64-bit indices the registers spill: 10^8
+// 331 / 372.  (Smaller tiles: 10^8 with 8192 elements 312 us, 4096 402.)
+constexpr int64_t kBigFilter = int64_t{1} << 25;
 
 // Counting waves per partition call (fixed, so the workspace size does not
 // depend on the device).
@@ -226,24 +234,25 @@ __global__ __launch_bounds__(1024) void flat_tile_scan_kernel(int64_t *wsum, int
     }
 }
 
-// Partition paths (PATH):
-//   0  the tile prefix and T come from the counting kernel and the tile scan;
+// Paths (PATH):
+//   0  (partition) the tile prefix and T come from the counting kernel and the tile scan;
+//   2  (filter) tiles of twice the size, from kBigFilter elements on;
 //   1  at most kSmallTiles tiles, counted by flat_count_small (one
 //      workgroup per tile, one wave per 1024 elements): every workgroup adds
 //      up the tile counts before its own and in total itself, and tile 0
 //      writes T.
 template <int VEC, class Pred, int MODE, class Idx, int PATH = 0>
-__global__ __launch_bounds__((FlatCfg<MODE, VEC>::kBlock)) void flat_scan_kernel(FlatArgs a, Pred pred) {
-    using Cfg = FlatCfg<MODE, VEC>;
+__global__ __launch_bounds__((FlatCfg<MODE, VEC, PATH>::kBlock)) void flat_scan_kernel(FlatArgs a, Pred pred) {
+    using Cfg = FlatCfg<MODE, VEC, PATH>;
     using T = typename Cfg::T;
     constexpr int kTile = T::kSize;
     constexpr int kRows = Cfg::kRows;
     constexpr int kBlock = Cfg::kBlock;
-    static_assert(PATH == 0 || MODE == IXP_MODE_PARTITION, "small paths are partitions");
+    static_assert(PATH == 0 || (PATH == 1) == (MODE == IXP_MODE_PARTITION), "path 1 partitions, path 2 filters");
     __shared__ uint32_t stage[kTile];
     __shared__ uint32_t wtot[T::kWaves];
     __shared__ int64_t sh[2];
-    __shared__ int64_t sh_small[PATH > 0 ? T::kWaves : 1][2];
+    __shared__ int64_t sh_small[PATH == 1 ? T::kWaves : 1][2];
 
     const int tid = threadIdx.x;
     const int wave = wave_id();
@@ -251,7 +260,7 @@ __global__ __launch_bounds__((FlatCfg<MODE, VEC>::kBlock)) void flat_scan_kernel
     int64_t t;
     if (MODE == IXP_MODE_PARTITION) {
 #if IXP_XCD_MAP
-        t = PATH > 0 ? blockIdx.x : xcd_tile(blockIdx.x, a.num_tiles);
+        t = PATH == 1 ? blockIdx.x : xcd_tile(blockIdx.x, a.num_tiles);
 #else
         t = blockIdx.x;
 #endif
@@ -271,9 +280,9 @@ __global__ __launch_bounds__((FlatCfg<MODE, VEC>::kBlock)) void flat_scan_kernel
 
     // small path: wsum[j] is tile j's count; each thread's share of the
     // counts is loaded before the tile, so the two loads overlap
-    constexpr int kPer = PATH > 0 ? (kSmallTiles + kBlock - 1) / kBlock : 1;
+    constexpr int kPer = PATH == 1 ? (kSmallTiles + kBlock - 1) / kBlock : 1;
     int64_t cnt[kPer];
-    if constexpr (PATH > 0) {
+    if constexpr (PATH == 1) {
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
             const int64_t j = static_cast<int64_t>(tid) * kPer + k;
@@ -284,7 +293,7 @@ __global__ __launch_bounds__((FlatCfg<MODE, VEC>::kBlock)) void flat_scan_kernel
     T tile;
     tile.load(a.keys, a.n, lo, lo, hi, pred, a.need_keys != 0, wave, lane);
     tile.wave_ranks();
-    if constexpr (PATH > 0) {
+    if constexpr (PATH == 1) {
         int64_t before = 0, all = 0;
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
@@ -302,7 +311,7 @@ __global__ __launch_bounds__((FlatCfg<MODE, VEC>::kBlock)) void flat_scan_kernel
     // (its barrier also publishes sh_small)
     const uint32_t tcount = tile.block_ranks(wtot, wave, lane);
 
-    if constexpr (PATH > 0) {
+    if constexpr (PATH == 1) {
         for (int w = 0; w < T::kWaves; ++w) {
             excl += sh_small[w][0];
             total += sh_small[w][1];
@@ -524,8 +533,9 @@ int launch_flat(FlatArgs a, const Pred &pred, int mode, int idx_t, hipStream_t s
                        dim3(static_cast<uint32_t>(nt)), dim3(Cfg::kBlock), cap, st, a, pred);
         }
     } else {
+        const bool big = n >= kBigFilter && idx_t == IXP_I32;
         using Cfg = FlatCfg<IXP_MODE_FILTER, VEC>;
-        a.num_tiles = ceil_div(n, Cfg::kTile);
+        a.num_tiles = ceil_div(n, big ? FlatCfg<IXP_MODE_FILTER, VEC, 2>::kTile : Cfg::kTile);
         const int64_t nt = a.num_tiles;
         const int64_t iblocks = nt > 0 ? (ceil_div(nt, 256) < 1024 ? ceil_div(nt, 256) : 1024) : 1;
         IXP_LAUNCH("flat_init", flat_init_kernel, dim3(static_cast<uint32_t>(iblocks)), dim3(256), 0, st,
@@ -536,12 +546,16 @@ int launch_flat(FlatArgs a, const Pred &pred, int mode, int idx_t, hipStream_t s
                        int64_t{0}, a.split, a.err);
             return launch_status();
         }
-        if (idx_t == IXP_I32)
-            IXP_LAUNCH("flat_scan_filter", (flat_scan_kernel<VEC, Pred, IXP_MODE_FILTER, int32_t>),
-                       dim3(static_cast<uint32_t>(nt)), dim3(Cfg::kBlock), 0, st, a, pred);
+        const dim3 grid(static_cast<uint32_t>(nt)), block(Cfg::kBlock);
+        if (big)
+            IXP_LAUNCH("flat_scan_filter", (flat_scan_kernel<VEC, Pred, IXP_MODE_FILTER, int32_t, 2>), grid, block, 0,
+                       st, a, pred);
+        else if (idx_t == IXP_I32)
+            IXP_LAUNCH("flat_scan_filter", (flat_scan_kernel<VEC, Pred, IXP_MODE_FILTER, int32_t>), grid, block, 0, st,
+                       a, pred);
         else
-            IXP_LAUNCH("flat_scan_filter", (flat_scan_kernel<VEC, Pred, IXP_MODE_FILTER, int64_t>),
-                       dim3(static_cast<uint32_t>(nt)), dim3(Cfg::kBlock), 0, st, a, pred);
+            IXP_LAUNCH("flat_scan_filter", (flat_scan_kernel<VEC, Pred, IXP_MODE_FILTER, int64_t>), grid, block, 0, st,
+                       a, pred);
     }
     return launch_status();
 }

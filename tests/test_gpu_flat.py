@@ -275,3 +275,13 @@ def test_one_launch_sizes(n, mode):
     P.partition(kt, P.Pred.mod_eq(2, 0), mode=mode, out_keys=out)
     if mode == 1:
         assert bool((out[int((keys % 2 == 0).sum()):] == -77).all())
+
+
+@pytest.mark.parametrize("n", [(1 << 25) - 1, 1 << 25, (1 << 25) + 32_767])
+def test_filter_tile_sizes(n):
+    """Filters with 32-bit indices take 32768-element tiles from 2^25 elements on."""
+    f32 = W.f32_uniform(n + 1, 97)
+    for s in (0.0, 0.4, 2.0):
+        run_both(f32[:n], "lt", 1, torch.int32, s=s)
+    run_both(f32[:n], "lt", 1, torch.int64, s=0.4)
+    run_both(f32[1:], "lt", 1, torch.int32, keys_t=torch.from_numpy(f32).to(DEV)[1:], s=0.4)   # element loads
