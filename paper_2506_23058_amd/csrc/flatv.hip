@@ -39,6 +39,9 @@ struct ClassMod {
         const uint32_t m = u - 3u * (__umulhi(u, 0xAAAAAAABu) >> 1);
         return m == 2 ? 0u : m + 1;
     }
+    // class <= K, for the counts
+    template <int K>
+    __device__ __forceinline__ bool upto(uint32_t bits, uint8_t b) const { return (*this)(bits, b) <= K; }
 };
 
 // f32 thresholds s0 <= s1 <= s2: class h for s_{h-1} <= x < s_h, the last
@@ -54,6 +57,10 @@ struct ClassThresh {
         if (V > 3 && x < s2) return 2;
         return V - 1;
     }
+    template <int K>   // (the thresholds do not decrease)
+    __device__ __forceinline__ bool upto(uint32_t bits, uint8_t) const {
+        return __uint_as_float(bits) < (K == 0 ? s0 : K == 1 ? s1 : s2);
+    }
 };
 
 // A caller byte per element; values past the last class count as the last.
@@ -64,6 +71,8 @@ struct ClassBytes {
     __device__ __forceinline__ uint32_t operator()(uint32_t, uint8_t b) const {
         return b < V - 1 ? b : V - 1;
     }
+    template <int K>
+    __device__ __forceinline__ bool upto(uint32_t, uint8_t b) const { return b <= K; }
 };
 
 // a[c] for a class c < V, as a[0] plus the steps a[k] - a[k-1] of every
@@ -173,25 +182,10 @@ struct TileV {
         }
     }
 
-    // One-hot counters packed 16 bits per class in a 64-bit word (a class
-    // holds at most 4096 elements of a tile, so no field overflows).
-    __device__ __forceinline__ uint64_t onehot(int r, int q) const {
-        return valid(r, q) ? (1ull << (16 * cls(r, q))) : 0ull;
-    }
+    // Counts of the classes, packed 16 bits each in a 64-bit word (a class holds
+    // at most 4096 elements of a tile, so no field overflows).
     __device__ static __forceinline__ uint32_t field(uint64_t x, uint32_t c) {
         return static_cast<uint32_t>(x >> (16 * c)) & 0xFFFFu;
-    }
-
-    // Per-class counts of this wave's valid elements (uniform), packed.
-    __device__ __forceinline__ uint64_t wave_counts() const {
-        uint64_t x = 0;
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) x += onehot(r, q);
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, kWave);
-        return x;
     }
 
     // Ranks inside this wave's run.  Per row, the counts of every class but
@@ -276,11 +270,57 @@ struct VArgs {
     int32_t need_keys;
 };
 
+// Adds to cum[k] the elements of class <= k of one ballot's worth of elements.
+template <int V, class Cls>
+__device__ __forceinline__ void count_upto(const Cls &cl, uint32_t key, uint8_t byte, bool ok, uint32_t (&cum)[V - 1]) {
+    cum[0] += static_cast<uint32_t>(__builtin_popcountll(ballot(ok && cl.template upto<0>(key, byte))));
+    if constexpr (V > 2)
+        cum[1] += static_cast<uint32_t>(__builtin_popcountll(ballot(ok && cl.template upto<1>(key, byte))));
+    if constexpr (V > 3)
+        cum[2] += static_cast<uint32_t>(__builtin_popcountll(ballot(ok && cl.template upto<2>(key, byte))));
+}
+
+// cum[k] = elements of class <= k among [lo, lo + kRows 64 x 4) before n, by one
+// wave; all its loads in flight at once where the stretch is whole.
+template <int V, int kRows, class Cls>
+__device__ __forceinline__ void wave_upto(const VArgs &a, const Cls &cl, int64_t lo, int lane, uint32_t (&cum)[V - 1]) {
+#pragma unroll
+    for (int k = 0; k < V - 1; ++k) cum[k] = 0;
+    if (lo + kRows * kWave * 4 <= a.n) {
+        uint32_t key[kRows][4];
+        uint8_t byte[kRows][4];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            const int64_t p = lo + r * (kWave * 4) + lane * 4;
+            if constexpr (Cls::kUsesBytes) load_flags<4>(cl.cls + p, byte[r]);
+            else load_group<4>(a.keys + p, key[r]);
+        }
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                count_upto<V>(cl, Cls::kUsesBytes ? 0u : key[r][q], Cls::kUsesBytes ? byte[r][q] : uint8_t{0}, true, cum);
+    } else {
+        const int64_t hi = lo + kRows * kWave * 4 < a.n ? lo + kRows * kWave * 4 : a.n;
+        for (int64_t p = lo + lane; p - lane < hi; p += kWave) {
+            const bool ok = p < hi;
+            uint32_t key = 0;
+            uint8_t byte = 0;
+            if constexpr (Cls::kUsesBytes) byte = ok ? cl.cls[p] : 0;
+            else key = ok ? a.keys[p] : 0u;
+            count_upto<V>(cl, key, byte, ok, cum);
+        }
+    }
+}
+
+// One wave per contiguous run of tiles, a whole tile per batch of loads.  The
+// classes are counted cumulatively (class <= k), one comparison and one scalar
+// popcount per element row and class: packed one-hot counters took a dozen
+// vector instructions an element and held the registers of half the batch
+// (5 10^7 keys in 3 classes 42 -> 35 us, 2 10^8 by modulus 182 -> 132).
 template <int V, class Cls>
 __global__ __launch_bounds__(256) void flatv_count_kernel(VArgs a, Cls cl) {
     constexpr int kTile = kVBlockThreads * kVRows * 4;
-    using WT = TileV<kWave, 8, V>;   // one wave, 2048 elements: 8 vector loads in flight per lane
-    constexpr int kChunks = kTile / WT::kSize;
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t w = static_cast<int64_t>(blockIdx.x) * (256 / kWave) + wave_id();
     const int64_t t0 = w * a.tiles_per_wave;
@@ -289,14 +329,8 @@ __global__ __launch_bounds__(256) void flatv_count_kernel(VArgs a, Cls cl) {
 #pragma unroll
     for (int k = 0; k < V - 1; ++k) run[k] = 0;
     for (int64_t t = t0; t < t1; ++t) {
-        const int64_t lo = t * kTile;
-        const int64_t hi = lo + kTile < a.n ? lo + kTile : a.n;
-        uint64_t cnt = 0;   // packed per-class counts of the tile
-        for (int c = 0; c < kChunks; ++c) {
-            WT chunk;
-            chunk.load(a.keys, a.n, lo + c * WT::kSize, lo, hi, cl, !Cls::kUsesBytes, 0, lane);
-            cnt += chunk.wave_counts();
-        }
+        uint32_t cum[V - 1];
+        wave_upto<V, kTile / (kWave * 4)>(a, cl, t * kTile, lane, cum);
         if (lane < V - 1) {
             uint64_t mine = run[0];
 #pragma unroll
@@ -304,7 +338,7 @@ __global__ __launch_bounds__(256) void flatv_count_kernel(VArgs a, Cls cl) {
             a.desc[t * 4 + lane] = mine;
         }
 #pragma unroll
-        for (int k = 0; k < V - 1; ++k) run[k] += WT::field(cnt, k);
+        for (int k = 0; k < V - 1; ++k) run[k] += cum[k] - (k > 0 ? cum[k - 1] : 0u);
     }
     if (lane < V - 1 && w < kVCountWaves) {
         uint64_t mine = run[0];
@@ -314,50 +348,85 @@ __global__ __launch_bounds__(256) void flatv_count_kernel(VArgs a, Cls cl) {
     }
 }
 
+// The same where a run is one tile: a workgroup per tile, a wave per quarter
+// (one wave a tile leaves most of the chip idle).
+template <int V, class Cls>
+__global__ __launch_bounds__(256) void flatv_count_small_kernel(VArgs a, Cls cl) {
+    constexpr int kQuarter = kVBlockThreads * kVRows;
+    __shared__ uint32_t sh[4][V - 1];
+    const int lane = threadIdx.x & (kWave - 1), wave = wave_id();
+    const int64_t t = blockIdx.x;
+    uint32_t cum[V - 1];
+    wave_upto<V, kQuarter / (kWave * 4)>(a, cl, (4 * t + wave) * kQuarter, lane, cum);
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < V - 1; ++k) sh[wave][k] = cum[k] - (k > 0 ? cum[k - 1] : 0u);
+    }
+    __syncthreads();
+    if (threadIdx.x < V - 1) {
+        const int k = threadIdx.x;
+        a.desc[t * 4 + k] = 0;
+        a.wsum[k * kVCountWaves + t] = static_cast<int64_t>(sh[0][k]) + sh[1][k] + sh[2][k] + sh[3][k];
+    }
+}
+
 // One workgroup: for every class but the last, the run totals become
-// exclusive prefixes (8 entries per thread, wave shuffles, LDS across waves);
+// exclusive prefixes (8 entries per thread, wave shuffles, LDS across waves;
+// the classes side by side, so that their loads and barriers are shared);
 // the class sizes go to counts[0..v).
 template <int V>
 __global__ __launch_bounds__(1024) void flatv_scan_kernel(int64_t *wsum, int64_t nw, int64_t n, int64_t *counts) {
     constexpr int kPer = 8;
     static_assert(kPer * 1024 >= kVCountWaves, "scan capacity");
-    __shared__ int64_t wtot[16];
+    __shared__ int64_t wtot[V - 1][16];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = wave_id();
-    int64_t rest = n;
+    int64_t v[V - 1][kPer], run[V - 1], inc[V - 1];
+#pragma unroll
     for (int k = 0; k < V - 1; ++k) {
-        int64_t *ws = wsum + k * kVCountWaves;
-        int64_t v[kPer];
-        int64_t run = 0;
+        run[k] = 0;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             const int64_t i = static_cast<int64_t>(tid) * kPer + j;
-            v[j] = i < nw ? ws[i] : 0;
-            run += v[j];
+            v[k][j] = i < nw ? wsum[k * kVCountWaves + i] : 0;
         }
-        int64_t inc = run;
+    }
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int64_t o = __shfl_up(inc, off, 64);
-            if (lane >= off) inc += o;
+    for (int k = 0; k < V - 1; ++k) {
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) run[k] += v[k][j];
+        inc[k] = run[k];
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+#pragma unroll
+        for (int k = 0; k < V - 1; ++k) {
+            const int64_t o = __shfl_up(inc[k], off, 64);
+            if (lane >= off) inc[k] += o;
         }
-        if (lane == 63) wtot[wave] = inc;
-        __syncthreads();
+    }
+    if (lane == 63) {
+#pragma unroll
+        for (int k = 0; k < V - 1; ++k) wtot[k][wave] = inc[k];
+    }
+    __syncthreads();
+    int64_t rest = n;
+#pragma unroll
+    for (int k = 0; k < V - 1; ++k) {
         int64_t before = 0, total = 0;
 #pragma unroll
         for (int w = 0; w < 16; ++w) {
-            const int64_t x = wtot[w];
+            const int64_t x = wtot[k][w];
             before += w < wave ? x : 0;
             total += x;
         }
-        __syncthreads();   // wtot is reused by the next class
-        int64_t acc = before + inc - run;
+        int64_t acc = before + inc[k] - run[k];
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             const int64_t i = static_cast<int64_t>(tid) * kPer + j;
-            if (i < nw) ws[i] = acc;
-            acc += v[j];
+            if (i < nw) wsum[k * kVCountWaves + i] = acc;
+            acc += v[k][j];
         }
         if (tid == 0) counts[k] = total;
         rest -= total;
@@ -440,8 +509,12 @@ int launch_v(VArgs a, const Cls &cl, int idx_t, hipStream_t st) {
     if (nt > 0) {
         a.tiles_per_wave = ceil_div(nt, kVCountWaves);
         nw = ceil_div(nt, a.tiles_per_wave);
-        IXP_LAUNCH("flatv_count", (flatv_count_kernel<V, Cls>), dim3(static_cast<uint32_t>(ceil_div(nw, 4))),
-                   dim3(256), 0, st, a, cl);
+        if (a.tiles_per_wave == 1)
+            IXP_LAUNCH("flatv_count", (flatv_count_small_kernel<V, Cls>), dim3(static_cast<uint32_t>(nt)), dim3(256), 0,
+                       st, a, cl);
+        else
+            IXP_LAUNCH("flatv_count", (flatv_count_kernel<V, Cls>), dim3(static_cast<uint32_t>(ceil_div(nw, 4))),
+                       dim3(256), 0, st, a, cl);
     }
     IXP_LAUNCH("flatv_scan", flatv_scan_kernel<V>, dim3(1), dim3(1024), 0, st, a.wsum, nw, a.n, a.counts);
     if (nt == 0) return launch_status();

@@ -83,3 +83,17 @@ def test_partition3_config_2e28():
     counting wave."""
     x = W.f32_uniform(W.FLAT_LARGE_N, W.FLAT_LARGE_SEED)
     run_both(x, 3, O.CLASS_THRESH, (1 / 3, 2 / 3, 0.0), idx_dtype=torch.int32)
+
+
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 4095, 4097, 8192 * 4096 - 3, 8192 * 4096 + 1])
+@pytest.mark.parametrize("v", [2, 3, 4])
+def test_partition_v_counting_widths(n, v):
+    """A wave counts 1024 elements of a tile up to 8192 tiles, whole tiles beyond:
+    both sides of the 1024-, 4096-element and 8192-tile edges, every kind of class."""
+    g = np.random.default_rng(n + v)
+    dt = torch.int32
+    run_both(g.integers(-2**31, 2**31, n).astype(np.int32), v, O.CLASS_MOD, idx_dtype=dt)
+    f = g.random(n).astype(np.float32)
+    f[g.integers(0, n, 3)] = np.nan
+    run_both(f, v, O.CLASS_THRESH, s=(0.25, 0.25, 0.75), idx_dtype=dt)
+    run_both(f, v, O.CLASS_BYTES, cls=g.integers(0, 6, n).astype(np.uint8), idx_dtype=dt)
