@@ -285,3 +285,12 @@ def test_filter_tile_sizes(n):
         run_both(f32[:n], "lt", 1, torch.int32, s=s)
     run_both(f32[:n], "lt", 1, torch.int64, s=0.4)
     run_both(f32[1:], "lt", 1, torch.int32, keys_t=torch.from_numpy(f32).to(DEV)[1:], s=0.4)   # element loads
+
+
+@pytest.mark.parametrize("n", [1024 * 4096 + 1, 8192 * 4096 - 5, 8192 * 4096, 8192 * 4096 + 1])
+def test_partition_counting_widths(n):
+    """A workgroup counts a tile up to 8192 tiles, a wave a run of tiles beyond;
+    up to 1024 tiles the scan of the counts is the scatter's."""
+    run_both(W.int_keys(n, 98), "mod", 0, torch.int32, d=3, r=1)
+    f32 = W.f32_uniform(n + 1, 99)
+    run_both(f32[1:], "lt", 0, torch.int32, keys_t=torch.from_numpy(f32).to(DEV)[1:], s=0.3)
