@@ -293,24 +293,32 @@ __device__ __forceinline__ int64_t lookback(const uint64_t *desc, int64_t t,
 }
 
 // ------------------------------------------------------------ streaming loads --
-// Input keys and flags are read exactly once: nontemporal loads keep them from
-// displacing reusable lines in the caches.
+// Input keys and flags that are read once, or that the Infinity Cache (256 MB)
+// could not hold until the next pass, take nontemporal loads (NT), which keep
+// them from displacing reusable lines; a pass whose input is read again soon
+// uses plain ones.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-template <int VEC>
+template <bool NT, class T>
+__device__ __forceinline__ T load_once(const T *p) {
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
+template <int VEC, bool NT = true>
 __device__ __forceinline__ void load_group(const uint32_t *p, uint32_t (&out)[VEC]) {
     if constexpr (VEC == 4) {
-        const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+        const u32x4 v = load_once<NT>(reinterpret_cast<const u32x4 *>(p));
         out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
     } else {
-        out[0] = __builtin_nontemporal_load(p);
+        out[0] = load_once<NT>(p);
     }
 }
 
-template <int VEC>
+template <int VEC, bool NT = true>
 __device__ __forceinline__ void load_flags(const uint8_t *p, uint8_t (&out)[VEC]) {
     if constexpr (VEC == 4) {
-        const uint32_t w = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p));
+        const uint32_t w = load_once<NT>(reinterpret_cast<const uint32_t *>(p));
 #pragma unroll
         for (int q = 0; q < VEC; ++q) out[q] = static_cast<uint8_t>(w >> (8 * q));
     } else {
@@ -368,8 +376,8 @@ struct Tile {
     // group) does the same, but rows that miss [lo, hi) re-read the group
     // containing lo instead (a cache hit), so the loads still form one
     // branch-free batch; the tile holding the incomplete last group uses
-    // element-wise guarded loads.
-    template <class Pred>
+    // element-wise guarded loads.  With NT = false the loads are plain ones.
+    template <bool NT = true, class Pred>
     __device__ __forceinline__ void load(const uint32_t *keys, int64_t n, int64_t base,
                                          int64_t lo, int64_t hi, const Pred &pred,
                                          bool need_keys, int wave, int lane) {
@@ -383,12 +391,12 @@ struct Tile {
             if constexpr (Pred::kUsesFlags) fp = pred.flags + pos(base, wave, 0, lane, 0);
 #pragma unroll
             for (int r = 0; r < ROWS; ++r) {
-                if (need_keys) load_group(kp + r * (kWave * VEC), kv[r]);
+                if (need_keys) load_group<VEC, NT>(kp + r * (kWave * VEC), kv[r]);
                 else {
 #pragma unroll
                     for (int q = 0; q < VEC; ++q) kv[r][q] = 0;
                 }
-                if constexpr (Pred::kUsesFlags) load_flags(fp + r * (kWave * VEC), fv[r]);
+                if constexpr (Pred::kUsesFlags) load_flags<VEC, NT>(fp + r * (kWave * VEC), fv[r]);
                 else {
 #pragma unroll
                     for (int q = 0; q < VEC; ++q) fv[r][q] = 0;
@@ -401,12 +409,12 @@ struct Tile {
                 const int64_t p0 = pos(base, wave, r, lane, 0);
                 const bool live = p0 + VEC > lo && p0 < hi;
                 const int64_t src = live ? p0 : park;
-                if (need_keys) load_group(keys + src, kv[r]);
+                if (need_keys) load_group<VEC, NT>(keys + src, kv[r]);
                 else {
 #pragma unroll
                     for (int q = 0; q < VEC; ++q) kv[r][q] = 0;
                 }
-                if constexpr (Pred::kUsesFlags) load_flags(pred.flags + src, fv[r]);
+                if constexpr (Pred::kUsesFlags) load_flags<VEC, NT>(pred.flags + src, fv[r]);
                 else {
 #pragma unroll
                     for (int q = 0; q < VEC; ++q) fv[r][q] = 0;

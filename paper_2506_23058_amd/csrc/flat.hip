@@ -132,7 +132,7 @@ __global__ void flat_init_kernel(uint32_t *ticket, int32_t *err, uint64_t *desc,
 // time (16 vector loads in flight per lane), writes
 // each tile's exclusive prefix inside the run to desc[t] and the run total to
 // wsum[w].
-template <int VEC, class Pred>
+template <int VEC, class Pred, bool NT>
 __global__ __launch_bounds__(256) void flat_count_kernel(FlatArgs a, Pred pred) {
     constexpr int kTile = FlatCfg<IXP_MODE_PARTITION, VEC>::kTile;
     using WT = Tile<kWave, (VEC == 4 ? IXP_COUNT_ROWS : 16), VEC>;
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(256) void flat_count_kernel(FlatArgs a, Pred pred) 
         uint32_t cnt = 0;
         for (int c = 0; c < kChunks; ++c) {
             WT chunk;
-            chunk.load(a.keys, a.n, lo + c * WT::kSize, lo, hi, pred, !Pred::kUsesFlags, 0, lane);
+            chunk.template load<NT>(a.keys, a.n, lo + c * WT::kSize, lo, hi, pred, !Pred::kUsesFlags, 0, lane);
             cnt += chunk.wave_count();
         }
         if (lane == 0) a.desc[t] = run;
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(256) void flat_count_kernel(FlatArgs a, Pred pred) 
 // scan).  One wave a tile leaves most of the chip idle: the count of 2 10^7 int32
 // keys took 22 us, now 14, and the partition 68.2 / 61.1; 5 10^6 23.5 / 20.9, 3.3 10^7
 // 103.4 / 97.6.
-template <int VEC, class Pred>
+template <int VEC, class Pred, bool NT>
 __global__ __launch_bounds__(256) void flat_count_small_kernel(FlatArgs a, Pred pred) {
     using WT = Tile<kWave, kSmallChunk / (kWave * VEC), VEC>;
     constexpr int kTile = FlatCfg<IXP_MODE_PARTITION, VEC>::kTile;
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(256) void flat_count_small_kernel(FlatArgs a, Pred 
         // [lo, lo + kSmallChunk).  (Passing min(thi, lo + kSmallChunk) here
         // made hipcc select the bound on a stale SCC after a VCC compare.)
         WT chunk;
-        chunk.load(a.keys, a.n, lo, lo, thi, pred, !Pred::kUsesFlags, 0, lane);
+        chunk.template load<NT>(a.keys, a.n, lo, lo, thi, pred, !Pred::kUsesFlags, 0, lane);
         cnt = chunk.wave_count();
     }
     if (lane == 0) wc[wave] = cnt;
@@ -243,6 +243,7 @@ __global__ __launch_bounds__(1024) void flat_tile_scan_kernel(int64_t *wsum, int
 // Paths (PATH):
 //   0  (partition) the tile prefix and T come from the counting kernel and the tile scan;
 //   2  (filter) tiles of twice the size, from kBigFilter elements on;
+//   3  (partition) as 0 with plain loads (see keep_keys);
 //   1  at most kSmallTiles tiles, counted by flat_count_small (one
 //      workgroup per tile, one wave per 1024 elements): every workgroup adds
 //      up the tile counts before its own and in total itself, and tile 0
@@ -254,7 +255,7 @@ __global__ __launch_bounds__((FlatCfg<MODE, VEC, PATH>::kBlock)) void flat_scan_
     constexpr int kTile = T::kSize;
     constexpr int kRows = Cfg::kRows;
     constexpr int kBlock = Cfg::kBlock;
-    static_assert(PATH == 0 || (PATH == 1) == (MODE == IXP_MODE_PARTITION), "path 1 partitions, path 2 filters");
+    static_assert(PATH == 0 || (PATH == 2) == (MODE == IXP_MODE_FILTER), "paths 1 and 3 partition, path 2 filters");
     __shared__ uint32_t stage[kTile];
     __shared__ uint32_t wtot[T::kWaves];
     __shared__ int64_t sh[2];
@@ -279,7 +280,7 @@ __global__ __launch_bounds__((FlatCfg<MODE, VEC, PATH>::kBlock)) void flat_scan_
     const int64_t hi = lo + kTile < a.n ? lo + kTile : a.n;
     // path 0: the tile prefix and T are ready before the kernel starts
     int64_t excl = 0, total = 0;
-    if (MODE == IXP_MODE_PARTITION && PATH == 0) {
+    if (MODE == IXP_MODE_PARTITION && PATH != 1) {
         excl = static_cast<int64_t>(a.desc[t]) + a.wsum[t / a.tiles_per_wave];
         total = *a.split;
     }
@@ -297,7 +298,7 @@ __global__ __launch_bounds__((FlatCfg<MODE, VEC, PATH>::kBlock)) void flat_scan_
     }
 
     T tile;
-    tile.load(a.keys, a.n, lo, lo, hi, pred, a.need_keys != 0, wave, lane);
+    tile.template load<PATH != 3>(a.keys, a.n, lo, lo, hi, pred, a.need_keys != 0, wave, lane);
     tile.wave_ranks();
     if constexpr (PATH == 1) {
         int64_t before = 0, all = 0;
@@ -495,6 +496,16 @@ int launch_one(const FlatArgs &a, const Pred &pred, int idx_t, hipStream_t st) {
     return launch_status();
 }
 
+// Whether a partition's two passes read the keys with plain loads: the Infinity
+// Cache (256 MB) then still holds part of them when the scatter comes, also of
+// arrays somewhat larger than itself.  Nontemporal / plain, f32 keys, 32-bit
+// indices: 8 10^6 28.2 / 28.0 us, 2 10^7 60.9 / 56.5, 5 10^7 147 / 127, 6.4 10^7 186 / 158,
+// 10^8 282 / 268, 1.2 10^8 336 / 328, 1.5 10^8 419 / 416, 2^28 712 / 749.  With 64-bit indices
+// the scatter's stores leave nothing to gain (5 10^7: 244 / 246).
+bool keep_keys(const FlatArgs &a, int idx_t) {
+    return (idx_t == IXP_I32 || !a.out_idx) && a.n >= (int64_t{1} << 23) && a.n <= (int64_t{1} << 27);
+}
+
 template <int VEC, class Pred>
 int launch_flat(FlatArgs a, const Pred &pred, int mode, int idx_t, hipStream_t st) {
     const int64_t n = a.n;
@@ -507,15 +518,22 @@ int launch_flat(FlatArgs a, const Pred &pred, int mode, int idx_t, hipStream_t s
         const int64_t nt = a.num_tiles;
         int64_t nw = 0;
         const bool small = nt > 0 && nt <= kSmallTiles;
+        const bool keep = keep_keys(a, idx_t);
         if (nt > 0 && nt <= kCountWaves) {
             nw = nt;
-            IXP_LAUNCH("flat_count", (flat_count_small_kernel<VEC, Pred>), dim3(static_cast<uint32_t>(nt)),
-                       dim3(256), 0, st, a, pred);
+            const dim3 grid(static_cast<uint32_t>(nt));
+            if (keep)
+                IXP_LAUNCH("flat_count", (flat_count_small_kernel<VEC, Pred, false>), grid, dim3(256), 0, st, a, pred);
+            else
+                IXP_LAUNCH("flat_count", (flat_count_small_kernel<VEC, Pred, true>), grid, dim3(256), 0, st, a, pred);
         } else if (nt > 0) {
             a.tiles_per_wave = ceil_div(nt, kCountWaves);
             nw = ceil_div(nt, a.tiles_per_wave);
-            IXP_LAUNCH("flat_count", (flat_count_kernel<VEC, Pred>),
-                       dim3(static_cast<uint32_t>(ceil_div(nw, 4))), dim3(256), 0, st, a, pred);
+            const dim3 grid(static_cast<uint32_t>(ceil_div(nw, 4)));
+            if (keep)
+                IXP_LAUNCH("flat_count", (flat_count_kernel<VEC, Pred, false>), grid, dim3(256), 0, st, a, pred);
+            else
+                IXP_LAUNCH("flat_count", (flat_count_kernel<VEC, Pred, true>), grid, dim3(256), 0, st, a, pred);
         }
         if (!small)
             IXP_LAUNCH("flat_tile_scan", flat_tile_scan_kernel, dim3(1), dim3(1024), 0, st, a.wsum, nw,
@@ -532,6 +550,9 @@ int launch_flat(FlatArgs a, const Pred &pred, int mode, int idx_t, hipStream_t s
                 IXP_LAUNCH("flat_scatter_partition",
                            (flat_scan_kernel<VEC, Pred, IXP_MODE_PARTITION, int64_t, 1>),
                            dim3(static_cast<uint32_t>(nt)), dim3(Cfg::kBlock), 0, st, a, pred);
+        } else if (keep) {
+            IXP_LAUNCH("flat_scatter_partition", (flat_scan_kernel<VEC, Pred, IXP_MODE_PARTITION, int32_t, 3>),
+                       dim3(static_cast<uint32_t>(nt)), dim3(Cfg::kBlock), cap, st, a, pred);
         } else if (idx_t == IXP_I32) {
             IXP_LAUNCH("flat_scatter_partition", (flat_scan_kernel<VEC, Pred, IXP_MODE_PARTITION, int32_t>),
                        dim3(static_cast<uint32_t>(nt)), dim3(Cfg::kBlock), cap, st, a, pred);
