@@ -122,7 +122,8 @@ struct TileV {
     // one unconditional 16-byte load per row for whole tiles, parked loads
     // for partial tiles, guarded element loads where the array's last group
     // is incomplete.
-    template <class Cls>
+    // NT = false: plain loads.
+    template <bool NT, class Cls>
     __device__ __forceinline__ void load(const uint32_t *keys, int64_t n, int64_t base, int64_t lo, int64_t hi,
                                          const Cls &cl, bool need_keys, int wave, int lane) {
         const bool tail = (n & 3) != 0 && hi > (n & ~int64_t{3});
@@ -137,13 +138,13 @@ struct TileV {
                 const bool live = whole || (p0 + 4 > lo && p0 < hi);
                 const int64_t src = live ? p0 : park;
                 uint32_t k4[4];
-                if (need_keys) load_group<4>(keys + src, k4);
+                if (need_keys) load_group<4, NT>(keys + src, k4);
                 else {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) k4[q] = 0;
                 }
                 uint8_t b4[4] = {0, 0, 0, 0};
-                if constexpr (Cls::kUsesBytes) load_flags<4>(cl.cls + src, b4);
+                if constexpr (Cls::kUsesBytes) load_flags<4, NT>(cl.cls + src, b4);
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     kv[r][q] = k4[q];
@@ -282,7 +283,7 @@ __device__ __forceinline__ void count_upto(const Cls &cl, uint32_t key, uint8_t 
 
 // cum[k] = elements of class <= k among [lo, lo + kRows 64 x 4) before n, by one
 // wave; all its loads in flight at once where the stretch is whole.
-template <int V, int kRows, class Cls>
+template <int V, int kRows, bool NT, class Cls>
 __device__ __forceinline__ void wave_upto(const VArgs &a, const Cls &cl, int64_t lo, int lane, uint32_t (&cum)[V - 1]) {
 #pragma unroll
     for (int k = 0; k < V - 1; ++k) cum[k] = 0;
@@ -292,8 +293,8 @@ __device__ __forceinline__ void wave_upto(const VArgs &a, const Cls &cl, int64_t
 #pragma unroll
         for (int r = 0; r < kRows; ++r) {
             const int64_t p = lo + r * (kWave * 4) + lane * 4;
-            if constexpr (Cls::kUsesBytes) load_flags<4>(cl.cls + p, byte[r]);
-            else load_group<4>(a.keys + p, key[r]);
+            if constexpr (Cls::kUsesBytes) load_flags<4, NT>(cl.cls + p, byte[r]);
+            else load_group<4, NT>(a.keys + p, key[r]);
         }
 #pragma unroll
         for (int r = 0; r < kRows; ++r)
@@ -318,7 +319,7 @@ __device__ __forceinline__ void wave_upto(const VArgs &a, const Cls &cl, int64_t
 // popcount per element row and class: packed one-hot counters took a dozen
 // vector instructions an element and held the registers of half the batch
 // (5 10^7 keys in 3 classes 42 -> 35 us, 2 10^8 by modulus 182 -> 132).
-template <int V, class Cls>
+template <int V, class Cls, bool NT>
 __global__ __launch_bounds__(256) void flatv_count_kernel(VArgs a, Cls cl) {
     constexpr int kTile = kVBlockThreads * kVRows * 4;
     const int lane = threadIdx.x & (kWave - 1);
@@ -330,7 +331,7 @@ __global__ __launch_bounds__(256) void flatv_count_kernel(VArgs a, Cls cl) {
     for (int k = 0; k < V - 1; ++k) run[k] = 0;
     for (int64_t t = t0; t < t1; ++t) {
         uint32_t cum[V - 1];
-        wave_upto<V, kTile / (kWave * 4)>(a, cl, t * kTile, lane, cum);
+        wave_upto<V, kTile / (kWave * 4), NT>(a, cl, t * kTile, lane, cum);
         if (lane < V - 1) {
             uint64_t mine = run[0];
 #pragma unroll
@@ -350,14 +351,14 @@ __global__ __launch_bounds__(256) void flatv_count_kernel(VArgs a, Cls cl) {
 
 // The same where a run is one tile: a workgroup per tile, a wave per quarter
 // (one wave a tile leaves most of the chip idle).
-template <int V, class Cls>
+template <int V, class Cls, bool NT>
 __global__ __launch_bounds__(256) void flatv_count_small_kernel(VArgs a, Cls cl) {
     constexpr int kQuarter = kVBlockThreads * kVRows;
     __shared__ uint32_t sh[4][V - 1];
     const int lane = threadIdx.x & (kWave - 1), wave = wave_id();
     const int64_t t = blockIdx.x;
     uint32_t cum[V - 1];
-    wave_upto<V, kQuarter / (kWave * 4)>(a, cl, (4 * t + wave) * kQuarter, lane, cum);
+    wave_upto<V, kQuarter / (kWave * 4), NT>(a, cl, (4 * t + wave) * kQuarter, lane, cum);
     if (lane == 0) {
 #pragma unroll
         for (int k = 0; k < V - 1; ++k) sh[wave][k] = cum[k] - (k > 0 ? cum[k - 1] : 0u);
@@ -434,7 +435,7 @@ __global__ __launch_bounds__(1024) void flatv_scan_kernel(int64_t *wsum, int64_t
     if (tid == 0) counts[V - 1] = rest;
 }
 
-template <int V, class Cls, class Idx>
+template <int V, class Cls, class Idx, bool NT>
 __global__ __launch_bounds__(kVBlockThreads) void flatv_scatter_kernel(VArgs a, Cls cl) {
     using T = TileV<kVBlockThreads, kVRows, V>;
     constexpr int kTile = T::kSize;
@@ -465,7 +466,7 @@ __global__ __launch_bounds__(kVBlockThreads) void flatv_scatter_kernel(VArgs a, 
     }
 
     T tile;
-    tile.load(a.keys, a.n, lo, lo, hi, cl, a.need_keys != 0, wave, lane);
+    tile.template load<NT>(a.keys, a.n, lo, lo, hi, cl, a.need_keys != 0, wave, lane);
     tile.wave_ranks(lane);
     const uint64_t ptot = tile.block_ranks(wt, wave, lane);
     uint32_t tot[V], sbase[V];   // class sizes and stage offsets inside the tile
@@ -500,8 +501,8 @@ __global__ __launch_bounds__(kVBlockThreads) void flatv_scatter_kernel(VArgs a, 
     }
 }
 
-template <int V, class Cls>
-int launch_v(VArgs a, const Cls &cl, int idx_t, hipStream_t st) {
+template <int V, class Cls, bool NT>
+int launch_passes(VArgs a, const Cls &cl, int idx_t, hipStream_t st) {
     constexpr int64_t kTile = kVBlockThreads * kVRows * 4;
     a.num_tiles = ceil_div(a.n, kTile);
     const int64_t nt = a.num_tiles;
@@ -510,21 +511,33 @@ int launch_v(VArgs a, const Cls &cl, int idx_t, hipStream_t st) {
         a.tiles_per_wave = ceil_div(nt, kVCountWaves);
         nw = ceil_div(nt, a.tiles_per_wave);
         if (a.tiles_per_wave == 1)
-            IXP_LAUNCH("flatv_count", (flatv_count_small_kernel<V, Cls>), dim3(static_cast<uint32_t>(nt)), dim3(256), 0,
-                       st, a, cl);
+            IXP_LAUNCH("flatv_count", (flatv_count_small_kernel<V, Cls, NT>), dim3(static_cast<uint32_t>(nt)),
+                       dim3(256), 0, st, a, cl);
         else
-            IXP_LAUNCH("flatv_count", (flatv_count_kernel<V, Cls>), dim3(static_cast<uint32_t>(ceil_div(nw, 4))),
+            IXP_LAUNCH("flatv_count", (flatv_count_kernel<V, Cls, NT>), dim3(static_cast<uint32_t>(ceil_div(nw, 4))),
                        dim3(256), 0, st, a, cl);
     }
     IXP_LAUNCH("flatv_scan", flatv_scan_kernel<V>, dim3(1), dim3(1024), 0, st, a.wsum, nw, a.n, a.counts);
     if (nt == 0) return launch_status();
+    const dim3 grid(static_cast<uint32_t>(nt));
     if (idx_t == IXP_I32)
-        IXP_LAUNCH("flatv_scatter", (flatv_scatter_kernel<V, Cls, int32_t>), dim3(static_cast<uint32_t>(nt)),
-                   dim3(kVBlockThreads), 0, st, a, cl);
+        IXP_LAUNCH("flatv_scatter", (flatv_scatter_kernel<V, Cls, int32_t, NT>), grid, dim3(kVBlockThreads), 0, st, a,
+                   cl);
     else
-        IXP_LAUNCH("flatv_scatter", (flatv_scatter_kernel<V, Cls, int64_t>), dim3(static_cast<uint32_t>(nt)),
-                   dim3(kVBlockThreads), 0, st, a, cl);
+        IXP_LAUNCH("flatv_scatter", (flatv_scatter_kernel<V, Cls, int64_t, NT>), grid, dim3(kVBlockThreads), 0, st, a,
+                   cl);
     return launch_status();
+}
+
+// Plain loads in both passes where the Infinity Cache (256 MB) still holds part
+// of the keys when the scatter comes.  Nontemporal / plain, 3 classes by
+// threshold, 32-bit indices: 8 10^6 30.7 / 28.9 us, 2 10^7 64.3 / 62.2, 5 10^7 149 / 130,
+// 8 10^7 229 / 223, 10^8 286 / 306; by modulus, 64-bit indices: 5 10^7 276 / 258, 8 10^7
+// 439 / 421, 10^8 547 / 557.
+template <int V, class Cls>
+int launch_v(const VArgs &a, const Cls &cl, int idx_t, hipStream_t st) {
+    const bool keep = a.n >= (int64_t{1} << 22) && a.n <= int64_t{5} << 24;
+    return keep ? launch_passes<V, Cls, false>(a, cl, idx_t, st) : launch_passes<V, Cls, true>(a, cl, idx_t, st);
 }
 
 template <int V>
