@@ -354,7 +354,14 @@ void props_scan_kernel(PropsArgs a) {
         if (tid == 0 && e0 > 0) wfirst = load_x(a.x, X64 ? 1 : 0, e0 - 1);
         __syncthreads();
     }
-    uint32_t off[kElems], meta[kElems];   // offset in bucket; bucket << 16 | rank, or kOut
+    // Offsets in Rcd of the thread's elements and which of them lie inside; the
+    // three other checks beside them, each skipped by the whole wave where it has
+    // nothing to report.
+    static_assert(kElems == 32, "a bit per element");
+    const uint64_t width = static_cast<uint64_t>(a.hi) - static_cast<uint64_t>(a.lo);
+    const bool whole = e1 - e0 == kChunk;   // (uniform)
+    const bool img_all = a.ilo <= a.lo && a.hi <= a.ihi;
+    uint32_t off[kElems], in_bits = 0;
 #pragma unroll
     for (int u = 0; u < kGroups; ++u) {
         const int64_t gi = g_lo + tid + u * kScanThreads;
@@ -368,7 +375,7 @@ void props_scan_kernel(PropsArgs a) {
             val[2 % kPer] = static_cast<int32_t>(raw[u].z);
             val[3 % kPer] = static_cast<int32_t>(raw[u].w);
         }
-        const bool live = gi < g_hi;
+        const bool live = whole || gi < g_hi;
         const int64_t p0 = gi * kPer;
         int64_t prev = 0;
         if (want_mono) {
@@ -380,26 +387,53 @@ void props_scan_kernel(PropsArgs a) {
 #pragma unroll
         for (int q = 0; q < kPer; ++q) {
             const int k = u * kPer + q;
-            const int64_t i = p0 + q;
+            const unsigned long long i = static_cast<unsigned long long>(p0 + q);
             const int64_t v = val[q];
-            meta[k] = kOut;
-            off[k] = 0;
-            if (!live) continue;
-            if (want_range && !(a.lo <= v && v < a.hi) && static_cast<unsigned long long>(i) < c_range)
-                c_range = i;
-            if (want_mono && i > 0 && !cmp.ok(prev, v) && static_cast<unsigned long long>(i) < c_mono)
-                c_mono = i;
-            prev = v;
-            if (a.lo <= v && v < a.hi) {
-                if (want_img && !(a.ilo <= v && v < a.ihi) && static_cast<unsigned long long>(i) < c_img)
-                    c_img = i;
-                const uint64_t o = static_cast<uint64_t>(v - a.lo);
-                const uint32_t bk = static_cast<uint32_t>(o >> a.bshift);
-                off[k] = static_cast<uint32_t>(o) & ((1u << a.bshift) - 1);
-                meta[k] = (bk << 16) | atomicAdd(bstart + bk, 1u);
+            // (v - lo as an unsigned number is below the width exactly when lo <= v < hi)
+            const uint64_t o = static_cast<uint64_t>(v) - static_cast<uint64_t>(a.lo);
+            const bool in = live && o < width;
+            off[k] = static_cast<uint32_t>(o);
+            in_bits |= static_cast<uint32_t>(in) << k;
+            if (want_range) {
+                const bool bad = live && !in;
+                if (ballot(bad) && bad && i < c_range) c_range = i;
+            }
+            if (want_mono) {
+                const bool bad = live && i > 0 && !cmp.ok(prev, v);
+                if (ballot(bad) && bad && i < c_mono) c_mono = i;
+                prev = v;
+            }
+            if (want_img && !img_all) {
+                const bool bad = in && !(a.ilo <= v && v < a.ihi);
+                if (ballot(bad) && bad && i < c_img) c_img = i;
             }
         }
     }
+    // Ranks inside the buckets.  A wave whose elements all lie in Rcd issues its
+    // LDS atomics back to back; a branch around each, with its result combined at
+    // once, made every one of them wait (2^27 int64: 294 -> 284 us, 2^28 811 -> 791 for
+    // Range + Inj + Bij).
+    uint32_t rank[kElems / 2];   // two 16-bit ranks each (a chunk holds 2^14 elements)
+    const bool all_in = ballot(in_bits != ~0u) == 0;
+    if (all_in) {
+#pragma unroll
+        for (int k = 0; k < kElems; k += 8) {
+            uint32_t r[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) r[j] = atomicAdd(bstart + (off[k + j] >> a.bshift), 1u);
+#pragma unroll
+            for (int j = 0; j < 8; j += 2) rank[(k + j) / 2] = r[j] | (r[j + 1] << 16);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kElems; k += 2) {
+            uint32_t r0 = 0, r1 = 0;
+            if ((in_bits >> k) & 1u) r0 = atomicAdd(bstart + (off[k] >> a.bshift), 1u);
+            if ((in_bits >> (k + 1)) & 1u) r1 = atomicAdd(bstart + (off[k + 1] >> a.bshift), 1u);
+            rank[k / 2] = r0 | (r1 << 16);
+        }
+    }
+    auto rank_of = [&](int k) { return (rank[k / 2] >> (16 * (k % 2))) & 0xFFFFu; };
     // the chunk's last n % kPer elements (only in the chunk holding the end
     // of the array): thread 0, one at a time
     uint32_t toff[3] = {0, 0, 0}, tmeta[3] = {kOut, kOut, kOut};
@@ -452,9 +486,15 @@ void props_scan_kernel(PropsArgs a) {
     __syncthreads();
     for (int b = tid; b <= nb; b += kScanThreads)
         a.ctab[static_cast<int64_t>(b) * a.nchunks + c] = static_cast<uint16_t>(bstart[b]);
+    const uint32_t bmask = (1u << a.bshift) - 1;
+    if (all_in) {
 #pragma unroll
-    for (int k = 0; k < kElems; ++k)
-        if (meta[k] != kOut) stage[bstart[meta[k] >> 16] + (meta[k] & 0xFFFFu)] = off[k];
+        for (int k = 0; k < kElems; ++k) stage[bstart[off[k] >> a.bshift] + rank_of(k)] = off[k] & bmask;
+    } else {
+#pragma unroll
+        for (int k = 0; k < kElems; ++k)
+            if ((in_bits >> k) & 1u) stage[bstart[off[k] >> a.bshift] + rank_of(k)] = off[k] & bmask;
+    }
     if (tid == 0) {
         for (int j = 0; j < 3; ++j)
             if (tmeta[j] != kOut) stage[bstart[tmeta[j] >> 16] + (tmeta[j] & 0xFFFFu)] = toff[j];
