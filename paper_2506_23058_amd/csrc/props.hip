@@ -55,7 +55,7 @@ struct PropsState {
     // FiltPart
     unsigned long long fp_fv;          // least index failing bits 1..4
     unsigned int fp_bits;              // OR of failing sub-check bits (2..16)
-    unsigned int pad1;
+    unsigned int done;                 // workgroups of the last kernel that are through
 };
 constexpr size_t kPropsHeader = 256;
 static_assert(sizeof(PropsState) <= kPropsHeader, "props header");
@@ -136,6 +136,7 @@ __global__ void props_init_kernel(PropsState *st, uint32_t *seen, uint32_t *dup,
         st->nrep = 0;
         st->fp_fv = kNone;
         st->fp_bits = 0;
+        st->done = 0;
     }
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
     typedef uint32_t v4 __attribute__((ext_vector_type(4)));
@@ -663,6 +664,31 @@ __device__ __forceinline__ uint32_t rep_hash(uint64_t o, int log2_slots) {
     return static_cast<uint32_t>((o * 0x9E3779B97F4A7C15ull) >> (64 - log2_slots));
 }
 
+// Value inserted by the Inj / Bij bitmap for element i, or false.
+__device__ __forceinline__ bool inserted_value(const PropsArgs &a, int64_t i, int64_t *v_out) {
+    const int64_t v = load_x(a.x, a.x64, i);
+    *v_out = v;
+    return a.lo <= v && v < a.hi;
+}
+
+__device__ __forceinline__ bool is_dup(const PropsArgs &a, int64_t v) {
+    const uint64_t o = static_cast<uint64_t>(v - a.lo);
+    return (a.dup[o >> 5] >> (o & 31)) & 1u;
+}
+
+// When more values repeat than the list holds: least index of every repeated
+// value, in the global table (the second pass over it is props_finish's).
+__device__ __forceinline__ void props_first(const PropsArgs &a) {
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < a.n; i += stride) {
+        int64_t v;
+        if (!inserted_value(a, i, &v) || !is_dup(a, v)) continue;
+        const uint64_t o = static_cast<uint64_t>(v - a.lo);
+        if (a.first64) atomicMin(a.first64 + o, static_cast<unsigned long long>(i));
+        else atomicMin(a.first + o, static_cast<uint32_t>(i));
+    }
+}
+
 // Streams X once more (only when some value repeats and the list held every
 // repeated value).  Each workgroup first builds an LDS hash table of the
 // listed values (entry: value - lo << 12 | position in the list; the layout
@@ -682,7 +708,11 @@ void props_rescan_kernel(PropsArgs a) {
     constexpr int kPer = X64 ? 2 : 4;
     __shared__ unsigned long long tab[kRepSlots];
     const uint32_t nrep = a.st->nrep;
-    if (nrep == 0 || nrep > static_cast<uint32_t>(kRepCap)) return;
+    if (nrep == 0) return;
+    if (nrep > static_cast<uint32_t>(kRepCap)) {
+        props_first(a);
+        return;
+    }
     uint32_t tsz = 64;
     while (tsz < 4 * nrep) tsz <<= 1;
     const int lg = __builtin_ctz(tsz);
@@ -779,35 +809,9 @@ void props_rescan_kernel(PropsArgs a) {
     if ((threadIdx.x & 63) == 0 && cand != kNone) atomicMin(&a.st->fv_inj, cand);
 }
 
-// Value inserted by the Inj / Bij bitmap for element i, or false.
-__device__ __forceinline__ bool inserted_value(const PropsArgs &a, int64_t i, int64_t *v_out) {
-    const int64_t v = load_x(a.x, a.x64, i);
-    *v_out = v;
-    return a.lo <= v && v < a.hi;
-}
-
-__device__ __forceinline__ bool is_dup(const PropsArgs &a, int64_t v) {
-    const uint64_t o = static_cast<uint64_t>(v - a.lo);
-    return (a.dup[o >> 5] >> (o & 31)) & 1u;
-}
-
-// Fallback when more values repeat than the list holds.  Pass 2: least index
-// of every repeated value.
-__global__ __launch_bounds__(kPropsBlock) void props_first_kernel(PropsArgs a) {
-    if (a.st->nrep <= static_cast<uint32_t>(kRepCap)) return;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < a.n; i += stride) {
-        int64_t v;
-        if (!inserted_value(a, i, &v) || !is_dup(a, v)) continue;
-        const uint64_t o = static_cast<uint64_t>(v - a.lo);
-        if (a.first64) atomicMin(a.first64 + o, static_cast<unsigned long long>(i));
-        else atomicMin(a.first + o, static_cast<uint32_t>(i));
-    }
-}
-
-// Fallback pass 3: least index that is not the first occurrence of its value.
-__global__ __launch_bounds__(kPropsBlock) void props_second_kernel(PropsArgs a, unsigned long long *target) {
-    if (a.st->nrep <= static_cast<uint32_t>(kRepCap)) return;
+// The table's second pass: least index that is not the first occurrence of its
+// value.
+__device__ __forceinline__ void props_second(const PropsArgs &a) {
     unsigned long long c = kNone;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < a.n; i += stride) {
@@ -818,16 +822,12 @@ __global__ __launch_bounds__(kPropsBlock) void props_second_kernel(PropsArgs a, 
         if (static_cast<uint64_t>(i) != f && static_cast<unsigned long long>(i) < c) c = i;
     }
     c = wave_min_u64(c);
-    if ((threadIdx.x & 63) == 0 && c != kNone) atomicMin(target, c);
+    if ((threadIdx.x & 63) == 0 && c != kNone) atomicMin(&a.st->fv_inj, c);
 }
 
 // Bij failing only on the count: least value of Img whose bit is clear.
-__global__ __launch_bounds__(kPropsBlock) void props_missing_kernel(PropsArgs a) {
-    if (a.bucketed) return;
+__device__ __forceinline__ void props_missing(const PropsArgs &a) {
     PropsState *st = a.st;
-    const unsigned long long inj = st->fv_inj, img = st->fv_img;
-    if (inj != kNone || img != kNone) return;
-    if (static_cast<int64_t>(st->in_count) == a.ihi - a.ilo) return;
     const int64_t b0 = a.ilo - a.lo, b1 = a.ihi - a.lo;   // bit range inside the bitmap
     unsigned long long c = kNone;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
@@ -918,6 +918,7 @@ __global__ __launch_bounds__(kFpThreads) void fp_last_kernel(PropsArgs a, Pred p
         a.st->dup_found = 0;
         a.st->fp_fv = kNone;
         a.st->fp_bits = 0;
+        a.st->done = 0;
     }
     const int64_t e0 = b * a.fp_range;
     const int64_t e1 = e0 + a.fp_range < a.n ? e0 + a.fp_range : a.n;
@@ -1174,11 +1175,10 @@ __global__ __launch_bounds__(kPropsBlock) void fp_insert_kernel(PropsArgs a, Pre
     if (ballot(dup_seen) != 0 && (threadIdx.x & 63) == 0) atomicOr(&a.st->dup_found, 1u);
 }
 
-// FiltPart's repeats, among the values fp_insert inserted.
+// FiltPart's repeats, among the values fp_insert inserted: pass 0 takes the least
+// index of each repeated value, pass 1 the least index that is not one of those.
 template <class Pred>
-__global__ __launch_bounds__(kPropsBlock) void fp_first_kernel(PropsArgs a, Pred pred, int pass,
-                                                               unsigned long long *target) {
-    if (a.st->dup_found == 0) return;
+__device__ __forceinline__ void fp_repeats(const PropsArgs &a, const Pred &pred, int pass) {
     const int64_t split = *a.fp_split;
     unsigned long long c = kNone;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
@@ -1197,18 +1197,24 @@ __global__ __launch_bounds__(kPropsBlock) void fp_first_kernel(PropsArgs a, Pred
     if (pass == 1) {
         c = wave_min_u64(c);
         if ((threadIdx.x & 63) == 0 && c != kNone) {
-            atomicMin(target, c);
+            atomicMin(&a.st->fp_fv, c);
             atomicOr(&a.st->fp_bits, 2u);
         }
     }
 }
 
-// Writes the five verdicts (one workgroup, which first adds up the ranges'
-// counts of trues for FiltPart).
-__global__ void props_finalize_kernel(PropsArgs a, ixp_verdict *out) {
+template <class Pred>
+__global__ __launch_bounds__(kPropsBlock) void fp_first_kernel(PropsArgs a, Pred pred) {
+    if (a.st->dup_found != 0) fp_repeats(a, pred, 0);
+}
+
+// Writes the five verdicts (one workgroup of at most 1024 threads, which first
+// adds up the ranges' counts of trues for FiltPart).  The state is read past the
+// caches: other workgroups of the same launch may have written it.
+__device__ __forceinline__ void props_verdicts(const PropsArgs &a, ixp_verdict *out) {
     __shared__ unsigned long long wsum[1024 / kWave];
     unsigned long long fp_trues = 0;
-    if (a.fp_nranges > 0) {
+    if (a.mask & IXP_FILTPART) {
         for (int64_t r = threadIdx.x; r < a.fp_nranges; r += blockDim.x) fp_trues += a.fp_count[r];
         fp_trues = wave_sum_u64(fp_trues);
         if ((threadIdx.x & (kWave - 1)) == 0) wsum[wave_id()] = fp_trues;
@@ -1217,7 +1223,14 @@ __global__ void props_finalize_kernel(PropsArgs a, ixp_verdict *out) {
         for (uint32_t w = 0; w < blockDim.x / kWave; ++w) fp_trues += wsum[w];
     }
     if (threadIdx.x != 0) return;
-    const PropsState *st = a.st;
+    PropsState *s = a.st;
+    auto get = [](const unsigned long long *p) {
+        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    const unsigned long long fv_range = get(&s->fv_range), fv_mono = get(&s->fv_mono), fv_img = get(&s->fv_img),
+                             fv_inj = get(&s->fv_inj), in_count = get(&s->in_count), missing = get(&s->missing),
+                             fp_fv = get(&s->fp_fv);
+    uint32_t fp_bits = __hip_atomic_load(&s->fp_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (int b = 0; b < 5; ++b) {
         out[b].holds = 1;
         out[b].reserved = 0;
@@ -1229,37 +1242,80 @@ __global__ void props_finalize_kernel(PropsArgs a, ixp_verdict *out) {
         out[b].first_violation = fv;
         out[b].aux = aux;
     };
-    if ((a.mask & IXP_RANGE) && st->fv_range != kNone)
-        fail(0, st->fv_range, load_x(a.x, a.x64, st->fv_range));
-    if ((a.mask & IXP_MONO) && st->fv_mono != kNone) fail(1, st->fv_mono, 0);
-    if ((a.mask & IXP_INJ) && st->fv_inj != kNone)
-        fail(2, st->fv_inj, load_x(a.x, a.x64, st->fv_inj));
+    if ((a.mask & IXP_RANGE) && fv_range != kNone) fail(0, fv_range, load_x(a.x, a.x64, fv_range));
+    if ((a.mask & IXP_MONO) && fv_mono != kNone) fail(1, fv_mono, 0);
+    if ((a.mask & IXP_INJ) && fv_inj != kNone) fail(2, fv_inj, load_x(a.x, a.x64, fv_inj));
     if (a.mask & IXP_BIJ) {
-        const unsigned long long f = st->fv_inj < st->fv_img ? st->fv_inj : st->fv_img;
+        const unsigned long long f = fv_inj < fv_img ? fv_inj : fv_img;
         if (f != kNone) fail(3, f, load_x(a.x, a.x64, f));
-        else if (static_cast<int64_t>(st->in_count) != a.ihi - a.ilo)
-            fail(3, a.n, a.ilo + static_cast<int64_t>(st->missing));
+        else if (static_cast<int64_t>(in_count) != a.ihi - a.ilo)
+            fail(3, a.n, a.ilo + static_cast<int64_t>(missing));
     }
     if (a.mask & IXP_FILTPART) {
-        uint32_t bits = st->fp_bits;
-        if (static_cast<int64_t>(fp_trues) != *a.fp_split) bits |= 1u;
-        if (bits) fail(4, st->fp_fv != kNone ? static_cast<int64_t>(st->fp_fv) : a.n, bits);
+        if (static_cast<int64_t>(fp_trues) != *a.fp_split) fp_bits |= 1u;
+        if (fp_bits) fail(4, fp_fv != kNone ? static_cast<int64_t>(fp_fv) : a.n, fp_bits);
     }
 }
 
+// True for the workgroup that passes here last of those that have `items` to go
+// over.  They have made atomics on the state and no stores, so waiting for those
+// orders them: a fence in each of 2048 workgroups, with every workgroup counted,
+// cost 100 us (a missing value among 5000 entries: 130 us, so 18.4).
+__device__ __forceinline__ bool last_workgroup(const PropsArgs &a, int64_t items) {
+    __shared__ int last;
+    int64_t parts = (items + blockDim.x - 1) / blockDim.x;
+    if (parts > gridDim.x) parts = gridDim.x;
+    if (parts < 1) parts = 1;
+    if (blockIdx.x >= parts) return false;
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0)
+        last = __hip_atomic_fetch_add(&a.st->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == parts;
+    __syncthreads();
+    return last != 0;
+}
+
+// The last kernel of a call without FiltPart (`out` is NULL when FiltPart's
+// follow): usually workgroup 0 writes the verdicts at once; a pass that is still
+// needed (the table's second one, or the least missing value) takes the whole
+// grid, and whichever workgroup ends last writes them.  A small call is bound by
+// its launches, about 2 us each: with the table's two passes, the missing value
+// and the verdicts in kernels of their own, Range, Inj and Bij of 5000 int64
+// entries took 24 us, now 18 us (1e6 entries: 30.6, now 28.7).
+__global__ __launch_bounds__(kPropsBlock) void props_finish_kernel(PropsArgs a, ixp_verdict *out) {
+    const PropsState *st = a.st;
+    const bool second = (a.mask & (IXP_INJ | IXP_BIJ)) && st->nrep > static_cast<uint32_t>(kRepCap);
+    const bool missing = !second && (a.mask & IXP_BIJ) && !a.bucketed && st->fv_inj == kNone && st->fv_img == kNone &&
+                         static_cast<int64_t>(st->in_count) != a.ihi - a.ilo;
+    if (second) props_second(a);
+    else if (missing) props_missing(a);
+    if (!out) return;
+    if (second || missing ? last_workgroup(a, second ? a.n : ((a.ihi - a.lo) >> 5) - ((a.ilo - a.lo) >> 5) + 1)
+                          : blockIdx.x == 0)
+        props_verdicts(a, out);
+}
+
+// The last kernel of a call with FiltPart.
 template <class Pred>
-int launch_filtpart(PropsArgs a, const Pred &pred, hipStream_t st, int grid, bool init) {
+__global__ __launch_bounds__(kPropsBlock) void fp_finish_kernel(PropsArgs a, PropsArgs main, Pred pred,
+                                                                ixp_verdict *out) {
+    const bool second = a.st->dup_found != 0;
+    if (second) fp_repeats(a, pred, 1);
+    if (second ? last_workgroup(a, a.n) : blockIdx.x == 0) props_verdicts(main, out);
+}
+
+template <class Pred>
+int launch_filtpart(const PropsArgs &a, const PropsArgs &main, const Pred &pred, ixp_verdict *out, hipStream_t st,
+                    int grid, bool init) {
     if (a.fp_nranges > 0) {
         const dim3 ranges(static_cast<uint32_t>(a.fp_nranges));
         IXP_LAUNCH("fp_last", (fp_last_kernel<Pred>), ranges, dim3(kFpThreads), 0, st, a, pred, init ? 1 : 0);
         if (a.x64) IXP_LAUNCH("fp_check", (fp_check_kernel<true, Pred>), ranges, dim3(kFpThreads), 0, st, a, pred);
         else IXP_LAUNCH("fp_check", (fp_check_kernel<false, Pred>), ranges, dim3(kFpThreads), 0, st, a, pred);
         IXP_LAUNCH("fp_insert", (fp_insert_kernel<Pred>), dim3(grid), dim3(kPropsBlock), 0, st, a, pred);
-        IXP_LAUNCH("fp_first", (fp_first_kernel<Pred>), dim3(grid), dim3(kPropsBlock), 0, st, a, pred, 0,
-                   &a.st->fp_fv);
-        IXP_LAUNCH("fp_second", (fp_first_kernel<Pred>), dim3(grid), dim3(kPropsBlock), 0, st, a, pred, 1,
-                   &a.st->fp_fv);
+        IXP_LAUNCH("fp_first", (fp_first_kernel<Pred>), dim3(grid), dim3(kPropsBlock), 0, st, a, pred);
     }
+    IXP_LAUNCH("fp_finish", (fp_finish_kernel<Pred>), dim3(grid), dim3(kPropsBlock), 0, st, a, main, pred, out);
     return launch_status();
 }
 
@@ -1456,15 +1512,15 @@ extern "C" int ixp_check_props(const void *x, int32_t x_t, int64_t n, uint32_t m
             else
                 IXP_LAUNCH("props_rescan", (props_rescan_kernel<false, 1>), dim3(kRescanGrid), dim3(kRescanThreads),
                            0, st, b);
-            IXP_LAUNCH("props_first", props_first_kernel, dim3(grid), dim3(kPropsBlock), 0, st, b);
-            IXP_LAUNCH("props_second", props_second_kernel, dim3(grid), dim3(kPropsBlock), 0, st, b,
-                       &a.st->fv_inj);
         }
-        if ((main_mask & IXP_BIJ) && !b.bucketed)   // props_check finds it on the chunked path
-            IXP_LAUNCH("props_missing", props_missing_kernel, dim3(grid), dim3(kPropsBlock), 0, st, b);
         if (launch_status() != IXP_OK) return IXP_EHIP;
-    } else if ((main_mask & IXP_BIJ) && n == 0) {
-        IXP_LAUNCH("props_missing", props_missing_kernel, dim3(grid), dim3(kPropsBlock), 0, st, a);
+    }
+    ixp_verdict *const fp_none = nullptr;
+    if (main_mask || !(mask & IXP_FILTPART)) {
+        PropsArgs b = a;
+        b.mask = main_mask;
+        IXP_LAUNCH("props_finish", props_finish_kernel, dim3(grid), dim3(kPropsBlock), 0, st, b,
+                   (mask & IXP_FILTPART) ? fp_none : d_out);
     }
     if (mask & IXP_FILTPART) {
         // FiltPart's bijection check uses its own bitmap over [0, n): the
@@ -1474,12 +1530,11 @@ extern "C" int ixp_check_props(const void *x, int32_t x_t, int64_t n, uint32_t m
         f.hi = n;
         int rc = IXP_OK;
         switch (hp.kind) {
-        case IXP_PRED_MOD_EQ: rc = launch_filtpart(f, mod_eq_pred(hp.d, hp.r), st, grid, fp_only); break;
-        case IXP_PRED_LT: rc = launch_filtpart(f, PredLt{hp.s}, st, grid, fp_only); break;
-        default: rc = launch_filtpart(f, PredFlags{hp.flags}, st, grid, fp_only); break;
+        case IXP_PRED_MOD_EQ: rc = launch_filtpart(f, a, mod_eq_pred(hp.d, hp.r), d_out, st, grid, fp_only); break;
+        case IXP_PRED_LT: rc = launch_filtpart(f, a, PredLt{hp.s}, d_out, st, grid, fp_only); break;
+        default: rc = launch_filtpart(f, a, PredFlags{hp.flags}, d_out, st, grid, fp_only); break;
         }
         if (rc != IXP_OK) return rc;
     }
-    IXP_LAUNCH("props_finalize", props_finalize_kernel, dim3(1), dim3(a.fp_nranges > 0 ? 1024 : kWave), 0, st, a, d_out);
     return launch_status();
 }

@@ -100,7 +100,7 @@ def workspace(nbytes: int, device, tag: str = "default") -> torch.Tensor:
     device; calls that share a tag must not overlap on different streams)."""
     key = _ws_key(device, tag)
     buf = _ws_cache.get(key)
-    if buf is None or buf.numel() < nbytes:
+    if buf is None or buf.nbytes < nbytes:
         buf = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
         _ws_cache[key] = buf
     return buf
@@ -459,9 +459,7 @@ def check_props(x: torch.Tensor, mask: int, lo: int = 0, hi: int = 0, img_lo: in
     rc = L.lib().ixp_check_props(_ptr(x), _IDX_T[x.dtype], n, mask, ctypes.byref(a), _ptr(out),
                                  _ptr(ws), ws.numel(), _stream_ptr(x.device))
     L.check(rc, "ixp_check_props")
-    v = out.view(5, 3).clone()
-    v[:, 0] = v[:, 0] & 0xFFFFFFFF   # holds is the low 32 bits of the first word
-    return v
+    return out.view(5, 3)   # (the word of `holds`: its upper half is written 0)
 
 
 def verdicts(v: torch.Tensor):

@@ -319,3 +319,23 @@ def test_bucket_widths(w):
     both(y - 3, ALL4, -3, w - 3, -3, w - 3)
     y[11] = y[60_000]
     both(y, ALL4, 0, w, 0, w)
+
+
+@pytest.mark.parametrize("n", [1, 255, 8192, 8193, 8225, 65_535, 70_001])
+def test_passes_of_the_last_kernel(n):
+    """A missing value, and more repeats than the list holds, with work for one, two
+    and several workgroups of the last kernel; FiltPart's verdict after both."""
+    g = np.random.default_rng(n)
+    p = g.permutation(n + 1)
+    both(p[:-1], ALL4, 0, n + 1, 0, n + 1)           # p[-1] is missing
+    both(p[:-1] - 40, ALL4, -45, n + 1, -40, n - 39)   # Img starts inside a word
+    x = g.integers(0, max(n // 2, 1), n)
+    v = both(x, ALL4, 0, n, 0, n)
+    keys = W.int_keys(n, 94)
+    op, gp = O.Pred.mod_eq(3, 1), P.Pred.mod_eq(3, 1)
+    ys, idx, t = O.partition2(keys, op, 0)
+    yt, st = torch.from_numpy(ys).to(DEV), torch.tensor([t], dtype=torch.int64, device=DEV)
+    fp = P.FiltPartArgs(torch.from_numpy(keys).to(DEV), yt, gp, st, 0)
+    for z, first in ((idx, [(1, -1, 0)] * 2), (x, v[2:4])):
+        got = P.verdicts(P.check_props(torch.from_numpy(z).to(DEV), ALL4 | P.FILTPART, 0, n, 0, n, fp=fp))
+        assert got[2:] == first + [O.check_filtpart(keys, op, 0, ys, z, t)]
