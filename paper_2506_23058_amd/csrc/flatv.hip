@@ -204,12 +204,7 @@ struct TileV {
             uint32_t mine = 0;
 #pragma unroll
             for (int q = 0; q < 4; ++q) mine += onehot9(cls(r, q), valid(r, q));
-            uint32_t inc = mine;
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) {
-                const uint32_t o = __shfl_up(inc, off, kWave);
-                if (lane >= off) inc += o;
-            }
+            const uint32_t inc = wave_scan_u32(mine);
             uint32_t run = inc - mine;
             const uint32_t pos0 = static_cast<uint32_t>(r * kWave * 4 + lane * 4);
 #pragma unroll
@@ -230,8 +225,7 @@ struct TileV {
         }
         // the last class of the run: valid elements minus the others
         uint32_t nvalid = static_cast<uint32_t>(__builtin_popcount(vbits));
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) nvalid += __shfl_xor(nvalid, off, kWave);
+        nvalid = wave_sum_u32(nvalid);
         uint32_t others = 0;
 #pragma unroll
         for (int k = 0; k < V - 1; ++k) others += field(acc, k);
@@ -397,16 +391,9 @@ __global__ __launch_bounds__(1024) void flatv_scan_kernel(int64_t *wsum, int64_t
     for (int k = 0; k < V - 1; ++k) {
 #pragma unroll
         for (int j = 0; j < kPer; ++j) run[k] += v[k][j];
-        inc[k] = run[k];
     }
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-#pragma unroll
-        for (int k = 0; k < V - 1; ++k) {
-            const int64_t o = __shfl_up(inc[k], off, 64);
-            if (lane >= off) inc[k] += o;
-        }
-    }
+    for (int k = 0; k < V - 1; ++k) inc[k] = wave_scan_i64(run[k]);
     if (lane == 63) {
 #pragma unroll
         for (int k = 0; k < V - 1; ++k) wtot[k][wave] = inc[k];

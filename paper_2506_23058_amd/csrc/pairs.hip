@@ -93,12 +93,7 @@ __global__ __launch_bounds__(kPairThreads) void pairs_bucket_kernel(PairArgs a) 
         uint32_t mine = 0;
         for (int j = 0; j < per; ++j)
             if (b0 + j <= nb) mine += bstart[b0 + j];
-        uint32_t inc = mine;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const uint32_t t = __shfl_up(inc, o, kWave);
-            if (lane >= o) inc += t;
-        }
+        const uint32_t inc = wave_scan_u32(mine);
         if (lane == kWave - 1) wtot[wave] = inc;
         __syncthreads();
         uint32_t run = inc - mine;
@@ -273,12 +268,7 @@ __global__ __launch_bounds__(1024) void pairs_scan_kernel(PairArgs a) {
             v[k] = i < a.nchunks ? a.count[i] : 0;
             run += v[k];
         }
-        int64_t inc = run;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const int64_t o = __shfl_up(inc, off, kWave);
-            if (lane >= off) inc += o;
-        }
+        const int64_t inc = wave_scan_i64(run);
         if (lane == kWave - 1) wtot[wave] = inc;
         __syncthreads();
         int64_t acc = carry + inc - run;
@@ -313,12 +303,7 @@ __global__ __launch_bounds__(256) void pairs_compact_kernel(PairArgs a) {
     {
         const uint64_t m = reinterpret_cast<const uint64_t *>(a.kept + c * kPairWords)[tid];
         const uint32_t n = static_cast<uint32_t>(__builtin_popcountll(m));
-        uint32_t inc = n;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const uint32_t t = __shfl_up(inc, o, kWave);
-            if (lane >= o) inc += t;
-        }
+        const uint32_t inc = wave_scan_u32(n);
         if (lane == kWave - 1) wtot[wave] = inc;
         mask[tid] = m;
         __syncthreads();

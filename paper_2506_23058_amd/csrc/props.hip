@@ -100,18 +100,11 @@ __device__ __forceinline__ int64_t load_x(const void *x, int32_t x64, int64_t i)
 }
 
 __device__ __forceinline__ unsigned long long wave_min_u64(unsigned long long v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const unsigned long long o = __shfl_xor(v, off, 64);
-        v = o < v ? o : v;
-    }
-    return v;
+    return wave_reduce_u64(v, [](uint64_t x, uint64_t y) { return x < y ? x : y; });
 }
 
 __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    return static_cast<unsigned long long>(wave_sum_i64(static_cast<int64_t>(v)));
 }
 
 __device__ __forceinline__ bool mono_ok(int64_t a, int64_t b, int op) {
@@ -466,12 +459,7 @@ void props_scan_kernel(PropsArgs a) {
         uint32_t mine = 0;
         for (int j = 0; j < per; ++j)
             if (b0 + j <= nb) mine += bstart[b0 + j];
-        uint32_t inc = mine;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const uint32_t t = __shfl_up(inc, o, 64);
-            if (lane >= o) inc += t;
-        }
+        const uint32_t inc = wave_scan_u32(mine);
         if (lane == kWave - 1) wtot[wave] = inc;
         __syncthreads();
         uint32_t run = inc - mine;
@@ -888,15 +876,6 @@ __device__ __forceinline__ FpElem fp_elem(const PropsArgs &a, const Pred &pred, 
 __device__ __forceinline__ bool fp_inserts(const PropsArgs &a, const FpElem &e, int64_t split) {
     return a.fp_mode == IXP_MODE_PARTITION ? (0 <= e.z && e.z < a.n)
                                            : (e.c && 0 <= e.z && e.z < split && e.z < a.n);
-}
-
-__device__ __forceinline__ int64_t wave_max_i64(int64_t v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const int64_t o = __shfl_xor(v, off, kWave);
-        v = o > v ? o : v;
-    }
-    return v;
 }
 
 // A value that is the same in every lane, moved to scalar registers.

@@ -172,12 +172,7 @@ template <int WAVES>
 __device__ __forceinline__ int64_t block_exclusive_scan(int64_t v, int64_t *lds, int64_t *total) {
     const int lane = threadIdx.x & 63;
     const int wave = wave_id();
-    int64_t inc = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int64_t o = __shfl_up(inc, off, 64);
-        if (lane >= off) inc += o;
-    }
+    const int64_t inc = wave_scan_i64(v);
     if (lane == 63) lds[wave] = inc;
     __syncthreads();
     int64_t before = 0, tot = 0;
@@ -328,16 +323,12 @@ __global__ __launch_bounds__(kSetupThreads) void seg_rows_kernel(SegArgs a) {
         const int64_t off0 = off + block_exclusive_scan<kSetupThreads / kWave>(sum_s, lds, &tot_s);
         int64_t prev = 0;
         if (a.short_max) {
-            int inc = last;   // running maximum over the lanes, then the waves
-#pragma unroll
-            for (int o = 1; o < kWave; o <<= 1) {
-                const int x = __shfl_up(inc, o, kWave);
-                if (lane >= o && x > inc) inc = x;
-            }
-            if (lane == kWave - 1) wlast[wave] = inc;
+            // `last` grows with the thread: the nearest one before, in the wave, then the waves
+            const uint64_t any = ballot(last != 0), under = any & ((1ull << lane) - 1);
+            int before = __shfl(last, under ? 63 - __builtin_clzll(under) : 0, kWave);
+            if (!under) before = 0;
+            if (lane == kWave - 1) wlast[wave] = last ? last : before;
             __syncthreads();
-            int before = __shfl_up(inc, 1, kWave);
-            if (lane == 0) before = 0;
             for (int w = 0; w < wave; ++w) before = wlast[w] > before ? wlast[w] : before;
             prev = before ? sz[before - 1] : 0;
             __syncthreads();   // wlast is reused
@@ -773,17 +764,15 @@ __device__ __forceinline__ void pack_starts(const SegArgs &a, const SegItem &d, 
         const int f1 = w1 ? 64 * lane + 32 + __builtin_ctz(w1) : kPackTile;
         const int l0 = w0 ? 64 * lane + 31 - __builtin_clz(w0) : -1;
         const int l1 = w1 ? 64 * lane + 63 - __builtin_clz(w1) : -1;
-        int last = l1 > l0 ? l1 : l0, next = f0 < f1 ? f0 : f1;
-#pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-            const int x = __shfl_up(last, o, kWave), y = __shfl_down(next, o, kWave);
-            if (lane >= o && x > last) last = x;
-            if (lane + o < kWave && y < next) next = y;
-        }
-        int before = __shfl_up(last, 1, kWave), after = __shfl_down(next, 1, kWave);
+        const int last = l1 > l0 ? l1 : l0, next = f0 < f1 ? f0 : f1;
+        // the nearest lanes on both sides with a start in their words
+        const uint64_t any = ballot((w0 | w1) != 0);
+        const uint64_t under = any & ((1ull << lane) - 1), over = any & ~((2ull << lane) - 1);
+        int before = __shfl(last, under ? 63 - __builtin_clzll(under) : 0, kWave);
+        int after = __shfl(next, over ? __builtin_ctzll(over) : 0, kWave);
         const int lo = static_cast<int>(d.lo - d.base), end = static_cast<int>(d.hi - d.base);
-        if (lane == 0 || before < lo) before = lo;
-        if (lane == kWave - 1 || after > end) after = end;
+        if (!under || before < lo) before = lo;
+        if (!over || after > end) after = end;
         p.before[2 * lane] = static_cast<int16_t>(before);
         p.before[2 * lane + 1] = static_cast<int16_t>(l0 >= 0 ? l0 : before);
         p.after[2 * lane + 1] = static_cast<int16_t>(after);

@@ -48,10 +48,7 @@ struct SgArgs {
 constexpr int kRedThreads = 256;
 
 __device__ __forceinline__ int64_t block_max(int64_t x, int64_t *lds) {
-    for (int off = 32; off > 0; off >>= 1) {
-        const int64_t o = __shfl_xor(x, off, kWave);
-        x = o > x ? o : x;
-    }
+    x = wave_max_i64(x);
     if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = x;
     __syncthreads();
     int64_t r = lds[0];
@@ -132,19 +129,17 @@ __global__ __launch_bounds__(1024) void sg_chunk_scan_kernel(SgArgs a) {
         e[k] = i < a.chunks ? Pair{a.agg_f[i] != 0, a.agg_v[i]} : Pair{false, 0};
         run = combine(run, e[k]);
     }
-    Pair inc = run;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        Pair o;
-        o.f = __shfl_up(static_cast<int>(inc.f), off, kWave) != 0;
-        o.v = __shfl_up(inc.v, off, kWave);
-        if (lane >= off) inc = combine(o, inc);
-    }
-    Pair before{__shfl_up(static_cast<int>(inc.f), 1, kWave) != 0, __shfl_up(inc.v, 1, kWave)};
-    if (lane == 0) before = Pair{false, 0};
+    // the sums wrap, so the sum since the last flag is a difference of plain
+    // prefix sums, as in the rescan
+    const uint64_t flagged = ballot(run.f);
+    const int64_t inc = wave_scan_i64(run.v), ex = inc - run.v;
+    const uint64_t below = flagged & ((1ull << lane) - 1);
+    const int64_t from = __shfl(ex, below ? 63 - __builtin_clzll(below) : 0, kWave);
+    const Pair before{below != 0, ex - from};
     if (lane == kWave - 1) {
-        wv[wave] = inc.v;
-        wf[wave] = inc.f ? 1 : 0;
+        const Pair all = combine(before, run);
+        wv[wave] = all.v;
+        wf[wave] = all.f ? 1 : 0;
     }
     __syncthreads();
     Pair acc{false, 0};
@@ -156,28 +151,6 @@ __global__ __launch_bounds__(1024) void sg_chunk_scan_kernel(SgArgs a) {
         if (i < a.chunks) a.agg_v[i] = acc.v;   // a flag only matters for later elements
         acc = combine(acc, e[k]);
     }
-}
-
-// Inclusive scan (+) over the lanes of a wave by DPP: four shifts inside the
-// rows of 16 lanes, then lane 15 of a row to the next row and lane 31 to the
-// upper half.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int64_t dpp_i64(int64_t v) {
-    const uint64_t u = static_cast<uint64_t>(v);
-    const uint32_t lo = static_cast<uint32_t>(
-        __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(u)), CTRL, ROWS, 0xF, false));
-    const uint32_t hi = static_cast<uint32_t>(
-        __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(u >> 32)), CTRL, ROWS, 0xF, false));
-    return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-__device__ __forceinline__ int64_t wave_scan_i64(int64_t v) {
-    v += dpp_i64<0x111, 0xF>(v);
-    v += dpp_i64<0x112, 0xF>(v);
-    v += dpp_i64<0x114, 0xF>(v);
-    v += dpp_i64<0x118, 0xF>(v);
-    v += dpp_i64<0x142, 0xA>(v);
-    v += dpp_i64<0x143, 0xC>(v);
-    return v;
 }
 
 // Rescan.  The sums wrap, so a running sum since the last flag is a difference
