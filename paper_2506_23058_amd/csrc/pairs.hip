@@ -18,9 +18,8 @@
 //   pairs_scan   -- one workgroup: exclusive scan of the chunks' counts;
 //   pairs_compact - one workgroup per chunk: copies the kept entries.
 // 28 bytes per entry in pairs_bucket, 24 to 28 in pairs_reduce, 4 in pairs_mark,
-// 16 to 32 in pairs_compact; for 2^26 entries over 2^24 vertices 359, 596, 50 and
-// 284 us (5.2, 2.9, 5.4 and 4.7 TB/s): 1280 us in all, 5130 step by step.
-// pairs_reduce is bound by instructions: half of its lanes hold an entry.
+// 16 to 32 in pairs_compact; for 2^26 entries over 2^24 vertices 353, 601, 49 and
+// 262 us (5.3, 2.9, 5.5 and 5.1 TB/s): 1255 us in all, 5130 step by step.
 #include "device.hpp"
 #include "host.hpp"
 
@@ -135,16 +134,22 @@ __global__ __launch_bounds__(kPairThreads) void pairs_bucket_kernel(PairArgs a) 
 }
 
 // Neighbouring buckets' runs share cache lines, so the buckets of one XCD are
-// consecutive.  A run is 16384 / nb entries on average (8 with 2048 buckets):
-// 16 lanes read one, kRuns runs per lane group at once (2: 643 us, 8: 597); what a
-// longer run holds beyond 16 entries is taken by the whole wave.  With 1024 buckets
-// of 128 KiB one workgroup fits a CU, and the kernel takes 964 us.
+// consecutive.  A run is 16384 / nb entries on average (8 with 2048 buckets), so a
+// wave takes the runs of 16 chunks as one sequence of positions, 64 a row: a bit
+// marks where a run starts, and a position's run is the number of such bits up to
+// it.  (With 16 lanes to a run half of them were idle, and longer runs took a loop
+// of their own: 7.7e6 entries over 6.2e5 vertices 61.6 us, so 39.4; 3e7 over 3e7
+// 336 us, so 324; 2^26 over 2^24 597, now 601.)  Past that the lines bound it: the XCD's workgroups drift
+// apart, and of 64 chunks to a wave too few of the shared lines stay in its L2
+// (2^26 entries over 2^24 vertices: 64 chunks 650 us, 8 642, 16 601).  With 1024
+// buckets of 128 KiB one workgroup fits a CU, and the kernel takes 964 us.
 template <int SHIFT>   // at least a.shift
 __global__ __launch_bounds__(kPairThreads) void pairs_reduce_kernel(PairArgs a) {
-    constexpr int kLanes = 16, kGroups = kWave / kLanes, kRuns = 4, kUnroll = 4;
+    constexpr int kWaves = kPairThreads / kWave, kUnroll = 4, kRows = 32, kRuns = 16;
+    __shared__ uint64_t heads[kWaves][kRows];   // where runs start, among kRows * 64 positions
+    __shared__ uint32_t places[kWaves][kWave];
     __shared__ int64_t lds[1 << SHIFT];   // this bucket's part of H
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = wave_id();
-    const int sub = lane / kLanes, sl = lane % kLanes;
     const int64_t b = xcd_tile(blockIdx.x, a.nb);
     const int64_t v0 = b << a.shift;
     const int width = static_cast<int>(a.n_verts - v0 < (int64_t{1} << a.shift) ? a.n_verts - v0
@@ -153,61 +158,59 @@ __global__ __launch_bounds__(kPairThreads) void pairs_reduce_kernel(PairArgs a) 
     for (int i = tid; i < width; i += kPairThreads) lds[i] = a.neutral;
     __syncthreads();
     const uint16_t *rs = a.ctab + b * a.nchunks, *re = rs + a.nchunks;
+    // few chunks are dealt to all waves
+    const int64_t each = ceil_div(a.nchunks, kWaves);
+    const int runs = each < kRuns ? static_cast<int>(each) : kRuns;
     auto pass = [&](auto &&take) {
-        constexpr int kStep = kGroups * kRuns;
-        for (int64_t cb = static_cast<int64_t>(wave) * kStep; cb < a.nchunks; cb += kPairThreads / kWave * kStep) {
-            uint32_t s[kRuns], e[kRuns], rec[kRuns];
-            int64_t id[kRuns];
+        for (int64_t cb = static_cast<int64_t>(wave) * runs; cb < a.nchunks; cb += kWaves * runs) {
+            const int64_t c = cb + lane;
+            const bool live = lane < runs && c < a.nchunks;
+            const uint32_t s = live ? rs[c] : 0u, n = live ? re[c] - s : 0u;
+            const uint32_t inc = wave_scan_u32(n), start = inc - n;
+            const uint32_t total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inc), kWave - 1));
+            // of the non-empty runs in turn: place of the run's first entry minus its position
+            const uint64_t any = ballot(n > 0);
+            if (n > 0) places[wave][rank_below(any)] = (static_cast<uint32_t>(lane) << kPairChunkLog) + s - start;
+            uint32_t *rec = a.rec + (cb << kPairChunkLog);
+            const int64_t *ids = a.ids + (cb << kPairChunkLog);
+            int before = -1;   // runs that start before the row, minus 1
+            for (uint32_t w0 = 0; w0 < total; w0 += kRows * kWave) {
+                if (lane < kRows) heads[wave][lane] = 0;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                if (n > 0 && start - w0 < static_cast<uint32_t>(kRows * kWave))
+                    atomicOr(reinterpret_cast<unsigned long long *>(&heads[wave][(start - w0) >> 6]),
+                             1ull << (start & 63));
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                for (int r = 0; r < kRows && w0 + r * kWave < total; r += kUnroll) {
+                    uint32_t at[kUnroll], x[kUnroll];
+                    int64_t id[kUnroll];
+                    const uint32_t p = w0 + r * kWave + lane;
 #pragma unroll
-            for (int u = 0; u < kRuns; ++u) {
-                const int64_t c = cb + u * kGroups + sub;
-                s[u] = c < a.nchunks ? rs[c] : 0u;
-                e[u] = c < a.nchunks ? re[c] : 0u;
-            }
-#pragma unroll
-            for (int u = 0; u < kRuns; ++u) {
-                const int64_t at = ((cb + u * kGroups + sub) << kPairChunkLog) + s[u] + sl;
-                const bool in = s[u] + sl < e[u];
-                rec[u] = in ? a.rec[at] : 0u;
-                id[u] = in ? a.ids[at] : 0;
-            }
-#pragma unroll
-            for (int u = 0; u < kRuns; ++u) {
-                const int64_t at = ((cb + u * kGroups + sub) << kPairChunkLog) + s[u] + sl;
-                if (s[u] + sl < e[u]) take(at, rec[u], id[u]);
-            }
-#pragma unroll
-            for (int u = 0; u < kRuns; ++u) {
-                uint64_t more = ballot(sl == 0 && e[u] - s[u] > kLanes);
-                while (more) {
-                    const int l = __builtin_ctzll(more);
-                    more &= more - 1;
-                    const uint32_t p1 = __builtin_amdgcn_readlane(e[u], l);
-                    const int64_t c0 = (cb + u * kGroups + l / kLanes) << kPairChunkLog;
-                    for (uint32_t p = __builtin_amdgcn_readlane(s[u], l) + kLanes + lane; ballot(p < p1);
-                         p += kUnroll * kWave) {
-                        uint32_t r[kUnroll];
-                        int64_t d[kUnroll];
-#pragma unroll
-                        for (int k = 0; k < kUnroll; ++k) {
-                            const bool in = p + k * kWave < p1;
-                            r[k] = in ? a.rec[c0 + p + k * kWave] : 0u;
-                            d[k] = in ? a.ids[c0 + p + k * kWave] : 0;
-                        }
-#pragma unroll
-                        for (int k = 0; k < kUnroll; ++k)
-                            if (p + k * kWave < p1) take(c0 + p + k * kWave, r[k], d[k]);
+                    for (int u = 0; u < kUnroll; ++u) {
+                        const uint64_t m = readlane_u64(heads[wave][r + u], 0);
+                        const int j = before + static_cast<int>(m & 1) + static_cast<int>(rank_below(m >> 1));
+                        before += __builtin_popcountll(m);
+                        at[u] = places[wave][j] + p + u * kWave;
                     }
+#pragma unroll
+                    for (int u = 0; u < kUnroll; ++u) {
+                        const bool in = p + u * kWave < total;
+                        x[u] = in ? rec[at[u]] : 0u;
+                        id[u] = in ? ids[at[u]] : 0;
+                    }
+#pragma unroll
+                    for (int u = 0; u < kUnroll; ++u)
+                        if (p + u * kWave < total) take(rec + at[u], x[u], id[u]);
                 }
             }
         }
     };
-    pass([&](int64_t, uint32_t r, int64_t id) {
+    pass([&](uint32_t *, uint32_t r, int64_t id) {
         atomicMin(reinterpret_cast<long long *>(lds) + (r & vmask), static_cast<long long>(id));
     });
     __syncthreads();
-    pass([&](int64_t at, uint32_t r, int64_t id) {
-        if (lds[r & vmask] == id) a.rec[at] = r | kKept;
+    pass([&](uint32_t *at, uint32_t r, int64_t id) {
+        if (lds[r & vmask] == id) *at = r | kKept;
     });
     for (int i = tid; i < width; i += kPairThreads) stream_store(a.hist + v0 + i, lds[i]);
 }

@@ -82,3 +82,17 @@ def test_pairs_beyond_the_fused_range(monkeypatch):
     es, is_ = g.integers(0, (1 << 25) + 1, 5000), g.permutation(5000)
     assert not P.SmallestPairs((1 << 25) + 1, 5000, torch.from_numpy(es).to(DEV), torch.from_numpy(is_).to(DEV)).fused
     _run((1 << 25) + 1, 5000, es, is_)
+
+
+@pytest.mark.parametrize("k", [63, 64, 65, 2047, 2048, 2049, 16384])
+def test_fused_pairs_positions_of_a_wave(k, monkeypatch):
+    """A wave of the reducing pass takes the runs of 16 chunks as rows of 64
+    positions, 2048 marked at a time: k entries of bucket 0 in a chunk, a chunk
+    without any, and more chunks than the workgroup's waves take at once."""
+    monkeypatch.setattr(P.SmallestPairs, "FUSED_MIN", 0)
+    g = np.random.default_rng(k)
+    m, verts = 257 * 16384 + 5, 1 << 20
+    es = g.integers(verts // 2, verts, m)
+    for c in (0, 1, 3, 15, 16, 255, 256):
+        es[c * 16384:c * 16384 + k] = g.integers(0, 64, k)
+    _fused(verts, m, es, g.permutation(m))
