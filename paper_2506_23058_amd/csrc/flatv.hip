@@ -7,14 +7,14 @@
 //   B_c = N_0 + ... + N_{c-1},   N_c = size of class c.
 // It is partition2 with v - 1 counters instead of one.  Three kernels, as for
 // partition2:
-//   count   -- one wave per contiguous run of tiles: per-class counts by
-//              ballot + popcount, each tile's per-class prefix inside its run
-//              and the run totals;
-//   scan    -- one workgroup: exclusive scan of the run totals of every
-//              class but the last, and the class sizes N_c;
-//   scatter -- one workgroup per tile: per-class in-tile ranks from one
-//              ballot per class and (row, quad), indices in input order, keys
-//              staged in LDS class by class and written as v contiguous runs.
+//   count   -- one workgroup per tile up to 8192 tiles, else one wave per
+//              contiguous run of tiles: per-class counts by cumulative ballots
+//              + popcount (each tile's prefix inside its run and the totals);
+//   scan    -- one workgroup: exclusive scan of the totals of every class but
+//              the last, and the class sizes N_c;
+//   scatter -- one workgroup per tile: per-class in-tile ranks from one packed
+//              DPP scan per row, indices in input order, keys staged in LDS
+//              class by class and written as v contiguous runs.
 #include "device.hpp"
 #include "host.hpp"
 

@@ -139,10 +139,11 @@ __global__ __launch_bounds__(kPairThreads) void pairs_bucket_kernel(PairArgs a) 
 // marks where a run starts, and a position's run is the number of such bits up to
 // it.  (With 16 lanes to a run half of them were idle, and longer runs took a loop
 // of their own: 7.7e6 entries over 6.2e5 vertices 61.6 us, so 39.4; 3e7 over 3e7
-// 336 us, so 324; 2^26 over 2^24 597, now 601.)  Past that the lines bound it: the XCD's workgroups drift
-// apart, and of 64 chunks to a wave too few of the shared lines stay in its L2
-// (2^26 entries over 2^24 vertices: 64 chunks 650 us, 8 642, 16 601).  With 1024
-// buckets of 128 KiB one workgroup fits a CU, and the kernel takes 964 us.
+// 336 us, so 324; 2^26 over 2^24 597, now 601.)  Past that the lines bound it: the
+// XCD's workgroups drift apart, and of 64 chunks to a wave too few of the shared
+// lines stay in its L2 (2^26 entries over 2^24 vertices: 64 chunks 650 us, 8 642,
+// 16 601).  With 1024 buckets of 128 KiB one workgroup fits a CU, and the kernel
+// takes 964 us.
 template <int SHIFT>   // at least a.shift
 __global__ __launch_bounds__(kPairThreads) void pairs_reduce_kernel(PairArgs a) {
     constexpr int kWaves = kPairThreads / kWave, kUnroll = 4, kRows = 32, kRuns = 16;

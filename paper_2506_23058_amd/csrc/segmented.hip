@@ -63,7 +63,7 @@ constexpr int kSibMax = 256;
 constexpr uint64_t kCntReady = kStA;
 constexpr uint32_t kSibPolls = 64;
 
-// Per-item descriptor written by seg_items and completed by seg_item_bases.
+// Per-item descriptor written by write_item and completed by seg_item_bases.
 struct alignas(16) SegItem {
     int64_t lo, hi;      // valid positions [lo, hi)
     int64_t base;        // first position of the item's tile (4-aligned; see row_first_base)
@@ -1446,9 +1446,16 @@ int launch_all(const SegArgs &a, const Pred &p, const SegGeom &g, int mode, int 
 // row / with packed items, by the rows' mean size: 16: 5165 / 172 us, 128: 750 /
 // 145, 512: 251 / 173, 1024: 171 / 170, 2048: 121 / 144 (a packed item costs
 // more per element, and rows above 1024 elements cut the packed ones short).
-constexpr int64_t kPackMean = 768;
+// Below kPackMinRows rows a workgroup per row fills the chip in a wave or two, and a
+// few packed items leave it idle.  Rows of 128, partition / filter / filter by a
+// predicate of the row / the helpers, an item per row against packed: 1000 rows
+// 23.5, 25.3, 25.2, 35.6 / 23.2, 25.6, 31.4, 37.6 us; 2000 rows 24.2, 30.7, 30.4,
+// 37.3 / 24.7, 26.0, 31.8, 39.1; 4000 rows 30.9, 38.9, 38.8, 41.9 / 25.3, 27.4,
+// 33.3, 41.6.
+constexpr int64_t kPackMean = 768, kPackMinRows = 2048;
 bool packs(int64_t n, int64_t m, const SegGeom &g) {
-    return g.block == kPackThreads && g.rows == kPackRows && m > 0 && n / m <= kPackMean && n < (int64_t{1} << 42);
+    return g.block == kPackThreads && g.rows == kPackRows && m >= kPackMinRows && n / m <= kPackMean &&
+           n < (int64_t{1} << 42);
 }
 
 size_t seg_workspace(int64_t n, int64_t m, const SegGeom &g) {

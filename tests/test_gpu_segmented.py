@@ -441,3 +441,19 @@ def test_invalid_shape_of_short_rows_writes_nothing(m):
                               seg_split=seg)
         assert P.segmented_error() == -1
         assert all(bool((t == -5).all()) for t in (out, idx, seg))
+
+
+@pytest.mark.parametrize("name", [k for k, v in _short_shapes().items() if len(v) < 2048])
+def test_short_rows_share_items_from_2048_rows_on(name, monkeypatch):
+    """The same edges in shapes with enough rows for items to be shared: the rows
+    are followed by empty ones."""
+    shape = np.concatenate([_short_shapes()[name].astype(np.int64), np.zeros(2048, np.int64)])
+    monkeypatch.setitem(globals(), "_short_shapes", lambda: {name: shape})
+    test_short_rows_share_items(name)
+
+
+@pytest.mark.parametrize("m", [2047, 2048, 2049])
+def test_short_rows_around_2048_rows(m, monkeypatch):
+    shape = np.random.default_rng(m).integers(0, 40, m)
+    monkeypatch.setitem(globals(), "_short_shapes", lambda: {"rows": shape})
+    test_short_rows_share_items("rows")
