@@ -114,6 +114,9 @@ size_t ixp_partition_workspace(int64_t n);
  * key_t: IXP_I32 or IXP_F32 (see ixp_pred); idx_t: IXP_I32 (needs n < 2^31)
  * or IXP_I64.  out_keys and out_idx may each be NULL (not produced); d_split
  * is required.  n == 0 is valid and writes T = 0.
+ * In place: out_keys may be `keys` in FILTER mode, or a 32-bit out_idx may be
+ * `keys` in both modes; otherwise no output may overlap an input or another
+ * output.
  * Enqueues 1 to 3 kernels on `stream`; capturable into a HIP graph. */
 int ixp_partition(const void *keys, int32_t key_t, int64_t n,
                   const ixp_pred *pred, int32_t mode, void *out_keys,

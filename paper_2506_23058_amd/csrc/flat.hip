@@ -287,6 +287,14 @@ __global__ __launch_bounds__((FlatCfg<MODE, VEC, PATH>::kBlock)) void flat_scan_
 
     T tile;
     tile.template load<PATH != 3>(a.keys, a.n, lo, lo, hi, pred, a.need_keys != 0, wave, lane);
+    if constexpr (MODE == IXP_MODE_FILTER && Pred::kUsesFlags) {
+        // the keys are here before the count is published: a later tile may then
+        // write over them (in place), and the count alone does not read them
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+#pragma unroll
+            for (int q = 0; q < VEC; ++q) asm volatile("" : "+v"(tile.key[r][q]));
+    }
     tile.wave_ranks();
     if constexpr (PATH == 1) {
         int64_t before = 0, all = 0;
@@ -495,9 +503,11 @@ bool keep_keys(const FlatArgs &a, int idx_t) {
 }
 
 template <int VEC, class Pred>
-int launch_flat(FlatArgs a, const Pred &pred, int mode, int idx_t, hipStream_t st) {
+int launch_flat(FlatArgs a, const Pred &pred, int mode, int idx_t, bool apart, hipStream_t st) {
     const int64_t n = a.n;
-    if (n > 0 && n <= kOneMax)
+    // flat_one's workgroups read each other's elements at any time, so several of
+    // them need outputs apart from the inputs (partition_impl)
+    if (n > 0 && n <= (apart ? kOneMax : int64_t{kOneTile}))
         return mode == IXP_MODE_PARTITION ? launch_one<VEC, Pred, IXP_MODE_PARTITION>(a, pred, idx_t, st)
                                           : launch_one<VEC, Pred, IXP_MODE_FILTER>(a, pred, idx_t, st);
     if (mode == IXP_MODE_PARTITION) {
@@ -577,19 +587,19 @@ int launch_flat(FlatArgs a, const Pred &pred, int mode, int idx_t, hipStream_t s
 }
 
 template <int VEC>
-int dispatch_pred(const FlatArgs &a, const HostPred &hp, int mode, int idx_t, hipStream_t st) {
+int dispatch_pred(const FlatArgs &a, const HostPred &hp, int mode, int idx_t, bool apart, hipStream_t st) {
     switch (hp.kind) {
     case IXP_PRED_MOD_EQ: {
         const PredModEq p = mod_eq_pred(hp.d, hp.r);
-        return launch_flat<VEC>(a, p, mode, idx_t, st);
+        return launch_flat<VEC>(a, p, mode, idx_t, apart, st);
     }
     case IXP_PRED_LT: {
         PredLt p{hp.s};
-        return launch_flat<VEC>(a, p, mode, idx_t, st);
+        return launch_flat<VEC>(a, p, mode, idx_t, apart, st);
     }
     default: {
         PredFlags p{hp.flags};
-        return launch_flat<VEC>(a, p, mode, idx_t, st);
+        return launch_flat<VEC>(a, p, mode, idx_t, apart, st);
     }
     }
 }
@@ -650,7 +660,18 @@ int partition_impl(const void *keys, int32_t key_t, int64_t n, const ixp_pred *p
 
     const bool vec4 = aligned(keys, 16) && aligned(out_idx, 16) &&
                       (hp.kind != IXP_PRED_FLAGS || aligned(hp.flags, 4));
-    return vec4 ? dispatch_pred<4>(a, hp, mode, idx_t, st) : dispatch_pred<1>(a, hp, mode, idx_t, st);
+    // In place (a filter's out_keys on keys, 32-bit out_idx on keys) the paths that
+    // read the other tiles' elements before any tile writes are the ones to take:
+    // the look-back, whose tiles write below their own end once the earlier ones
+    // have loaded, and the counting launch of a partition.
+    const uint8_t *flags = hp.kind == IXP_PRED_FLAGS ? hp.flags : nullptr;
+    auto meets = [&](const void *out, size_t esz) {
+        const size_t bytes = static_cast<size_t>(n) * esz;
+        return (need_keys && overlap(out, bytes, keys, static_cast<size_t>(n) * 4)) ||
+               overlap(out, bytes, flags, static_cast<size_t>(n));
+    };
+    const bool apart = !meets(out_keys, 4) && !meets(out_idx, isz);
+    return vec4 ? dispatch_pred<4>(a, hp, mode, idx_t, apart, st) : dispatch_pred<1>(a, hp, mode, idx_t, apart, st);
 }
 
 // Static scratch of ixp_partition_noalloc: one copy per device, allocated when

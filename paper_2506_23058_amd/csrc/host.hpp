@@ -14,6 +14,12 @@ inline bool aligned(const void *p, uintptr_t a) {
     return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0;
 }
 
+// Whether [p, p + np) and [q, q + nq) share a byte (a NULL buffer has none).
+inline bool overlap(const void *p, size_t np, const void *q, size_t nq) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+    return p && q && a < b + nq && b < a + np;
+}
+
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 inline size_t round_up(size_t a, size_t b) { return (a + b - 1) / b * b; }

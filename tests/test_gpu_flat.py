@@ -294,3 +294,45 @@ def test_partition_counting_widths(n):
     run_both(W.int_keys(n, 98), "mod", 0, torch.int32, d=3, r=1)
     f32 = W.f32_uniform(n + 1, 99)
     run_both(f32[1:], "lt", 0, torch.int32, keys_t=torch.from_numpy(f32).to(DEV)[1:], s=0.3)
+
+
+@pytest.mark.parametrize("n", [4095, 4096, 4097, 8193, 16_384, 16_385, 20_481, 32_768, 32_769, 100_003])
+def test_in_place(n):
+    """A filter may write its kept keys over its keys, and 32-bit indices may
+    take the place of the keys they are computed from, at the sizes where one
+    launch does it all and around them, with a workspace and without."""
+    import ctypes
+    lib = P._lib.lib()
+    g = np.random.default_rng(n)
+    ints, f32 = W.int_keys(n, 41), W.f32_uniform(n, 42)
+    fl = (g.random(n) < 0.6).astype(np.uint8)
+    ft = torch.from_numpy(fl).to(DEV)
+    for x, gp, op in ((ints, P.Pred.mod_eq(3, 1), O.Pred.mod_eq(3, 1)), (f32, P.Pred.lt(0.7), O.Pred.lt(0.7)),
+                      (ints, P.Pred.from_flags(ft), O.Pred.from_flags(fl))):
+        src = torch.from_numpy(x).to(DEV)
+        for off in (0, 1):   # whole groups, and element loads
+            for rep in range(3):
+                print(f"[flat in place] n={n} pred={gp.kind} off={off} rep={rep}", flush=True)
+                ys, idx, t = O.partition2(x, op, 1)
+                buf = torch.empty(n + 1, dtype=src.dtype, device=DEV)[off:off + n]
+                for noalloc in (False, True):
+                    buf.copy_(src)
+                    if noalloc:
+                        oi = torch.empty(n, dtype=torch.int64, device=DEV)
+                        sp = torch.empty(1, dtype=torch.int64, device=DEV)
+                        pc = gp.c()
+                        assert lib.ixp_partition_noalloc(
+                            buf.data_ptr(), P._lib.I32 if x.dtype == np.int32 else P._lib.F32, n, ctypes.byref(pc),
+                            P.MODE_FILTER, buf.data_ptr(), oi.data_ptr(), P._lib.I64, sp.data_ptr(),
+                            torch.cuda.current_stream().cuda_stream) == 0
+                    else:
+                        _, oi, sp = P.partition(buf, gp, P.MODE_FILTER, out_keys=buf)
+                    assert int(sp.item()) == t and np.array_equal(oi.cpu().numpy(), idx)
+                    assert np.array_equal(buf.cpu().numpy()[:t].view(np.uint32), ys[:t].view(np.uint32))
+                for mode in (0, 1):
+                    ys, idx, t = O.partition2(x, op, mode)
+                    buf.copy_(src)
+                    ok, oi, sp = P.partition(buf, gp, mode, torch.int32, out_idx=buf.view(torch.int32))
+                    nout = n if mode == 0 else t
+                    assert int(sp.item()) == t and np.array_equal(oi.cpu().numpy(), idx)
+                    assert np.array_equal(ok.cpu().numpy()[:nout].view(np.uint32), ys[:nout].view(np.uint32))
