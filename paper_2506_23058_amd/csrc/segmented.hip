@@ -110,7 +110,7 @@ struct SegArgs {
     int64_t chunk_rows;   // rows per workgroup of seg_sizes / seg_rows / seg_records
     int64_t nchunks;
     int64_t *csum, *citems, *ccounted, *cbad;   // [kShapeChunks] of a chunk: elements, items, counted
-                                                // items, whether a size is negative
+                                                // items, whether a size is bad
 };
 
 constexpr int64_t kShapeFusedRows = 16384;   // up to here the shape takes one launch (seg_shape)
@@ -129,6 +129,13 @@ int64_t seg_max_items(int64_t n, int64_t m, int64_t tile, bool pack) {
     const int64_t bound = packed + (n + 3 * longs) / tile + longs + 2;
     return bound < plain ? bound : plain;
 }
+
+// A row's size as it is counted.  One outside [0, n] makes the shape invalid and
+// counts 0: then the offsets' and items' sums cannot wrap, and the records of an
+// invalid shape stay inside [0, max_items) (they are written before the last
+// chunk has found it invalid).
+__device__ __forceinline__ bool size_bad(const SegArgs &a, int64_t v) { return v < 0 || v > a.n; }
+__device__ __forceinline__ int64_t size_counted(const SegArgs &a, int64_t v) { return size_bad(a, v) ? 0 : v; }
 
 // The items a row begins: 0 for an empty row and for a short row that joins
 // the item of the row before it (`prev` elements, 0 if the block of rows
@@ -268,17 +275,17 @@ __global__ __launch_bounds__(kSetupThreads) void seg_sizes_kernel(SegArgs a) {
     if (threadIdx.x == 0) bad = 0;
     __syncthreads();
     int64_t sum = 0;
-    bool neg = false;
+    bool wrong = false;
     for (int64_t b = r0; b < r1; b += kSetupThreads * kSetupPer) {
 #pragma unroll
         for (int j = 0; j < kSetupPer; ++j) {
             const int64_t k = b + j * kSetupThreads + threadIdx.x;
             const int64_t v = k < r1 ? a.shape[k] : 0;
-            neg |= v < 0;
-            sum += v < 0 ? 0 : v;
+            wrong |= size_bad(a, v);
+            sum += size_counted(a, v);
         }
     }
-    if (ballot(neg) != 0 && (threadIdx.x & 63) == 0) atomicOr(&bad, 1);
+    if (ballot(wrong) != 0 && (threadIdx.x & 63) == 0) atomicOr(&bad, 1);
     sum = block_sum_of(sum, lds);
     if (threadIdx.x == 0) {
         a.csum[c] = sum;
@@ -308,7 +315,7 @@ __global__ __launch_bounds__(kSetupThreads) void seg_rows_kernel(SegArgs a) {
         for (int j = 0; j < kSetupPer; ++j) {
             const int64_t k = b + j * kSetupThreads + tid;
             const int64_t v = k < c1 ? a.shape[k] : 0;
-            sz[j * kSetupThreads + tid] = v < 0 ? 0 : v;
+            sz[j * kSetupThreads + tid] = size_counted(a, v);
         }
         __syncthreads();
         int64_t s[kSetupPer], sum_s = 0;
@@ -429,8 +436,7 @@ __global__ __launch_bounds__(kShapeThreads) void seg_shape_kernel(SegArgs a) {
         if (g == 0) *a.scan_ticket = 0;
     }
     __syncthreads();
-    // coalesced loads into LDS, all in flight at once; a negative size marks
-    // the shape bad and counts 0
+    // coalesced loads into LDS, all in flight at once
     {
         constexpr int kLoads = kShapeFusedRows / kShapeThreads;
         int64_t v[kLoads];
@@ -442,8 +448,8 @@ __global__ __launch_bounds__(kShapeThreads) void seg_shape_kernel(SegArgs a) {
 #pragma unroll
         for (int j = 0; j < kLoads; ++j) {
             const int64_t k = tid + static_cast<int64_t>(j) * kShapeThreads;
-            if (v[j] < 0) atomicOr(&bad, 1);
-            if (k < rend) sz[k] = v[j] < 0 ? 0 : v[j];
+            if (size_bad(a, v[j])) atomicOr(&bad, 1);
+            if (k < rend) sz[k] = size_counted(a, v[j]);
         }
     }
     __syncthreads();

@@ -457,3 +457,31 @@ def test_short_rows_around_2048_rows(m, monkeypatch):
     shape = np.random.default_rng(m).integers(0, 40, m)
     monkeypatch.setitem(globals(), "_short_shapes", lambda: {"rows": shape})
     test_short_rows_share_items("rows")
+
+
+@pytest.mark.parametrize("m", [300, 2100, 16_384, 16_385, 20_000])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_sizes_far_beyond_the_array_are_reported(m, mode):
+    """Shapes that hold anything (sizes up to 2^63 - 1, sums that wrap, even to n
+    itself): an error, no output, and the next call on the workspace is right."""
+    g = np.random.default_rng(m)
+    good = g.integers(0, 9, m)
+    n = int(good.sum())
+    wrap = good.copy()
+    wrap[:4] += 1 << 62   # adds 2^64
+    cases = {"2^62": np.full(m, 1 << 62), "anything": g.integers(-2**63, 2**63 - 1, m),
+             "greatest": np.full(m, 2**63 - 1), "greatest first": np.r_[2**63 - 1, good[1:]],
+             "greatest last": np.r_[good[:-1], 2**63 - 1], "wraps to n": wrap, "n each": np.full(m, n),
+             "n + 1": np.r_[good[:-1] * 0, n + 1]}
+    keys = torch.from_numpy(W.int_keys(n, 134)).to(DEV)
+    for name, bad in cases.items():
+        print(f"[seg] m={m} mode={mode} shape={name}", flush=True)
+        out = torch.full((n,), -5, dtype=torch.int32, device=DEV)
+        idx, seg = out.clone(), torch.full((m,), -5, dtype=torch.int64, device=DEV)
+        st = torch.from_numpy(bad.astype(np.int64)).to(DEV)
+        P.segmented_partition(keys, st, P.Pred.mod_eq(2, 0), mode, out_keys=out, out_idx=idx, seg_split=seg)
+        assert P.segmented_error() == P._lib.IXP_EINVAL
+        ii = P.mk_ii(st, n, torch.int32, out=torch.full((n,), -5, dtype=torch.int32, device=DEV))
+        assert P.shape_tools_error() == P._lib.IXP_EINVAL
+        assert all(bool((t == -5).all()) for t in (out, idx, seg, ii))
+    run_both(W.int_keys(n, 134), good, "mod", mode, d=2, r=0)
