@@ -130,3 +130,23 @@ def test_new_entry_points_validate_on_the_host():
     rc = lib.ixp_partition(None, L.F32, 0, ctypes.byref(p), 0, None, None, L.I64,
                            ctypes.addressof(split), ws, len(ws), None)
     assert rc == L.IXP_EINVAL
+
+
+def test_a_segmented_workspace_serves_smaller_calls():
+    """A workspace sized for the most elements and rows is large enough for every
+    call of fewer, also where those take an item per row and the largest does not."""
+    import random
+    import paper_2506_23058_amd._lib as L
+    lib = L.lib()
+    rng = random.Random(5)
+    edges = [1, 100, 2047, 2048, 2049, 16384, 16385, 41_667, 1 << 20]
+    tune = lib.ixp_segmented_workspace.argtypes[2]._type_()
+    tune.block, tune.rows = 512, 2
+    for t in (None, ctypes.byref(tune)):
+        for _ in range(4000):
+            m = rng.choice(edges) if rng.random() < 0.5 else int(2 ** rng.uniform(0, 22))
+            n = m * rng.choice([1, 32, 767, 768, 769, 1500]) if rng.random() < 0.5 else int(2 ** rng.uniform(0, 32))
+            m2 = min(m, rng.choice(edges) if rng.random() < 0.5 else rng.randint(0, m))
+            n2 = rng.choice([n, rng.randint(0, n), min(n, 768 * m2), min(n, 769 * m2)])
+            assert lib.ixp_segmented_workspace(n2, m2, t) <= lib.ixp_segmented_workspace(n, m, t), (n, m, n2, m2)
+            assert lib.ixp_mk_ii_workspace(n2, m2) <= lib.ixp_mk_ii_workspace(n, m), (n, m, n2, m2)
