@@ -1332,6 +1332,18 @@ int buckets_for(int64_t n, uint32_t mask, const ixp_prop_args *a) {
     return b <= kMaxBuckets ? static_cast<int>(b) : 0;
 }
 
+// Buckets that a workspace has room for: the most that any Rcd of no more values
+// takes (wider buckets may be fewer), so that one sized for the widest serves all.
+int buckets_room(int64_t n, uint32_t mask, const ixp_prop_args *a) {
+    if (!(mask & (IXP_INJ | IXP_BIJ)) || !a) return 0;
+    const int64_t w = a->hi - a->lo;
+    if (w > static_cast<int64_t>(kMaxBuckets) << kBucketShift) return 0;
+    ixp_prop_args narrow{};
+    narrow.hi = w < kBuckets << 5 ? w : kBuckets << 5;
+    const int at = buckets_for(n, mask, a), most = buckets_for(n, mask, &narrow);
+    return at > most ? at : most;
+}
+
 int64_t chunks_for(int64_t n) { return ceil_div(n, kChunk); }
 
 // Chunked path: the chunks' records and the bucket-start table.
@@ -1365,7 +1377,7 @@ extern "C" size_t ixp_check_props_workspace(int64_t n, uint32_t mask, const ixp_
     const size_t first_bytes = static_cast<size_t>(w) * (n >= (int64_t{1} << 32) ? 8 : 4);
     return kPropsHeader + 2 * round_up(words * 4, 256) + round_up(first_bytes, 256) +
            ((mask & IXP_FILTPART) ? kFpBytes : 0) + kRepBytes +
-           bucket_bytes(n, buckets_for(n, mask, a));
+           bucket_bytes(n, buckets_room(n, mask, a));
 }
 
 extern "C" int ixp_check_props(const void *x, int32_t x_t, int64_t n, uint32_t mask,

@@ -150,3 +150,24 @@ def test_a_segmented_workspace_serves_smaller_calls():
             n2 = rng.choice([n, rng.randint(0, n), min(n, 768 * m2), min(n, 769 * m2)])
             assert lib.ixp_segmented_workspace(n2, m2, t) <= lib.ixp_segmented_workspace(n, m, t), (n, m, n2, m2)
             assert lib.ixp_mk_ii_workspace(n2, m2) <= lib.ixp_mk_ii_workspace(n, m), (n, m, n2, m2)
+
+
+def test_a_check_workspace_serves_narrower_calls():
+    """A workspace of the checkers sized for the widest Rcd (up to 2^32 values)
+    is large enough for every narrower one."""
+    import random
+    import paper_2506_23058_amd._lib as L
+    lib = L.lib()
+    rng = random.Random(6)
+    a = lib.ixp_check_props_workspace.argtypes[2]._type_()
+
+    def room(n, w, mask):
+        a.lo, a.hi = -3, w - 3
+        return lib.ixp_check_props_workspace(n, mask, ctypes.byref(a))
+
+    for _ in range(6000):
+        w = (1 << rng.randint(0, 31)) + rng.randint(0, 2)
+        w2 = min(w, (1 << rng.randint(0, 31)) + rng.randint(0, 2)) if rng.random() < 0.7 else rng.randint(0, w)
+        n = int(2 ** rng.uniform(10, 33))
+        mask = rng.choice([L.INJ, L.BIJ, L.RANGE | L.INJ | L.BIJ, L.INJ | L.FILTPART])
+        assert room(n, w2, mask) <= room(n, w, mask), (n, w, w2, mask)
