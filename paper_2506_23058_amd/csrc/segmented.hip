@@ -1457,7 +1457,7 @@ int launch_all(const SegArgs &a, const Pred &p, const SegGeom &g, int mode, int 
 // predicate of the row / the helpers, an item per row against packed: 1000 rows
 // 23.5, 25.3, 25.2, 35.6 / 23.2, 25.6, 31.4, 37.6 us; 2000 rows 24.2, 30.7, 30.4,
 // 37.3 / 24.7, 26.0, 31.8, 39.1; 4000 rows 30.9, 38.9, 38.8, 41.9 / 25.3, 27.4,
-// 33.3, 41.6.
+// 33.3, 41.6.  (The tuning cache's key, _packs_short_rows in ops.py, follows this.)
 constexpr int64_t kPackMean = 768, kPackMinRows = 2048;
 bool packs(int64_t n, int64_t m, const SegGeom &g) {
     return g.block == kPackThreads && g.rows == kPackRows && m >= kPackMinRows && n / m <= kPackMean &&

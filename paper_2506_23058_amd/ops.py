@@ -677,18 +677,28 @@ def _tune_cache_path():
                           os.path.join(os.path.expanduser("~"), ".cache", "ixpart", "tune.json"))
 
 
+def _packs_short_rows(n: int, m: int) -> bool:
+    """Whether rows share work items under the default tile (kPackMinRows and
+    kPackMean of segmented.hip)."""
+    return m >= 2048 and n // m <= 768
+
+
 def autotuned_tiling(keys, shape, pred, mode=L.MODE_PARTITION, idx_dtype=torch.int32,
                      want_flags=True, reps: int = 5):
     """Tiling for a segmented call from the autotuner cache (a JSON file keyed
-    by GPU architecture, key dtype, mode, index dtype and the power-of-two bins
-    of n and m; path in $IXP_TUNE_CACHE), running the tuner on a miss."""
+    by GPU architecture, key dtype, mode, index dtype, the power-of-two bins of
+    n and m, and whether the default tile packs short rows; path in
+    $IXP_TUNE_CACHE), running the tuner on a miss."""
     import json
     import math
     import os
     arch = torch.cuda.get_device_properties(keys.device).gcnArchName.split(":")[0]
     n, m = keys.numel(), shape.numel()
-    key = "|".join(["tiling+rowsync", arch, str(keys.dtype), str(mode), str(idx_dtype), pred.kind.__str__(),
-                    f"n2^{int(math.log2(max(n, 1)))}", f"m2^{int(math.log2(max(m, 1)))}"])
+    # the first word names the algorithms that the times are of: entries of a library
+    # without packed rows ("tiling+rowsync") are not used
+    key = "|".join(["tiling+rowsync+packing", arch, str(keys.dtype), str(mode), str(idx_dtype), pred.kind.__str__(),
+                    f"n2^{int(math.log2(max(n, 1)))}", f"m2^{int(math.log2(max(m, 1)))}",
+                    "short" if _packs_short_rows(n, m) else "long"])
     path = _tune_cache_path()
     cache = {}
     if os.path.exists(path):
