@@ -596,15 +596,30 @@ class SmallestPairs:
         # the fused call where the library has it and the array is large enough to pay
         need = L.lib().ixp_smallest_pairs_workspace(m, self.n_verts) if m >= self.FUSED_MIN else 0
         self.fused = need > 0
+        self._flags = self._pos = None
         if not self.fused:
-            self.flags = torch.empty(m, dtype=torch.uint8, device=dev)
-            self.pos = torch.empty(m, dtype=torch.int64, device=dev)
-            self._pred = Pred.from_flags(self.flags).c()
+            self._flags = torch.empty(m, dtype=torch.uint8, device=dev)
+            self._pos = torch.empty(m, dtype=torch.int64, device=dev)
+            self._pred = Pred.from_flags(self._flags).c()
             need = L.lib().ixp_partition_workspace(m)
         self.es_out = torch.empty(m, dtype=torch.int64, device=dev)
         self.is_out = torch.empty(m, dtype=torch.int64, device=dev)
         self.split = torch.empty(1, dtype=torch.int64, device=dev)
         self.ws = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
+
+    @property
+    def flags(self) -> torch.Tensor:
+        """uint8 per entry: kept by the last run (the fused call holds no such
+        array: there it is computed from hist, es and is when asked for)."""
+        return match_min(self.hist[:self.n_verts], self.es, self.is_) if self.fused else self._flags
+
+    @property
+    def pos(self) -> torch.Tensor:
+        """Per entry its place among the kept ones, -1 if dropped (as ``flags``)."""
+        if not self.fused:
+            return self._pos
+        return partition(self.es.view(torch.int32)[:self.es.shape[0]], Pred.from_flags(self.flags), L.MODE_FILTER,
+                         want_keys=False)[1]
 
     def run(self):
         lib, m, st = L.lib(), self.es.shape[0], _stream_ptr(self.es.device)
@@ -615,13 +630,13 @@ class SmallestPairs:
             return self.es_out, self.is_out, self.split
         L.check(lib.ixp_hist_min(_ptr(self.hist), self.n_verts, self.n_es, _ptr(self.es), L.I64,
                                  _ptr(self.is_), m, st), "ixp_hist_min")
-        L.check(lib.ixp_match_min(_ptr(self.flags), _ptr(self.hist), self.n_verts, _ptr(self.es), L.I64,
+        L.check(lib.ixp_match_min(_ptr(self._flags), _ptr(self.hist), self.n_verts, _ptr(self.es), L.I64,
                                   _ptr(self.is_), m, st), "ixp_match_min")
         L.check(lib.ixp_partition(None, L.I32, m, ctypes.byref(self._pred), L.MODE_FILTER, None,
-                                  _ptr(self.pos), L.I64, _ptr(self.split), _ptr(self.ws), self.ws.numel(), st),
+                                  _ptr(self._pos), L.I64, _ptr(self.split), _ptr(self.ws), self.ws.numel(), st),
                 "ixp_partition")
         for src, dst in ((self.es, self.es_out), (self.is_, self.is_out)):
-            L.check(lib.ixp_scatter_inj(_ptr(dst), m, _ptr(self.pos), L.I64, _ptr(src), m, 8, st),
+            L.check(lib.ixp_scatter_inj(_ptr(dst), m, _ptr(self._pos), L.I64, _ptr(src), m, 8, st),
                     "ixp_scatter_inj")
         return self.es_out, self.is_out, self.split
 

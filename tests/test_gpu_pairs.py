@@ -96,3 +96,20 @@ def test_fused_pairs_positions_of_a_wave(k, monkeypatch):
     for c in (0, 1, 3, 15, 16, 255, 256):
         es[c * 16384:c * 16384 + k] = g.integers(0, 64, k)
     _fused(verts, m, es, g.permutation(m))
+
+
+def test_flags_and_positions_of_both_ways(monkeypatch):
+    """``flags`` and ``pos`` read the same after a fused run and a step by step one."""
+    g = np.random.default_rng(6)
+    m, verts = 50_001, 9000
+    es = torch.from_numpy(np.where(g.random(m) < 0.1, -3, g.integers(0, verts, m))).to(DEV)
+    is_ = torch.from_numpy(g.permutation(2 * m)[:m]).to(DEV)
+    step = P.SmallestPairs(verts, m, es, is_)
+    monkeypatch.setattr(P.SmallestPairs, "FUSED_MIN", 0)
+    fused = P.SmallestPairs(verts, m, es, is_)
+    assert fused.fused and not step.fused
+    step.run()
+    fused.run()
+    assert torch.equal(step.flags, fused.flags) and torch.equal(step.pos, fused.pos)
+    assert fused.flags.dtype == torch.uint8 and fused.pos.dtype == torch.int64
+    assert int(fused.flags.sum()) == int(fused.split) == int(step.split)
