@@ -339,3 +339,18 @@ def test_passes_of_the_last_kernel(n):
     for z, first in ((idx, [(1, -1, 0)] * 2), (x, v[2:4])):
         got = P.verdicts(P.check_props(torch.from_numpy(z).to(DEV), ALL4 | P.FILTPART, 0, n, 0, n, fp=fp))
         assert got[2:] == first + [O.check_filtpart(keys, op, 0, ys, z, t)]
+
+
+@pytest.mark.parametrize("w", [1, 31, 32, 33, 2049, 8192, 8193])
+def test_narrow_rcd(w):
+    """Rcd of few values and many entries (buckets of 32 values on): every value
+    repeated, most entries outside Rcd and the rest injective, one value repeated."""
+    g = np.random.default_rng(w)
+    n = 70_001
+    both(g.integers(0, w, n), ALL4, 0, w, 0, w)
+    x = g.integers(w, 2 * w + 1000, n)
+    x[g.permutation(n)[:w]] = g.permutation(w)
+    both(x, ALL4, 0, w, 0, w)                     # injective, every value attained
+    x[g.integers(0, n)] = 0
+    both(x - 7, ALL4, -7, w - 7, -7, w - 7)
+    both(np.full(n, w - 1), ALL4, 0, w, 0, w)
