@@ -422,7 +422,8 @@ __global__ __launch_bounds__(kShapeThreads) void seg_shape_kernel(SegArgs a) {
     __shared__ int64_t s_off[257], s_it[257];
     __shared__ int64_t sz[kShapeFusedRows];   // the sizes of rows [0, rend)
     __shared__ int bad;
-    const int tid = threadIdx.x;
+    __shared__ int wlast[kShapeThreads / kWave];   // 1 + a wave's last non-empty row
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = wave_id();
     const int64_t r0 = static_cast<int64_t>(blockIdx.x) * 256;
     const int64_t rend = a.m - r0 < 256 ? a.m : r0 + 256;   // rows [0, rend) are scanned
     const int nr = static_cast<int>(rend - r0);
@@ -457,19 +458,32 @@ __global__ __launch_bounds__(kShapeThreads) void seg_shape_kernel(SegArgs a) {
     const int per = static_cast<int>((rend + kShapeThreads - 1) / kShapeThreads);
     const int64_t k0 = static_cast<int64_t>(tid) * per;
     const int64_t k1 = k0 + per < rend ? k0 + per : rend;
+    const bool pack = a.short_max > 0;
     int64_t sum_s = 0;
-    for (int64_t k = k0; k < k1; ++k) sum_s += sz[k];
+    int filled = 0;   // 1 + this thread's last non-empty row, then 1 + the last one before its rows
+    for (int64_t k = k0; k < k1; ++k) {
+        sum_s += sz[k];
+        if (sz[k] > 0) filled = static_cast<int>(k) + 1;
+    }
+    if (pack) {
+        // the nearest one of the lanes below, then of the waves before; looking for it
+        // row by row took 15 us where 1 row in 97 is not empty
+        const uint64_t under = ballot(filled != 0) & ((1ull << lane) - 1);
+        const int at = __shfl(filled, under ? 63 - __builtin_clzll(under) : 0, kWave);
+        const int before = under ? at : 0;
+        if (lane == kWave - 1) wlast[wave] = filled ? filled : before;
+        filled = before;
+    }
     int64_t tot_s;
-    const int64_t off0 = block_exclusive_scan<16>(sum_s, lds_a, &tot_s);
+    const int64_t off0 = block_exclusive_scan<16>(sum_s, lds_a, &tot_s);   // (its barriers publish wlast)
+    if (pack)
+        for (int w = 0; w < wave; ++w) filled = wlast[w] > filled ? wlast[w] : filled;
     // calls row(k, o, items) for this thread's rows; the packed form keeps the
     // last non-empty size before a row in its block of rows
-    const bool pack = a.short_max > 0;
     auto rows = [&](auto packed, auto &&row) {
         constexpr bool kPack = decltype(packed)::value;
         constexpr int64_t kBlock = int64_t{1} << kFusedPackShift;
-        int64_t o = off0, prev = 0;
-        if (kPack)
-            for (int64_t k = k0 - 1; k >= (k0 & ~(kBlock - 1)) && k < rend && prev == 0; --k) prev = sz[k];
+        int64_t o = off0, prev = kPack && filled > (k0 & ~(kBlock - 1)) ? sz[filled - 1] : 0;
         for (int64_t k = k0; k < k1; ++k) {
             const int64_t sk = sz[k];
             if (kPack) {

@@ -485,3 +485,15 @@ def test_sizes_far_beyond_the_array_are_reported(m, mode):
         assert P.shape_tools_error() == P._lib.IXP_EINVAL
         assert all(bool((t == -5).all()) for t in (out, idx, seg, ii))
     run_both(W.int_keys(n, 134), good, "mod", mode, d=2, r=0)
+
+
+@pytest.mark.parametrize("m", [2048, 5003, 16_384])
+@pytest.mark.parametrize("gap", [3, 97, 255, 256, 257, 700])
+def test_short_rows_far_apart(m, gap, monkeypatch):
+    """The row before a row in its block of 256 may lie any number of empty rows
+    back: in the thread's own rows, another lane's, another wave's, or in no one's."""
+    g = np.random.default_rng(m + gap)
+    shape = np.zeros(m, np.int64)
+    shape[gap - 1::gap] = g.integers(1, 1025, len(shape[gap - 1::gap]))
+    monkeypatch.setitem(globals(), "_short_shapes", lambda: {"rows": shape})
+    test_short_rows_share_items("rows")
