@@ -235,9 +235,11 @@ __device__ __forceinline__ void write_item(const SegArgs &a, int64_t idx, const 
     SegItem d;
     d.fbase = 0;
     d.row = static_cast<int32_t>(r0 + j);
-    if (e - o <= a.short_max) {
-        // up to the row that begins the next item, or the end of the block
-        if (idx + 1 >= s_it[nr]) j1 = nr;
+    // a short row's item reaches up to the row that begins the next item, or to the
+    // end of the block; one that holds no other row's elements is an ordinary item
+    // (rows of 1100 and 300 in turn, a filter by a row predicate: 187 -> 150 us)
+    if (idx + 1 >= s_it[nr]) j1 = nr;
+    if (e - o <= a.short_max && s_off[j1] > e) {
         d.lo = o;
         d.hi = s_off[j1];
         d.base = o & ~int64_t{31};
@@ -1462,10 +1464,15 @@ int launch_all(const SegArgs &a, const Pred &p, const SegGeom &g, int mode, int 
 
 // Short rows are packed when rows have at most kPackMean elements on average
 // (the sizes themselves are known on the device only) and the tile is the
-// default one.  2^25 int32 keys in log-normal rows, a partition with an item per
-// row / with packed items, by the rows' mean size: 16: 5165 / 172 us, 128: 750 /
-// 145, 512: 251 / 173, 1024: 171 / 170, 2048: 121 / 144 (a packed item costs
-// more per element, and rows above 1024 elements cut the packed ones short).
+// default one.  A packed item costs more per element than a row of its own, rows
+// above 1024 elements cut the packed items short, and the kernel that knows packed
+// items runs fewer waves (a partition of long rows alone: 1.1 to 1.2 of the other
+// one's time).  16,000 rows, item per row / packed, us, by the rows' mean: partition of
+// log-normal sizes 256: 79 / 50, 512: 85 / 68, 768: 92 / 84, 1100: 99 / 100; of equal ones
+// 512: 78 / 57, 768: 84 / 68; of uniform ones from 0 512: 84 / 57, 640: 88 / 81, 768: 90 / 92, 1100:
+// 96 / 105; 60,000 rows, uniform 768: 245 / 243.  So the line is where uniform sizes break
+// even; rows that are either 1100 or below 60 elements do at 448 (16,000 rows 640: 89 / 100,
+// 768: 92 / 106), the worst there is.
 // Below kPackMinRows rows a workgroup per row fills the chip in a wave or two, and a
 // few packed items leave it idle.  Rows of 128, partition / filter / filter by a
 // predicate of the row / the helpers, an item per row against packed: 1000 rows

@@ -497,3 +497,33 @@ def test_short_rows_far_apart(m, gap, monkeypatch):
     shape[gap - 1::gap] = g.integers(1, 1025, len(shape[gap - 1::gap]))
     monkeypatch.setitem(globals(), "_short_shapes", lambda: {"rows": shape})
     test_short_rows_share_items("rows")
+
+
+@pytest.mark.parametrize("m", [2048, 5003, 16_385])
+@pytest.mark.parametrize("extra", [-1, 0, 1])
+def test_mean_at_the_packing_rule(m, extra, monkeypatch):
+    """Rows of 1, 1024 and 1025 elements whose mean is the greatest that shares
+    items, that mean with the greatest remainder, and the next one."""
+    g = np.random.default_rng(m)
+    shape = g.choice([1, 1024, 1025], m, p=[0.28, 0.36, 0.36]).astype(np.int64)
+    target = 768 * m + (0, m - 1, m)[extra + 1]
+    shape[m // 2] += target - shape.sum()
+    assert shape.min() > 0 and shape.sum() // m == 768 + (extra == 1)
+    monkeypatch.setitem(globals(), "_short_shapes", lambda: {"rows": shape})
+    test_short_rows_share_items("rows")
+
+
+@pytest.mark.parametrize("m", [2048, 16_384, 16_385])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_invalid_shape_that_asks_for_more_items_than_fit(m, mode):
+    """Short rows by n and m, but rows past the limit of 1024 in the shape: an item
+    each, many more than the records of a packed call."""
+    n = 32 * m
+    keys = torch.from_numpy(W.int_keys(n, 135)).to(DEV)
+    for size in (1025, 1024, 5000):
+        out = torch.full((n,), -5, dtype=torch.int32, device=DEV)
+        idx, seg = out.clone(), torch.full((m,), -5, dtype=torch.int64, device=DEV)
+        st = torch.full((m,), size, dtype=torch.int64, device=DEV)
+        P.segmented_partition(keys, st, P.Pred.mod_eq(2, 0), mode, out_keys=out, out_idx=idx, seg_split=seg)
+        assert P.segmented_error() == P._lib.IXP_EINVAL
+        assert all(bool((t == -5).all()) for t in (out, idx, seg))
