@@ -1288,20 +1288,22 @@ __device__ __forceinline__ void fill_packed(const SegArgs &a, const SegItem &d, 
     __syncthreads();   // the LDS is the next item's
 }
 
-template <int TOOL, class Out>
+template <int TOOL, class Out, bool PACK>
 __global__ __launch_bounds__(256) void seg_fill_kernel(SegArgs a, Out *out, const int64_t *xs) {
     constexpr int kV = 16 / sizeof(Out);   // elements per 16-byte group
     typedef Out vec_t __attribute__((ext_vector_type(kV)));
-    __shared__ PackLds pk;
-    __shared__ uint32_t val[kPackTile];
     if (*a.err != 0) return;
     const int64_t nitems = *a.num_items;
     const bool vec_ok = (reinterpret_cast<uintptr_t>(out) & 15) == 0;
     for (int64_t it = blockIdx.x; it < nitems; it += gridDim.x) {
         const SegItem d = a.items[it];
-        if (d.kind & kPacked) {
-            fill_packed<TOOL, Out>(a, d, out, xs, vec_ok, pk, val);
-            continue;
+        if constexpr (PACK) {
+            if (d.kind & kPacked) {
+                __shared__ PackLds pk;
+                __shared__ uint32_t val[kPackTile];
+                fill_packed<TOOL, Out>(a, d, out, xs, vec_ok, pk, val);
+                continue;
+            }
         }
         const bool first = (d.kind & 2) != 0;
         const Out fill = TOOL == 0 ? static_cast<Out>(d.row) : static_cast<Out>(0);
@@ -1348,14 +1350,21 @@ int launch_tool(const SegArgs &a, Out *out, const int64_t *xs, hipStream_t st) {
     if (launch_shape(a, st) != IXP_OK) return IXP_EHIP;
     const int64_t cap = static_cast<int64_t>(device_cus()) * 16;
     const int64_t grid = a.max_items < cap ? (a.max_items > 0 ? a.max_items : 1) : cap;
-    IXP_LAUNCH(TOOL == 0 ? "seg_mk_ii" : "seg_mk_sgm_descr", (seg_fill_kernel<TOOL, Out>),
-               dim3(static_cast<uint32_t>(grid)), dim3(256), 0, st, a, out, xs);
+    const char *name = TOOL == 0 ? "seg_mk_ii" : "seg_mk_sgm_descr";
+    if (a.short_max > 0)
+        IXP_LAUNCH(name, (seg_fill_kernel<TOOL, Out, true>), dim3(static_cast<uint32_t>(grid)), dim3(256), 0, st, a, out,
+                   xs);
+    else
+        IXP_LAUNCH(name, (seg_fill_kernel<TOOL, Out, false>), dim3(static_cast<uint32_t>(grid)), dim3(256), 0, st, a, out,
+                   xs);
     return launch_status();
 }
 
 // ----------------------------------------------------------------- launch --
+constexpr int64_t kPackMinRows = 2048, kToolPackMinRows = 8192;   // (see packs)
 struct SegGeom {
     int block, rows, wgs_per_cu, row_sync;
+    int64_t pack_rows = kPackMinRows;
     int64_t tile() const { return static_cast<int64_t>(block) * rows * 4; }
 };
 
@@ -1388,6 +1397,13 @@ SegGeom geom_from(const ixp_tuning *t) {
     // the in-kernel count exchange pays when a row's items run at the same
     // time, i.e. on oversubscribed grids that the hardware fills in order
     if (g.row_sync == IXP_ROW_SYNC_AUTO) g.row_sync = g.wgs_per_cu >= 16 ? IXP_ROW_SYNC_WAIT : IXP_ROW_SYNC_COUNT;
+    return g;
+}
+
+// Of the segment helpers.
+SegGeom tool_geom() {
+    SegGeom g = geom_from(nullptr);
+    g.pack_rows = kToolPackMinRows;
     return g;
 }
 
@@ -1478,21 +1494,23 @@ int launch_all(const SegArgs &a, const Pred &p, const SegGeom &g, int mode, int 
 // predicate of the row / the helpers, an item per row against packed: 1000 rows
 // 23.5, 25.3, 25.2, 35.6 / 23.2, 25.6, 31.4, 37.6 us; 2000 rows 24.2, 30.7, 30.4,
 // 37.3 / 24.7, 26.0, 31.8, 39.1; 4000 rows 30.9, 38.9, 38.8, 41.9 / 25.3, 27.4,
-// 33.3, 41.6.  (The tuning cache's key, _packs_short_rows in ops.py, follows this.)
-constexpr int64_t kPackMean = 768, kPackMinRows = 2048;
+// 33.3, 41.6.  The helpers alone, which only write, gain later (the
+// descriptor, rows of 32: 4000 rows 14.7 / 15.5, 8192 rows 19.8 / 18.0, 16,000 rows 30.7 / 25.2).
+// (The tuning cache's key, _packs_short_rows in ops.py, follows this.)
+constexpr int64_t kPackMean = 768;
 bool packs(int64_t n, int64_t m, const SegGeom &g) {
-    return g.block == kPackThreads && g.rows == kPackRows && m >= kPackMinRows && n / m <= kPackMean &&
+    return g.block == kPackThreads && g.rows == kPackRows && m >= g.pack_rows && n / m <= kPackMean &&
            n < (int64_t{1} << 42);
 }
 
 // Enough for every call of no more elements and no more rows as well: some of
-// those have an item per row (fewer than kPackMinRows rows, or a mean above
+// those have an item per row (fewer than pack_rows rows, or a mean above
 // kPackMean) and so more records than a packed call of more rows.
 size_t seg_workspace(int64_t n, int64_t m, const SegGeom &g) {
     const bool pack = packs(n, m, g);
     int64_t mi = seg_max_items(n, m, g.tile(), pack);
     if (pack) {
-        const int64_t rows = kPackMinRows - 1 > n / (kPackMean + 1) ? kPackMinRows - 1 : n / (kPackMean + 1);
+        const int64_t rows = g.pack_rows - 1 > n / (kPackMean + 1) ? g.pack_rows - 1 : n / (kPackMean + 1);
         const int64_t apart = seg_max_items(n, rows < m ? rows : m, g.tile(), false);
         if (apart > mi) mi = apart;
     }
@@ -1754,14 +1772,14 @@ extern "C" int ixp_graph_destroy(ixp_graph g) {
 
 extern "C" size_t ixp_mk_ii_workspace(int64_t n, int64_t m) {
     if (n < 0 || m < 0) return 0;
-    return seg_workspace(n, m, geom_from(nullptr));
+    return seg_workspace(n, m, tool_geom());
 }
 
 extern "C" int ixp_mk_ii(const int64_t *d_shape, int64_t m, int64_t n, void *out, int32_t out_t, void *ws,
                          size_t ws_bytes, void *stream) {
     if (n < 0 || m < 0 || m > 0x7FFFFFFFll || (m > 0 && !d_shape) || (n > 0 && !out)) return IXP_EINVAL;
     if (out_t != IXP_I32 && out_t != IXP_I64) return IXP_EINVAL;
-    const SegGeom g = geom_from(nullptr);
+    const SegGeom g = tool_geom();
     if (!ws || ws_bytes < seg_workspace(n, m, g)) return IXP_EWORKSPACE;
     if (!aligned(d_shape, 8) || !aligned(out, out_t == IXP_I32 ? 4 : 8) || !aligned(ws, 16)) return IXP_EINVAL;
     SegArgs a;
@@ -1775,7 +1793,7 @@ extern "C" int ixp_mk_sgm_descr(const int64_t *d_shape, int64_t m, int64_t n, co
                                 int64_t *d_out, void *ws, size_t ws_bytes, void *stream) {
     if (n < 0 || m < 0 || m > 0x7FFFFFFFll || (m > 0 && (!d_shape || !d_xs)) || (n > 0 && !d_out))
         return IXP_EINVAL;
-    const SegGeom g = geom_from(nullptr);
+    const SegGeom g = tool_geom();
     if (!ws || ws_bytes < seg_workspace(n, m, g)) return IXP_EWORKSPACE;
     if (!aligned(d_shape, 8) || !aligned(d_xs, 8) || !aligned(d_out, 8) || !aligned(ws, 16)) return IXP_EINVAL;
     SegArgs a;

@@ -139,7 +139,7 @@ def test_a_segmented_workspace_serves_smaller_calls():
     import paper_2506_23058_amd._lib as L
     lib = L.lib()
     rng = random.Random(5)
-    edges = [1, 100, 2047, 2048, 2049, 16384, 16385, 41_667, 1 << 20]
+    edges = [1, 100, 2047, 2048, 2049, 8191, 8192, 16384, 16385, 41_667, 1 << 20]
     tune = lib.ixp_segmented_workspace.argtypes[2]._type_()
     tune.block, tune.rows = 512, 2
     for t in (None, ctypes.byref(tune)):
