@@ -1146,19 +1146,64 @@ __global__ __launch_bounds__(kFpThreads) void fp_check_kernel(PropsArgs a, Pred 
     }
 }
 
+// OR of a 32-bit value over the 64 lanes, wave-uniform (as wave_sum_u32).
+__device__ __forceinline__ uint32_t wave_or_u32(uint32_t v) {
+    v |= dpp_row_ror<8>(v);
+    v |= dpp_row_ror<4>(v);
+    v |= dpp_row_ror<2>(v);
+    v |= dpp_row_ror<1>(v);
+    const int iv = static_cast<int>(v);
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(iv, 0) | __builtin_amdgcn_readlane(iv, 16) |
+                                 __builtin_amdgcn_readlane(iv, 32) | __builtin_amdgcn_readlane(iv, 48));
+}
+
 // After a failed class order or stability check, repeats are possible: the
-// bitmap insertions of the elements that take part in the bijection.
+// bitmap insertions of the elements that take part in the bijection.  Bound by
+// the atomics, which queue at a word: 64 elements of a nearly right partition lie
+// in a few words (each class's indices count on), so the lanes of a word make one
+// atomic for up to kFpWords words, and one each beyond.  (The whole check of 4 10^7 int32
+// entries rolled by one / with one repeat: an atomic per element 3240 / 3090 us, so 660 /
+// 565; inside fp_check, as it once was, 2420 / 2550.)
+constexpr int kFpWords = 6;
+
 template <class Pred>
 __global__ __launch_bounds__(kPropsBlock) void fp_insert_kernel(PropsArgs a, Pred pred) {
     if (!(a.st->fp_bits & 12u)) return;
+    const int lane = threadIdx.x & (kWave - 1);
     const int64_t split = *a.fp_split;
     bool dup_seen = false;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < a.n; i += stride) {
-        const FpElem e = fp_elem(a, pred, i);
-        if (fp_inserts(a, e, split)) insert_value<false>(a, e.z, &dup_seen);
+    for (int64_t i0 = static_cast<int64_t>(blockIdx.x) * blockDim.x + wave_id() * kWave; i0 < a.n; i0 += stride) {
+        FpElem e{false, false, 0, 0};
+        bool ins = false;
+        if (i0 + lane < a.n) {
+            e = fp_elem(a, pred, i0 + lane);
+            ins = fp_inserts(a, e, split);   // (then 0 <= z < n, and lo is 0)
+        }
+        const uint32_t word = static_cast<uint32_t>(e.z >> 5), bit = 1u << (e.z & 31);
+        uint64_t left = ballot(ins);
+        for (int k = 0; k < kFpWords && left; ++k) {
+            const int lead = __builtin_ctzll(left);
+            const uint32_t w = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(word), lead));
+            const bool mine = ins && word == w;
+            const uint64_t m = ballot(mine);
+            const uint32_t bits = wave_or_u32(mine ? bit : 0u);
+            left &= ~m;
+            if (__builtin_popcount(bits) != __builtin_popcountll(m)) {   // repeats among these lanes
+                if (mine) insert_value<false>(a, e.z, &dup_seen);
+                continue;
+            }
+            uint32_t old = 0;
+            if (lane == lead) old = atomicOr(a.seen + w, bits);
+            old = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(old), lead));
+            if (mine && (old & bit)) {
+                note_repeat(a, static_cast<uint64_t>(e.z), false);
+                dup_seen = true;
+            }
+        }
+        if ((left >> lane) & 1u) insert_value<false>(a, e.z, &dup_seen);
     }
-    if (ballot(dup_seen) != 0 && (threadIdx.x & 63) == 0) atomicOr(&a.st->dup_found, 1u);
+    if (ballot(dup_seen) != 0 && lane == 0) atomicOr(&a.st->dup_found, 1u);
 }
 
 // FiltPart's repeats, among the values fp_insert inserted: pass 0 takes the least

@@ -354,3 +354,22 @@ def test_narrow_rcd(w):
     x[g.integers(0, n)] = 0
     both(x - 7, ALL4, -7, w - 7, -7, w - 7)
     both(np.full(n, w - 1), ALL4, 0, w, 0, w)
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("n", [2, 64, 70_001])
+def test_filtpart_repeats_of_a_wave(n, mode):
+    """Broken orders, whose indices go to a bitmap, the lanes of one word together:
+    repeats of neighbouring lanes, of a whole wave, of the far end, more words than
+    a wave combines, and indices outside the outputs."""
+    g = np.random.default_rng(n)
+    keys = W.int_keys(n, 96)
+    op, gp = O.Pred.mod_eq(2, 0), P.Pred.mod_eq(2, 0)
+    ys, idx, t = O.partition2(keys, op, mode)
+    rolled, swapped, pairs, far = np.roll(idx, 1), idx[::-1].copy(), np.roll(idx, 1), np.roll(idx, 1)
+    pairs[1::2] = pairs[:-1:2][:len(pairs[1::2])]
+    far[-1] = far[0]
+    wide = np.concatenate([np.roll(idx, 1)[:n // 2], g.integers(-n, 2 * n, n - n // 2)])
+    for z in (rolled, swapped, pairs, far, wide, np.full(n, idx[0]), g.permutation(n), g.integers(0, n, n), idx ^ 1):
+        for dt in (np.int32, np.int64):
+            _fp_both(keys, op, gp, mode, ys, z, t, dt)
