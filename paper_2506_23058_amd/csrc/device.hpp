@@ -73,11 +73,10 @@ __device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
     return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROWS, 0xF, false));
 }
 template <int CTRL, int ROWS>
-__device__ __forceinline__ int64_t dpp_i64(int64_t v) {
-    const uint64_t u = static_cast<uint64_t>(v);
-    const uint32_t lo = dpp_u32<CTRL, ROWS>(static_cast<uint32_t>(u));
-    const uint32_t hi = dpp_u32<CTRL, ROWS>(static_cast<uint32_t>(u >> 32));
-    return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t v) {
+    const uint32_t lo = dpp_u32<CTRL, ROWS>(static_cast<uint32_t>(v));
+    const uint32_t hi = dpp_u32<CTRL, ROWS>(static_cast<uint32_t>(v >> 32));
+    return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
     v += dpp_u32<0x111, 0xF>(v);
@@ -88,23 +87,27 @@ __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
     v += dpp_u32<0x143, 0xC>(v);
     return v;
 }
-__device__ __forceinline__ int64_t wave_scan_i64(int64_t v) {
-    v += dpp_i64<0x111, 0xF>(v);
-    v += dpp_i64<0x112, 0xF>(v);
-    v += dpp_i64<0x114, 0xF>(v);
-    v += dpp_i64<0x118, 0xF>(v);
-    v += dpp_i64<0x142, 0xA>(v);
-    v += dpp_i64<0x143, 0xC>(v);
+// (Unsigned, so that sums which wrap, as prefix sums of any int64 values may, are defined.)
+__device__ __forceinline__ uint64_t wave_scan_u64(uint64_t v) {
+    v += dpp_u64<0x111, 0xF>(v);
+    v += dpp_u64<0x112, 0xF>(v);
+    v += dpp_u64<0x114, 0xF>(v);
+    v += dpp_u64<0x118, 0xF>(v);
+    v += dpp_u64<0x142, 0xA>(v);
+    v += dpp_u64<0x143, 0xC>(v);
     return v;
+}
+__device__ __forceinline__ int64_t wave_scan_i64(int64_t v) {
+    return static_cast<int64_t>(wave_scan_u64(static_cast<uint64_t>(v)));
 }
 
 // op over a 64-bit value of the 64 lanes, returned wave-uniform (as wave_sum_u32).
 template <class Op>
 __device__ __forceinline__ uint64_t wave_reduce_u64(uint64_t v, const Op &op) {
-    v = op(v, static_cast<uint64_t>(dpp_i64<0x128, 0xF>(static_cast<int64_t>(v))));
-    v = op(v, static_cast<uint64_t>(dpp_i64<0x124, 0xF>(static_cast<int64_t>(v))));
-    v = op(v, static_cast<uint64_t>(dpp_i64<0x122, 0xF>(static_cast<int64_t>(v))));
-    v = op(v, static_cast<uint64_t>(dpp_i64<0x121, 0xF>(static_cast<int64_t>(v))));
+    v = op(v, dpp_u64<0x128, 0xF>(v));
+    v = op(v, dpp_u64<0x124, 0xF>(v));
+    v = op(v, dpp_u64<0x122, 0xF>(v));
+    v = op(v, dpp_u64<0x121, 0xF>(v));
     return op(op(readlane_u64(v, 0), readlane_u64(v, 16)), op(readlane_u64(v, 32), readlane_u64(v, 48)));
 }
 

@@ -24,21 +24,23 @@ namespace {
 constexpr int64_t kSgTile = 8192;      // chunks are multiples of this
 constexpr int64_t kSgMaxChunks = 8192;
 
+// The values are summed as unsigned words: the plain prefix sums used below pass
+// segment borders and may wrap where no segment's sum does.
 struct Pair {
     bool f;
-    int64_t v;
+    uint64_t v;
 };
 
 __device__ __forceinline__ Pair combine(Pair x, Pair y) { return Pair{x.f || y.f, y.f ? y.v : x.v + y.v}; }
 
 struct SgArgs {
     const uint8_t *flags;
-    const int64_t *xs;
-    int64_t *out;
+    const uint64_t *xs;
+    uint64_t *out;
     int64_t n;
     int64_t chunk;      // elements per chunk, a multiple of kSgTile
     int64_t chunks;
-    int64_t *agg_v;     // [chunks] aggregate value, then exclusive prefix value
+    uint64_t *agg_v;    // [chunks] aggregate value, then exclusive prefix value
     int32_t *agg_f;     // [chunks] aggregate flag
 };
 
@@ -72,6 +74,7 @@ __global__ __launch_bounds__(kRedThreads) void sg_reduce_kernel(SgArgs a) {
     constexpr int kLoads = kSgTile / (8 * kRedThreads);   // flag groups of a tile per thread
     constexpr int kVals = 8;                              // values in flight per thread
     __shared__ int64_t lds[kRedThreads / kWave];
+    __shared__ uint64_t sums[kRedThreads / kWave];
     const int tid = threadIdx.x;
     const int64_t c = blockIdx.x;
     const int64_t lo = c * a.chunk;
@@ -95,20 +98,20 @@ __global__ __launch_bounds__(kRedThreads) void sg_reduce_kernel(SgArgs a) {
     last = block_max(last, lds);
     // a flagged element restarts the sum with its own value
     const int64_t start = last >= lo ? last : lo;
-    int64_t s = 0;
+    uint64_t s = 0;
     for (int64_t p = start + tid; p < hi; p += kVals * kRedThreads) {
-        int64_t v[kVals];
+        uint64_t v[kVals];
 #pragma unroll
         for (int j = 0; j < kVals; ++j) v[j] = p + j * kRedThreads < hi ? a.xs[p + j * kRedThreads] : 0;
 #pragma unroll
         for (int j = 0; j < kVals; ++j) s += v[j];
     }
-    s = wave_sum_i64(s);
-    if ((tid & 63) == 0) lds[tid >> 6] = s;
+    s = wave_reduce_u64(s, [](uint64_t x, uint64_t y) { return x + y; });
+    if ((tid & 63) == 0) sums[tid >> 6] = s;
     __syncthreads();
     if (tid == 0) {
         s = 0;
-        for (int w = 0; w < kRedThreads / kWave; ++w) s += lds[w];
+        for (int w = 0; w < kRedThreads / kWave; ++w) s += sums[w];
         a.agg_v[c] = s;
         a.agg_f[c] = last >= lo ? 1 : 0;
     }
@@ -118,7 +121,7 @@ __global__ __launch_bounds__(kRedThreads) void sg_reduce_kernel(SgArgs a) {
 __global__ __launch_bounds__(1024) void sg_chunk_scan_kernel(SgArgs a) {
     constexpr int kPer = 8;
     static_assert(kPer * 1024 >= kSgMaxChunks, "scan capacity");
-    __shared__ int64_t wv[16];
+    __shared__ uint64_t wv[16];
     __shared__ int32_t wf[16];
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
     Pair e[kPer];
@@ -132,9 +135,9 @@ __global__ __launch_bounds__(1024) void sg_chunk_scan_kernel(SgArgs a) {
     // the sums wrap, so the sum since the last flag is a difference of plain
     // prefix sums, as in the rescan
     const uint64_t flagged = ballot(run.f);
-    const int64_t inc = wave_scan_i64(run.v), ex = inc - run.v;
+    const uint64_t inc = wave_scan_u64(run.v), ex = inc - run.v;
     const uint64_t below = flagged & ((1ull << lane) - 1);
-    const int64_t from = __shfl(ex, below ? 63 - __builtin_clzll(below) : 0, kWave);
+    const uint64_t from = __shfl(ex, below ? 63 - __builtin_clzll(below) : 0, kWave);
     const Pair before{below != 0, ex - from};
     if (lane == kWave - 1) {
         const Pair all = combine(before, run);
@@ -170,14 +173,14 @@ static_assert(kSgTile % kScStep == 0, "whole steps");
 
 __global__ __launch_bounds__(kScThreads) void sg_rescan_kernel(SgArgs a) {
     constexpr int kWaves = kScThreads / kWave;
-    typedef int64_t i64x2 __attribute__((ext_vector_type(2)));
-    __shared__ int64_t wv[2][kWaves];   // by parity of the step
+    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+    __shared__ uint64_t wv[2][kWaves];   // by parity of the step
     __shared__ int32_t wf[2][kWaves];
     const int lane = threadIdx.x & (kWave - 1), wave = wave_id();
     const int64_t c = blockIdx.x;
     const int64_t lo_c = c * a.chunk;
     const int64_t hi_c = lo_c + a.chunk < a.n ? lo_c + a.chunk : a.n;
-    int64_t carry = a.agg_v[c];   // running sum before the chunk (a flag inside the chunk resets it)
+    uint64_t carry = a.agg_v[c];   // running sum before the chunk (a flag inside the chunk resets it)
     const bool fvec = (reinterpret_cast<uintptr_t>(a.flags) & 1) == 0;
     const bool xvec = (reinterpret_cast<uintptr_t>(a.xs) & 15) == 0;
     const bool ovec = (reinterpret_cast<uintptr_t>(a.out) & 15) == 0;
@@ -185,12 +188,12 @@ __global__ __launch_bounds__(kScThreads) void sg_rescan_kernel(SgArgs a) {
     for (int64_t lo = lo_c; lo < hi_c; lo += kScStep, par ^= 1) {
         const int64_t e0 = lo + wave * kScWave + 2 * lane;
         const bool whole = lo + (wave + 1) * kScWave <= hi_c;   // (wave-uniform)
-        int64_t v[kScRows][2];
+        uint64_t v[kScRows][2];
         uint32_t fl[kScRows];   // the pair's flags: nonzero low byte, nonzero second byte
         if (whole && xvec && fvec) {
 #pragma unroll
             for (int r = 0; r < kScRows; ++r) {
-                const i64x2 x = __builtin_nontemporal_load(reinterpret_cast<const i64x2 *>(a.xs + e0 + r * 2 * kWave));
+                const u64x2 x = __builtin_nontemporal_load(reinterpret_cast<const u64x2 *>(a.xs + e0 + r * 2 * kWave));
                 fl[r] = __builtin_nontemporal_load(reinterpret_cast<const uint16_t *>(a.flags + e0 + r * 2 * kWave));
                 v[r][0] = x.x;
                 v[r][1] = x.y;
@@ -207,26 +210,25 @@ __global__ __launch_bounds__(kScThreads) void sg_rescan_kernel(SgArgs a) {
         // run: running sum before the row, from the wave's start; seen: some
         // flag before the row; open: bit r*2+q, the element adds what comes
         // before the wave
-        int64_t run = 0;
+        uint64_t run = 0;
         bool seen = false;
         uint32_t open = 0;
 #pragma unroll
         for (int r = 0; r < kScRows; ++r) {
             const bool f0 = (fl[r] & 0xFFu) != 0, f1 = (fl[r] >> 8) != 0;
-            const int64_t inc = wave_scan_i64(v[r][0] + v[r][1]);
-            const int64_t excl = inc - v[r][0] - v[r][1];
-            const int64_t total = static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(inc), kWave - 1));
+            const uint64_t inc = wave_scan_u64(v[r][0] + v[r][1]);
+            const uint64_t excl = inc - v[r][0] - v[r][1];
+            const uint64_t total = readlane_u64(inc, kWave - 1);
             const uint64_t m = ballot(f0 | f1);
-            const int64_t at = f1 ? excl + v[r][0] : excl;   // prefix before this lane's last flag
+            const uint64_t at = f1 ? excl + v[r][0] : excl;   // prefix before this lane's last flag
             const uint64_t below = m & ((1ull << lane) - 1);
-            const int64_t from = __shfl(at, below ? 63 - __builtin_clzll(below) : 0, kWave);
-            const int64_t x0 = f0 ? v[r][0] : v[r][0] + excl + (below ? -from : run);
+            const uint64_t from = __shfl(at, below ? 63 - __builtin_clzll(below) : 0, kWave);
+            const uint64_t x0 = f0 ? v[r][0] : v[r][0] + excl + (below ? -from : run);
             const bool o0 = !(f0 | seen | (below != 0));
             open |= (static_cast<uint32_t>(o0) | static_cast<uint32_t>(o0 & !f1) << 1) << (2 * r);
             v[r][1] += f1 ? 0 : x0;
             v[r][0] = x0;
-            run = m ? total - static_cast<int64_t>(readlane_u64(static_cast<uint64_t>(at), 63 - __builtin_clzll(m)))
-                    : run + total;
+            run = m ? total - readlane_u64(at, 63 - __builtin_clzll(m)) : run + total;
             seen |= m != 0;
         }
         if (lane == 0) {
@@ -234,10 +236,10 @@ __global__ __launch_bounds__(kScThreads) void sg_rescan_kernel(SgArgs a) {
             wf[par][wave] = seen ? 1 : 0;
         }
         __syncthreads();
-        int64_t before = carry;   // running sum before this wave
+        uint64_t before = carry;   // running sum before this wave
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
-            const int64_t x = wv[par][w];
+            const uint64_t x = wv[par][w];
             const bool f = wf[par][w] != 0;
             carry = f ? x : carry + x;
             if (w < wave) before = carry;
@@ -245,14 +247,14 @@ __global__ __launch_bounds__(kScThreads) void sg_rescan_kernel(SgArgs a) {
 #pragma unroll
         for (int r = 0; r < kScRows; ++r) {
             const int64_t e = e0 + r * 2 * kWave;
-            i64x2 y;
+            u64x2 y;
             y.x = v[r][0] + ((open >> (2 * r)) & 1u ? before : 0);
             y.y = v[r][1] + ((open >> (2 * r + 1)) & 1u ? before : 0);
             if (whole && ovec) {
-                stream_store(reinterpret_cast<i64x2 *>(a.out + e), y);
+                stream_store(reinterpret_cast<u64x2 *>(a.out + e), y);
             } else {
-                if (e < hi_c) stream_store(a.out + e, static_cast<int64_t>(y.x));
-                if (e + 1 < hi_c) stream_store(a.out + e + 1, static_cast<int64_t>(y.y));
+                if (e < hi_c) stream_store(a.out + e, static_cast<uint64_t>(y.x));
+                if (e + 1 < hi_c) stream_store(a.out + e + 1, static_cast<uint64_t>(y.y));
             }
         }
     }
@@ -286,11 +288,11 @@ extern "C" int ixp_sgm_sum(const uint8_t *d_flags, const int64_t *d_xs, int64_t 
     if (n == 0) return IXP_OK;
     SgArgs a;
     a.flags = d_flags;
-    a.xs = d_xs;
-    a.out = d_out;
+    a.xs = reinterpret_cast<const uint64_t *>(d_xs);
+    a.out = reinterpret_cast<uint64_t *>(d_out);
     a.n = n;
     sg_geometry(n, &a.chunk, &a.chunks);
-    a.agg_v = static_cast<int64_t *>(ws);
+    a.agg_v = static_cast<uint64_t *>(ws);
     a.agg_f = reinterpret_cast<int32_t *>(static_cast<char *>(ws) + round_up(static_cast<size_t>(a.chunks) * 8, 256));
     hipStream_t st = as_stream(stream);
     const dim3 grid(static_cast<uint32_t>(a.chunks));
