@@ -243,6 +243,10 @@ size_t ixp_segmented_workspace(int64_t n, int64_t m, const ixp_tuning *tune);
  * synchronisation: capturable into a HIP graph.  Under IXP_ROW_SYNC_WAIT the
  * main kernel's workgroups wait on one another's published counts; the wait
  * is bounded, so no workgroup depends on another being resident.
+ * In place, where every row fits one tile from any start (at most tile - 3
+ * elements): out_keys may be `keys` in PARTITION mode, or a 32-bit out_idx may
+ * be `keys` in both modes; otherwise no output may overlap an input or another
+ * output.
  * Alignment (else IXP_EINVAL): keys and ws 16 bytes, out_idx 4 indices,
  * out_keys, d_flags_out and a flag predicate's array 4 bytes. */
 int ixp_segmented_partition(const void *keys, int32_t key_t, int64_t n,

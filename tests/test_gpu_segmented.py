@@ -527,3 +527,28 @@ def test_invalid_shape_that_asks_for_more_items_than_fit(m, mode):
         P.segmented_partition(keys, st, P.Pred.mod_eq(2, 0), mode, out_keys=out, out_idx=idx, seg_split=seg)
         assert P.segmented_error() == P._lib.IXP_EINVAL
         assert all(bool((t == -5).all()) for t in (out, idx, seg))
+
+
+@pytest.mark.parametrize("m", [1500, 9000, 20_000])
+@pytest.mark.parametrize("longest", [60, 4000])
+def test_rows_of_one_item_in_place(m, longest):
+    """Rows that fit one item may be partitioned in place, and 32-bit indices may
+    take the place of their keys in both modes, with shared items and without."""
+    g = np.random.default_rng(m + longest)
+    shape = g.integers(0, longest, m if longest < 100 else m // 10)
+    n = int(shape.sum())
+    x = W.int_keys(n, 136)
+    st = torch.from_numpy(shape).to(DEV)
+    pred, op = P.Pred.mod_eq(3, 1), O.Pred.mod_eq(3, 1)
+    for mode in (0, 1):
+        ys, idx, seg, _ = O.partition2L(x, shape, op, mode)
+        nout = n if mode == 0 else int(seg.sum())
+        for rep in range(3):
+            kt = torch.from_numpy(x).to(DEV)
+            ok, oi, ss, _ = P.segmented_partition(kt, st, pred, mode, out_idx=kt)
+            assert np.array_equal(oi.cpu().numpy(), idx) and np.array_equal(ss.cpu().numpy(), seg)
+            assert np.array_equal(ok.cpu().numpy()[:nout], ys[:nout])
+            if mode == 0:
+                kt = torch.from_numpy(x).to(DEV)
+                ok, oi, ss, _ = P.segmented_partition(kt, st, pred, mode, out_keys=kt)
+                assert np.array_equal(oi.cpu().numpy(), idx) and np.array_equal(ok.cpu().numpy(), ys)
