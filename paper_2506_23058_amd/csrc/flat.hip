@@ -13,18 +13,21 @@
 // Partition (three kernels on the caller's stream).  The falses cannot be
 // placed before T is known, so a counting pass comes first; it yields every
 // tile's true count, which makes a look-back unnecessary:
-//   count     -- one wave per tile (nontemporal vector loads, ballot +
-//                popcount), writes the tile's count;
-//   tile_scan -- one workgroup: exclusive scan of the tile counts (DPP wave
-//                scans), writes each tile's prefix, T and clears the error word;
+//   count     -- a workgroup per tile up to 8192 tiles, else a wave per run of
+//                tiles (vector loads, ballot + popcount): the tiles' counts, or
+//                their prefixes inside the run and the runs' totals;
+//   tile_scan -- one workgroup: exclusive scan of those counts or totals (DPP
+//                wave scans), writes T and clears the error word;
 //   scatter   -- one workgroup per tile: flags by ballot, in-tile ranks by
 //                mbcnt, the tile prefix by one load; indices written in input
 //                order with vector stores, keys staged in LDS in output order
 //                and written as the tile's two contiguous runs.
-// Up to 1024 tiles (n <= 2^22) skip the tile scan: one workgroup counts each
-// tile (a wave per 1024 elements), and each scatter workgroup adds up the tile
-// counts before its tile and in total itself.  Up to 32768 elements a partition
-// or filter is one launch, each workgroup counting the whole array (flat_one).
+// Both passes load past the caches, except where the Infinity Cache still holds
+// part of the keys for the second one (2^23 to 2^27 keys, 32-bit indices).
+// Up to 1024 tiles (n <= 2^22) skip the tile scan: each scatter workgroup adds
+// up the tile counts before its tile and in total itself.  Up to 32768 elements
+// a partition or filter is one launch, each workgroup counting the whole array
+// (flat_one), unless an output shares bytes with an input.
 // Filter (single pass, two kernels):
 //   init      -- clears the tile descriptors, ticket and error word;
 //   scan      -- tiles taken in ticket order; each publishes its count, finds
@@ -43,7 +46,8 @@ namespace {
 constexpr size_t kWsHeader = 256;   // ticket (u32), error word (i32), padding
 
 // Tile geometry.  Partition: 256 threads x 4 rows x 4 = 4096 elements per
-// tile (the count kernel uses the same tiles).  Filter: 1024 x 4 x 4 = 16384:
+// tile (the count kernel uses the same tiles).  Filter: 1024 x 4 x 4 = 16384,
+// from 2^25 elements on with 32-bit indices 1024 x 8 x 4 = 32768 (kBigFilter):
 // every filter tile takes one ticket from a single counter, whose atomics
 // serialise (~10 ns each), and its look-back must reach a published inclusive
 // prefix in one round, so fewer, larger tiles go faster.  Unaligned buffers
@@ -93,9 +97,8 @@ struct FlatArgs {
 };
 
 // A partition of at most this many tiles skips the one-workgroup tile scan:
-// one workgroup counts each tile (a wave per kSmallChunk elements), and every
-// scatter workgroup adds up the tile counts itself (4 words per thread) and
-// tile 0 writes T.
+// every scatter workgroup adds up the tile counts itself (4 words per thread)
+// and tile 0 writes T.
 constexpr int64_t kSmallTiles = 1024;
 constexpr int64_t kSmallChunk = 1024;
 

@@ -191,8 +191,8 @@ struct TileV {
 
     // Ranks inside this wave's run.  Per row, the counts of every class but
     // the last are packed 9 bits each into 32 bits (a row of a wave holds at
-    // most 256 elements) and scanned over the lanes with shuffles; the rank
-    // of a last-class element is its position minus the earlier elements of
+    // most 256 elements) and scanned over the lanes by DPP (all lanes take
+    // part); the rank of a last-class element is its position minus the earlier elements of
     // the other classes (the valid elements of a run form a prefix).
     __device__ static __forceinline__ uint32_t onehot9(uint32_t c, bool ok) {
         return (ok && c < static_cast<uint32_t>(V - 1)) ? (1u << (9 * c)) : 0u;

@@ -18,8 +18,10 @@
 //   pairs_scan   -- one workgroup: exclusive scan of the chunks' counts;
 //   pairs_compact - one workgroup per chunk: copies the kept entries.
 // 28 bytes per entry in pairs_bucket, 24 to 28 in pairs_reduce, 4 in pairs_mark,
-// 16 to 32 in pairs_compact; for 2^26 entries over 2^24 vertices 353, 601, 49 and
-// 262 us (5.3, 2.9, 5.5 and 5.1 TB/s): 1255 us in all, 5130 step by step.
+// 16 to 32 in pairs_compact; for 2^26 entries over 2^24 vertices 356, 649, 46, 5 and
+// 260 us by rocprofv3 (5.3, 2.7, 5.8, - and 5.1 TB/s); the call takes 1255 us, step by
+// step 5130.  (The times of variants below are those of HIP events, without a
+// profiler: 601 us for the same pairs_reduce.)
 #include "device.hpp"
 #include "host.hpp"
 

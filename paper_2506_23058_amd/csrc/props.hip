@@ -1290,7 +1290,8 @@ __device__ __forceinline__ void props_verdicts(const PropsArgs &a, ixp_verdict *
 
 // True for the workgroup that passes here last of those that have `items` to go
 // over.  They have made atomics on the state and no stores, so waiting for those
-// orders them: a fence in each of 2048 workgroups, with every workgroup counted,
+// orders them (so props_second, props_missing and fp_repeats may write nothing but
+// such atomics, and props_verdicts reads past the caches): a fence in each of 2048 workgroups, with every workgroup counted,
 // cost 100 us (a missing value among 5000 entries: 130 us, so 18.4).
 __device__ __forceinline__ bool last_workgroup(const PropsArgs &a, int64_t items) {
     __shared__ int last;

@@ -584,7 +584,7 @@ __global__ __launch_bounds__(256) void seg_count_kernel(SegArgs a, Pred pred) {
 // ------------------------------------------------------------------- scan --
 // Exclusive scan of the item counts into prefix[0..num_items]; items of rows
 // counted in place (partition, one item) count 0.  Workgroups take chunks of
-// 8192 counts in ticket order, scan them (8 per thread, wave shuffles, LDS)
+// 8192 counts in ticket order, scan them (8 per thread, DPP wave scans, LDS)
 // and chain the chunks with a decoupled look-back.
 __global__ __launch_bounds__(1024) void seg_scan_items_kernel(SegArgs a) {
     __shared__ int64_t lds[16];
@@ -1028,7 +1028,7 @@ __global__ __launch_bounds__(kPackThreads) void seg_count_packed_kernel(SegArgs 
 // Workgroups take items round-robin (item = blockIdx.x + k * gridDim.x: no
 // shared queue counter, whose serialised atomics would cost ~10 ns per
 // item); a grid smaller than the item count makes them persistent.  Wave 0
-// prefetches the next item's 48-byte descriptor, one 8-byte word per lane,
+// prefetches the next item's 64-byte descriptor, one 8-byte word per lane,
 // while the workgroup processes the current one.
 //
 // Each wave owns the LDS run of its own elements: right after ranking them it

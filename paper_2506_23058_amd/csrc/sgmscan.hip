@@ -9,7 +9,7 @@
 //             chunk finds the last flag from the flag bytes, then sums only
 //             the values from there;
 //   scan   -- one workgroup: exclusive scan of the C aggregates under the
-//             lifted operator (8 per thread, wave shuffles, LDS);
+//             lifted operator (8 per thread, DPP wave scans, LDS);
 //   rescan -- one workgroup per chunk: a wave holds rows of 128 consecutive
 //             elements, two per lane, and hands its last running sum to the
 //             waves after it.

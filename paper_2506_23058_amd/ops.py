@@ -580,8 +580,14 @@ class SmallestPairs:
     outputs (synchronising)."""
 
     # the fused call moves every entry through memory once more, the step by step
-    # calls make two random accesses an entry: 2^19 entries 58 against 49 us,
-    # 2^20 entries 62 against 80
+    # calls make two accesses an entry to its vertex.  Random endpoints, four entries a
+    # vertex, fused against step by step, us: 600,000 entries 43 / 55, 786,432 49 / 65,
+    # 2^20 53 / 80, 2^26 1250 / 5150.  Sorted endpoints, whose accesses share lines, draw even
+    # later: 600,000 56 / 47, 786,432 60 / 55, 1.2e6 72 / 74, 2^22 129 / 216 (one entry a vertex
+    # 786,432 61 / 50, 1.5e6 77 / 77), so the line lies between the two.
+    # Few or heavy vertices, one workgroup's share here, queue the atomics there: 2^20
+    # entries of 1 / 16 / 256 vertices 1270 / 122 / 53 against 11,900 / 2590 / 388; one vertex
+    # with a tenth of 2^26 entries 9.2 ms against 79.
     FUSED_MIN = 3 << 18
 
     def __init__(self, n_verts: int, n_es: int, es: torch.Tensor, is_: torch.Tensor):
