@@ -1503,17 +1503,11 @@ bool packs(int64_t n, int64_t m, const SegGeom &g) {
            n < (int64_t{1} << 42);
 }
 
-// Enough for every call of no more elements and no more rows as well: some of
-// those have an item per row (fewer than pack_rows rows, or a mean above
-// kPackMean) and so more records than a packed call of more rows.
+// With room for an item per row also where rows are packed: calls of fewer rows, of
+// larger tiles and the helpers may take one, and a workspace sized once, for the
+// largest call, serves them all.
 size_t seg_workspace(int64_t n, int64_t m, const SegGeom &g) {
-    const bool pack = packs(n, m, g);
-    int64_t mi = seg_max_items(n, m, g.tile(), pack);
-    if (pack) {
-        const int64_t rows = g.pack_rows - 1 > n / (kPackMean + 1) ? g.pack_rows - 1 : n / (kPackMean + 1);
-        const int64_t apart = seg_max_items(n, rows < m ? rows : m, g.tile(), false);
-        if (apart > mi) mi = apart;
-    }
+    const int64_t mi = seg_max_items(n, m, g.tile(), false);
     return kSegHeader + round_up(static_cast<size_t>(m + 1) * 8, 256) * 2 +
            round_up(static_cast<size_t>(mi) * sizeof(SegItem), 256) +
            round_up(static_cast<size_t>(mi + 1) * 8, 256) + round_up(static_cast<size_t>(mi) * 8, 256) +

@@ -141,7 +141,7 @@ def test_a_segmented_workspace_serves_smaller_calls():
     rng = random.Random(5)
     edges = [1, 100, 2047, 2048, 2049, 8191, 8192, 16384, 16385, 41_667, 1 << 20]
     tune = lib.ixp_segmented_workspace.argtypes[2]._type_()
-    tune.block, tune.rows = 512, 2
+    tune.block, tune.rows = 512, 4   # a larger tile than the default
     for t in (None, ctypes.byref(tune)):
         for _ in range(4000):
             m = rng.choice(edges) if rng.random() < 0.5 else int(2 ** rng.uniform(0, 22))
@@ -150,6 +150,9 @@ def test_a_segmented_workspace_serves_smaller_calls():
             n2 = rng.choice([n, rng.randint(0, n), min(n, 768 * m2), min(n, 769 * m2)])
             assert lib.ixp_segmented_workspace(n2, m2, t) <= lib.ixp_segmented_workspace(n, m, t), (n, m, n2, m2)
             assert lib.ixp_mk_ii_workspace(n2, m2) <= lib.ixp_mk_ii_workspace(n, m), (n, m, n2, m2)
+            assert lib.ixp_segmented_workspace(n, m, ctypes.byref(tune)) <= lib.ixp_segmented_workspace(n, m, None)
+            # the helpers' is that of a segmented call of the default tiling
+            assert lib.ixp_mk_ii_workspace(n, m) == lib.ixp_segmented_workspace(n, m, None), (n, m)
 
 
 def test_a_check_workspace_serves_narrower_calls():
